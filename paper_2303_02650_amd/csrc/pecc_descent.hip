@@ -52,12 +52,15 @@ constexpr float kFarCoord = 3.0e18f;      // (3e18)^2 * 2 is finite in FP32
 // j at storage (hd + j) mod 10) is contiguous from offset hd.
 constexpr int kRS = 4 * kMM + 1;
 
-template <int ELL>
+// ALL: every wave decides (the dense batch descent, which also lends the list
+// build its pass buffer for the sorted positions).
+template <int ELL, bool ALL>
 struct DescentShared {
     float2 pos[kMaxN + 1];         // pos[kMaxN]: the far point
     int cell_start[kMaxCells + 1];
     uint16_t cell_circ[kMaxN];
     uint16_t slot_tmp[kMaxN];
+    float2 psort[ALL ? 1 : kMaxN + 4];   // positions in cell order (see build_lists)
     uint16_t list[ELL][kMaxN];     // slot-major: lanes read consecutive entries; byte offsets into pos
     uint8_t  list_n[kMaxN];
     float red[2][kDW][kWave];
@@ -315,7 +318,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
     // every wave decides only in the dense mode
     static_assert(SOLO || DENSE, "the limited-memory modes decide on one wave");
     constexpr int ELL = SEQ ? kEllSeq : kEll;
-    __shared__ DescentShared<ELL> sh;
+    __shared__ DescentShared<ELL, DENSE> sh;
     __shared__ std::conditional_t<DENSE, DenseShared, std::conditional_t<SEQ, SeqShared, NoShared>> sq;
     const int tid = threadIdx.x;
     // (lane ids are recomputed per evaluation from an opaque copy of tid)
@@ -460,6 +463,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
         int cur = 0;                   // Bm buffer in use
         int tcount = 0;                // evaluations so far (flag parity)
         bool overflow = false;         // list did not fit: sweep the cell grid
+        int mlist = 0;                 // longest list of this wave's circles
         int64_t pair_mine = 0;         // listed pairs i<j swept, summed over evaluations (uniform)
         int rebuilds = 0, evals = 0;
         bool fp64 = false;
@@ -972,101 +976,26 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
             if (tid == 0) sh.flag[par ^ 1] = 0;
             if (sh.flag[par]) {
                 // ---- neighbor list rebuild at the positions in sh.pos -------
-                if (tid == 0) sh.over = 0;    // set again below only after bin_circles' barriers
+                if (tid == 0) sh.over = 0;    // set again below only after sort_cells' barriers
                 if (tid <= kMaxSeqBatches) sh.npair[tid] = 0;
-                bin_circles<kDB>(sh.pos, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp,
-                                 sh.scan_tmp);
                 // ascending circle index inside every cell: lists (cells in
                 // row order, then index) are then a function of the
                 // positions alone, and so is every sum over them
-                for (int cc = tid; cc < grid.nc * grid.nc; cc += kDB) {
-                    const int a = sh.cell_start[cc], z = sh.cell_start[cc + 1];
-                    for (int q = a + 1; q < z; ++q) {
-                        const uint16_t key = sh.cell_circ[q];
-                        int t = q - 1;
-                        while (t >= a && sh.cell_circ[t] > key) { sh.cell_circ[t + 1] = sh.cell_circ[t]; --t; }
-                        sh.cell_circ[t + 1] = key;
-                    }
-                }
-                __syncthreads();
-                // one pass: every circle writes its neighbors into its own
-                // ELL slots; more than ELL switches this list epoch to
-                // sweeping the cell grid instead
-                int up_c[kCPT] = {};
+                float2 *psort;
+                if constexpr (DENSE) psort = reinterpret_cast<float2 *>(sq.part);
+                else psort = sh.psort;
+                int own[kCPT], up_c[kCPT];
+                sort_cells<kDB, kCPT>(tid, xt, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp,
+                                      psort, sh.scan_tmp, own);
+                // every circle writes its neighbors into its own ELL slots;
+                // more than ELL switches this list epoch to sweeping the
+                // cell grid instead
+                mlist = build_lists<kDB, kCPT, ELL, kMaxN>(
+                    tid, xt, act, own, grid, sh.cell_start, sh.cell_circ, psort, A.c2,
+                    &sh.list[0][0], sh.list_n, kFarOff, up_c, &sh.over);
 #pragma unroll
-                for (int c = 0; c < kCPT; ++c) {
-                    const int i = tid + c * kDB;
-                    // the candidates are the circles of the 3 x 3 cells
-                    // around the circle's own, in cell order: three cell rows
-                    // (start, length), read together, indexed as one run
-                    int ra[3], rl[3];
-                    {
-                        const int cx = cell_coord(xt[c].x, grid), cy = cell_coord(xt[c].y, grid);
-                        const int y0 = cy > 0 ? cy - 1 : 0, y1 = cy < grid.nc - 1 ? cy + 1 : grid.nc - 1;
-                        const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < grid.nc - 1 ? cx + 1 : grid.nc - 1;
-#pragma unroll
-                        for (int r = 0; r < 3; ++r) {
-                            const bool row = act[c] && y0 + r <= y1;
-                            const int yy = y0 + r <= y1 ? y0 + r : y0;
-                            const int a = sh.cell_start[yy * grid.nc + x0];
-                            const int z = sh.cell_start[yy * grid.nc + x1 + 1];
-                            ra[r] = row ? a : 0;
-                            rl[r] = row ? z - a : 0;
-                        }
-                    }
-                    const int K = rl[0] + rl[1] + rl[2];
-                    // the wave walks its longest run, four candidates per
-                    // step with their index and position reads in flight
-                    const int kmax = wave_max_dpp(K);
-                    int m = 0, up = 0;
-                    for (int k0 = 0; k0 < kmax; k0 += 4) {
-                        int jv[4];
-                        bool ok[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int k = k0 + u;
-                            ok[u] = k < K;
-                            const int t = k < rl[0]         ? ra[0] + k
-                                        : k < rl[0] + rl[1] ? ra[1] + (k - rl[0])
-                                                            : ra[2] + (k - rl[0] - rl[1]);
-                            const int jj = sh.cell_circ[ok[u] ? t : 0];
-                            jv[u] = ok[u] ? jj : i;
-                        }
-                        float2 pv[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) pv[u] = sh.pos[jv[u]];
-                        // the FP32 test decides outside a band of +-1e-5
-                        // around the cutoff, the FP64 one inside it (the
-                        // near_cut predicate; the band is rare, so one uniform
-                        // branch covers the wave's four candidates)
-                        bool nb[4], band[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const float dx = xt[c].x - pv[u].x, dy = xt[c].y - pv[u].y;
-                            const float l2 = dx * dx + dy * dy;
-                            const bool cand = ok[u] && jv[u] != i;
-                            nb[u] = cand && l2 < c2lo;
-                            band[u] = cand && l2 >= c2lo && l2 <= c2hi;
-                        }
-                        if (__builtin_amdgcn_ballot_w64(band[0] || band[1] || band[2] || band[3])) {
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                if (band[u]) nb[u] = near64(xt[c], pv[u], A.c2);
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            if (nb[u] && m < ELL) sh.list[m][i] = (uint16_t)(jv[u] * (int)sizeof(float2));
-                            m += nb[u] ? 1 : 0;
-                            up += (nb[u] && jv[u] > i) ? 1 : 0;
-                        }
-                    }
-                    if (act[c]) {
-                        if (m > ELL) sh.over = 1;
-                        sh.list_n[i] = (uint8_t)(m < ELL ? m : ELL);
-                        up_c[c] = up;
-                        xr[c] = xt[c];
-                    }
-                }
+                for (int c = 0; c < kCPT; ++c)
+                    if (act[c]) xr[c] = xt[c];
                 // listed pairs from their lower index, per wave, then one
                 // integer add per wave (the same totals in any order): in all,
                 // and per batch for the batch descent
@@ -1082,21 +1011,6 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                             if (lane == 0 && v != 0) atomicAdd(&sh.npair[q], v);
                         }
                     }
-                }
-                // pad every list with the far point up to the longest list
-                // of the wave (the sweep's trip count; circles past n count
-                // as empty lists)
-                {
-                    int mlen[kCPT], mw = 0;
-#pragma unroll
-                    for (int c = 0; c < kCPT; ++c) {
-                        mlen[c] = act[c] ? (int)sh.list_n[tid + c * kDB] : 0;
-                        mw = mlen[c] > mw ? mlen[c] : mw;
-                    }
-                    mw = wave_max_dpp(mw);
-#pragma unroll
-                    for (int c = 0; c < kCPT; ++c)
-                        for (int t = mlen[c]; t < mw; ++t) sh.list[t][tid + c * kDB] = (uint16_t)kFarOff;
                 }
                 ++rebuilds;
                 __syncthreads();
@@ -1126,14 +1040,15 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                 // trip count: the longest swept list of the wave (uniform);
                 // shorter lists are padded with the far point
                 bool use[kCPT];
-                int mm = 0;
+                int mm = mlist;
 #pragma unroll
-                for (int c = 0; c < kCPT; ++c) {
-                    use[c] = act[c] && inb[c];
-                    const int mcc = use[c] ? (int)sh.list_n[tid + c * kDB] : 0;
-                    mm = mcc > mm ? mcc : mm;
+                for (int c = 0; c < kCPT; ++c) use[c] = act[c] && inb[c];
+                if (SEQ && masked) {
+                    mm = 0;
+#pragma unroll
+                    for (int c = 0; c < kCPT; ++c) mm = max(mm, use[c] ? (int)sh.list_n[tid + c * kDB] : 0);
+                    mm = wave_max_dpp(mm);
                 }
-                mm = wave_max_dpp(mm);
                 // one copy of the loop per (unit-circle energy, FP64 terms)
                 // regime, so neither costs instructions where it is off.  The
                 // list entries of slot t + 1 are read while slot t is summed,

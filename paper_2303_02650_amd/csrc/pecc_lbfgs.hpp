@@ -5,6 +5,8 @@
 #pragma once
 #include "pecc_device.hpp"
 
+#include <type_traits>
+
 namespace pecc {
 
 constexpr int kMM = 10;                   // history slots (max m)
@@ -188,6 +190,19 @@ __device__ __forceinline__ int wave_sum_int(int v)
     v += dppi<kDppBcast15, 0xa>(v);
     v += dppi<kDppBcast31, 0xc>(v);
     return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Inclusive prefix sum of an int over the 64 lanes (row shifts inside the
+// 16-lane rows, then the row totals passed on).
+__device__ __forceinline__ int wave_scan_dpp(int v)
+{
+    v += dppi<0x111>(v);                 // row_shr 1, 2, 4, 8
+    v += dppi<0x112>(v);
+    v += dppi<0x114>(v);
+    v += dppi<0x118>(v);
+    v += dppi<kDppBcast15, 0xa>(v);
+    v += dppi<kDppBcast31, 0xc>(v);
+    return v;
 }
 
 // The same sum for a double: each DPP step moves the two 32-bit halves.
@@ -378,6 +393,252 @@ __device__ __forceinline__ bool near_cut(float2 a, float2 b, float c2lo, float c
     if (l2 < c2lo) return true;
     if (l2 > c2hi) return false;
     return near64(a, b, c2);
+}
+
+// ---------------------------------------------------------------------------
+// Counting sort of the n circles of one instance into grid cells, ascending
+// circle index inside every cell, with the positions copied in that order:
+//   cell_start [ncell + 1]  first slot of each cell
+//   cell_circ  [n]          circle of each slot
+//   psort      [n]          its position (the list build reads a cell row as
+//                           one contiguous run of them, without the index)
+//   own[u]                  slot of circle tid + u * BLOCK
+// tmp: n entries of scratch (by slot, in arrival order); scan_tmp: BLOCK / 64
+// ints.  The order inside a cell comes from ranking each circle among its
+// cell's circles (one or two of them at the cutoff's cell size), which every
+// circle does at once; sorting each cell by one thread left most lanes idle
+// behind chains of dependent LDS accesses.  The scan sums the cells a
+// thread owns, then the lanes by DPP: one barrier.  Ends with a barrier.
+// ---------------------------------------------------------------------------
+template <int BLOCK, int CPT>
+__device__ __forceinline__ void sort_cells(int tid, const float2 (&x)[CPT], int n, const Grid &g,
+                                           int *cell_start, uint16_t *cell_circ, uint16_t *tmp,
+                                           float2 *psort, int *scan_tmp, int (&own)[CPT])
+{
+    constexpr int NW = BLOCK / kWave;
+    const int ncell = g.nc * g.nc;
+    for (int c = tid; c <= ncell; c += BLOCK) cell_start[c] = 0;
+    __syncthreads();
+    int cell[CPT], slot[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        cell[u] = slot[u] = 0;
+        if (tid + u * BLOCK < n) {
+            cell[u] = cell_of(x[u], g);
+            slot[u] = atomicAdd(&cell_start[cell[u]], 1);
+        }
+    }
+    __syncthreads();
+    const int ch = (ncell + BLOCK - 1) / BLOCK;
+    const int c0 = tid * ch, c1 = c0 + ch < ncell ? c0 + ch : ncell;
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += cell_start[c];
+    const int inc = wave_scan_dpp(sum);
+    int run = inc - sum;
+    if constexpr (NW > 1) {
+        if ((tid & (kWave - 1)) == kWave - 1) scan_tmp[tid / kWave] = inc;
+        __syncthreads();
+        const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+#pragma unroll
+        for (int q = 0; q < NW - 1; ++q) run += q < w ? scan_tmp[q] : 0;
+    }
+    for (int c = c0; c < c1; ++c) {
+        const int v = cell_start[c];
+        cell_start[c] = run;
+        run += v;
+    }
+    if (tid == 0) cell_start[ncell] = n;
+    __syncthreads();
+    int a[CPT], z[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        a[u] = cell_start[cell[u]];
+        z[u] = cell_start[cell[u] + 1];
+        if (tid + u * BLOCK < n) tmp[a[u] + slot[u]] = (uint16_t)(tid + u * BLOCK);
+        else z[u] = a[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        const int i = tid + u * BLOCK;
+        int r = a[u];
+        for (int t = a[u]; t < z[u]; ++t) r += (int)tmp[t] < i ? 1 : 0;
+        own[u] = r;
+        if (i < n) {
+            cell_circ[r] = (uint16_t)i;
+            psort[r] = x[u];
+        }
+    }
+    __syncthreads();
+}
+
+// Slots of the 3 x 3 cells around the cell of p: three cell rows (first slot,
+// length; rows outside the grid are empty); own: the slot of p's circle, self
+// receives its place in the run of the three rows.
+__device__ __forceinline__ void cell_rows(float2 p, bool act, int own, const Grid &g,
+                                          const int *cell_start, int (&ra)[3], int (&rl)[3],
+                                          int &self)
+{
+    const int cx = cell_coord(p.x, g), cy = cell_coord(p.y, g);
+    const int y0 = cy > 0 ? cy - 1 : 0, y1 = cy < g.nc - 1 ? cy + 1 : g.nc - 1;
+    const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < g.nc - 1 ? cx + 1 : g.nc - 1;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const bool row = act && y0 + r <= y1;
+        const int yy = y0 + r <= y1 ? y0 + r : y0;
+        const int a = cell_start[yy * g.nc + x0];
+        const int z = cell_start[yy * g.nc + x1 + 1];
+        ra[r] = row ? a : 0;
+        rl[r] = row ? z - a : 0;
+    }
+    self = cy > y0 ? rl[0] + own - ra[1] : own - ra[0];
+}
+
+// Neighbor lists of a workgroup's circles (tid + c * BLOCK) into ELL slots,
+// slot-major (list[t * NMAX + i]: byte offset of the t-th neighbor in the
+// position array), in the order of the sorted cells, every list padded with
+// far_off up to the longest of the wave; list_n: list lengths.  Neighbor: the
+// predicate near64 with c2, decided in FP32 outside a band of 1e-6 c2 around
+// it (the FP32 distance is within 4e-7).  Returns the wave's longest list (its
+// pad length); up: listed neighbors with a higher index; *over is set when a
+// list does not fit.
+//
+// Bound by instruction issue (two waves per SIMD): about 13 candidates per
+// circle, but 20 to 30 for the wave's longest run, so the candidates' part is
+// kept small -- an FP32 distance and one mask bit each, from consecutive
+// sorted positions -- and everything that only a neighbor needs (its index,
+// the list write) runs over the mask bits, at most 7 or 8 per wave.  The FP64
+// predicate runs for the whole wave when any of its distances falls in the
+// band (at n = 1000 about one wave in a thousand).  The candidate-by-candidate
+// loop this replaces tested, masked and stored about 40 instructions per
+// candidate: a 256 x n = 1000 descent 30.1 -> 28.1 ms, 448 SED candidates of
+// n = 300 .. 1000 17.7 -> 16.8 ms, one start of n = 20 446 -> 405 us.
+template <int BLOCK, int CPT, int ELL, int NMAX>
+__device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], const bool (&act)[CPT],
+                                           const int (&own)[CPT], const Grid &g,
+                                           const int *cell_start, const uint16_t *cell_circ,
+                                           const float2 *psort, double c2, uint16_t *list,
+                                           uint8_t *list_n, int far_off, int (&up)[CPT], int *over)
+{
+    int ra[CPT][3], rl[CPT][3], self[CPT], cnt[CPT];
+    int kmax[3] = {0, 0, 0};
+    bool fits = true;              // three runs of at most 32, 64 candidates in all
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+        cell_rows(x[c], act[c], own[c], g, cell_start, ra[c], rl[c], self[c]);
+        cnt[c] = up[c] = 0;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) kmax[r] = max(kmax[r], rl[c][r]);
+        fits = fits && rl[c][0] + rl[c][1] + rl[c][2] <= 64;
+    }
+#pragma unroll
+    for (int r = 0; r < 3; ++r) kmax[r] = wave_max_dpp(kmax[r]);
+    int m = 0;
+    if (max(kmax[0], max(kmax[1], kmax[2])) <= 32 && !__builtin_amdgcn_ballot_w64(!fits)) {
+        unsigned long long mask[CPT];
+        const float c2f = (float)c2, band = c2f * 1e-6f;
+        float dmin = 3.0e38f;
+        auto scan = [&](auto exact) {
+            unsigned mr[CPT][3];
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) mr[c][r] = 0;
+                for (int k0 = 0; k0 < kmax[r]; k0 += 4) {
+                    float2 pv[CPT][4];
+                    unsigned bits[CPT];
+#pragma unroll
+                    for (int c = 0; c < CPT; ++c) {
+                        // past a run's end: any readable position (psort has
+                        // NMAX + 4), its bits are cut off below
+                        const float2 *src = psort + min(ra[c][r] + k0, NMAX);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) pv[c][u] = src[u];
+                        bits[c] = 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int c = 0; c < CPT; ++c) {
+                            bool nb;
+                            if constexpr (decltype(exact)::value) {
+                                nb = near64(x[c], pv[c][u], c2);
+                            } else {
+                                const float dx = x[c].x - pv[c][u].x, dy = x[c].y - pv[c][u].y;
+                                const float t = dx * dx + dy * dy - c2f;
+                                nb = t < 0.f;
+                                dmin = fminf(dmin, fabsf(t));
+                            }
+                            bits[c] |= nb ? 1u << u : 0u;
+                        }
+#pragma unroll
+                    for (int c = 0; c < CPT; ++c) mr[c][r] |= bits[c] << k0;
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                mask[c] = 0;
+#pragma unroll
+                for (int r = 2; r >= 0; --r) {
+                    const unsigned keep = rl[c][r] < 32 ? (1u << rl[c][r]) - 1u : ~0u;
+                    mask[c] = (mask[c] << rl[c][r]) | (unsigned long long)(mr[c][r] & keep);
+                }
+                if (act[c]) mask[c] &= ~(1ull << self[c]);
+            }
+        };
+        scan(std::false_type{});
+        if (__builtin_amdgcn_ballot_w64(dmin <= band)) scan(std::true_type{});
+        // neighbors: one mask bit of every circle per turn
+        for (;; ++m) {
+            bool any = false;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) any = any || mask[c] != 0;
+            if (!__builtin_amdgcn_ballot_w64(any)) break;
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                const int i = tid + c * BLOCK;
+                const bool has = mask[c] != 0;
+                const int k = __builtin_ctzll(has ? mask[c] : 1ull);
+                mask[c] &= mask[c] - 1;
+                const int t = k < rl[c][0]              ? ra[c][0] + k
+                            : k < rl[c][0] + rl[c][1] ? ra[c][1] + (k - rl[c][0])
+                                                      : ra[c][2] + (k - rl[c][0] - rl[c][1]);
+                const int j = cell_circ[has ? t : 0];
+                if (m < ELL) list[m * NMAX + i] = (uint16_t)(has ? j * (int)sizeof(float2) : far_off);
+                cnt[c] += has ? 1 : 0;
+                up[c] += (has && j > i) ? 1 : 0;
+            }
+        }
+    } else {
+        // a crowded neighborhood: candidate by candidate
+        int longest = 0;
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            const int i = tid + c * BLOCK;
+            for (int r = 0; r < 3; ++r) {
+                for (int t = ra[c][r]; t < ra[c][r] + rl[c][r]; ++t) {
+                    if (t != own[c] && near64(x[c], psort[t], c2)) {
+                        const int j = cell_circ[t];
+                        if (cnt[c] < ELL) list[cnt[c] * NMAX + i] = (uint16_t)(j * (int)sizeof(float2));
+                        ++cnt[c];
+                        up[c] += j > i ? 1 : 0;
+                    }
+                }
+            }
+            longest = max(longest, cnt[c]);
+        }
+        m = wave_max_dpp(longest);
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+            for (int t = cnt[c]; t < min(m, ELL); ++t) list[t * NMAX + tid + c * BLOCK] = (uint16_t)far_off;
+    }
+#pragma unroll
+    for (int c = 0; c < CPT; ++c)
+        if (act[c]) {
+            if (cnt[c] > ELL) *over = 1;
+            list_n[tid + c * BLOCK] = (uint8_t)min(cnt[c], ELL);
+        }
+    return min(m, ELL);
 }
 
 // FP32 pair term of circle i (at q) with circle j (at pj): energy on the
