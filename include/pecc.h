@@ -24,8 +24,9 @@
  *    calling thread.  Per-instance numerical outcomes (non-finite input, a
  *    line search that cannot decrease E, ...) are reported in result
  *    structs, never as return codes.  Device-side argument problems that
- *    the host cannot see (n_b > PECC_MAX_N, decreasing offsets) make the
- *    affected instance report PECC_STATUS_BAD_INSTANCE or an empty result.
+ *    the host cannot see (n_b > PECC_MAX_N, n_b > max_n, decreasing offsets)
+ *    make the affected instance report PECC_STATUS_BAD_INSTANCE or an empty
+ *    result.
  */
 #ifndef PECC_H
 #define PECC_H

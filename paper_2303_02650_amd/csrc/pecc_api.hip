@@ -225,9 +225,8 @@ int pecc_lbfgs_descend(const pecc_instances *inst, float *xy, const pecc_descent
     pecc_lbfgs_descend_workspace_size(inst, &need);
     if (!workspace || workspace_bytes < need)
         return fail(PECC_ERR_WORKSPACE, "%s: workspace needs %zu bytes", fn, need);
-    const int grid = pecc::descend_grid(inst->num_instances);
     return check_hip(pecc::launch_descend(inst->offset, inst->R, inst->R64, xy, inst->num_instances,
-                                          inst->total_n, a, out, (int32_t *)workspace, grid,
+                                          inst->max_n, inst->total_n, a, out, (int32_t *)workspace,
                                           stream),
                      fn);
 }
@@ -247,10 +246,9 @@ int pecc_lbfgs_descend_noalloc(const pecc_instances *inst, float *xy,
     pecc::DescentArgs a;
     rc = descent_args(p, fn, &a);
     if (rc) return rc;
-    const int grid = pecc::descend_grid(inst->num_instances);
     return check_hip(pecc::launch_descend_noalloc(inst->offset, inst->R, inst->R64, xy,
-                                                  inst->num_instances, inst->total_n, a, out,
-                                                  grid, stream),
+                                                  inst->num_instances, inst->max_n,
+                                                  inst->total_n, a, out, stream),
                      fn);
 }
 
@@ -280,10 +278,9 @@ int pecc_adjust_container(const pecc_instances *inst, float *xy, const pecc_desc
     pecc_lbfgs_descend_workspace_size(inst, &need);
     if (!workspace || workspace_bytes < need)
         return fail(PECC_ERR_WORKSPACE, "%s: workspace needs %zu bytes", fn, need);
-    const int grid = pecc::descend_grid(inst->num_instances);
     return check_hip(pecc::launch_adjust(inst->offset, inst->R, xy, inst->num_instances,
-                                         inst->total_n, a, R_out, out, (int32_t *)workspace, grid,
-                                         stream),
+                                         inst->max_n, inst->total_n, a, R_out, out,
+                                         (int32_t *)workspace, stream),
                      fn);
 }
 
@@ -331,9 +328,9 @@ int pecc_gbo_kbatch_descend(const pecc_instances *inst, float *xy, const int32_t
     pecc_lbfgs_descend_workspace_size(inst, &need);
     if (!workspace || workspace_bytes < need)
         return fail(PECC_ERR_WORKSPACE, "%s: workspace needs %zu bytes", fn, need);
-    const int grid = pecc::descend_grid(inst->num_instances);
     return check_hip(pecc::launch_seq(inst->offset, inst->R, inst->R64, xy, inst->num_instances,
-                                      inst->total_n, a, batch_of, out, (int32_t *)workspace, grid,
+                                      inst->max_n, inst->total_n, a, batch_of, out,
+                                      (int32_t *)workspace,
                                       stream),
                      fn);
 }
@@ -400,10 +397,9 @@ int pecc_gbo_kbatch_bfgs_descend(const pecc_instances *inst, float *xy, const in
     size_t q = 0;
     pecc_lbfgs_descend_workspace_size(inst, &q);
     float *H = reinterpret_cast<float *>(static_cast<char *>(workspace) + q);
-    const int grid = pecc::descend_grid(inst->num_instances);
     return check_hip(pecc::launch_dense(inst->offset, inst->R, inst->R64, xy, inst->num_instances,
                                         inst->total_n, a, batch_of, H, out, (int32_t *)workspace,
-                                        grid, stream),
+                                        stream),
                      fn);
 }
 

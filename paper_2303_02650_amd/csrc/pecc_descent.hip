@@ -31,9 +31,7 @@
 
 namespace pecc {
 
-constexpr int kDB = 512;                  // threads per workgroup
-constexpr int kDW = kDB / kWave;          // waves per workgroup
-constexpr int kCPT = kMaxN / kDB;         // circles per thread
+constexpr int kFullBlock = 512;           // threads per workgroup for n <= kMaxN
 constexpr int kEll = 24;                  // neighbor slots per circle (ELL list)
 constexpr int kEllSeq = 32;               // ... in the batch descent (l_cut up to 4)
 
@@ -42,7 +40,7 @@ enum : int { kModeWhole = 0, kModeAdj = 1, kModeSeq = 2, kModeDense = 3 };
 // Byte offset (into the position array) of the far point that pads every
 // neighbor list up to the longest list of its wave: a pair with it has no
 // overlap, so its terms add exact zeros and the list loop needs no test.
-constexpr int kFarOff = kMaxN * (int)sizeof(float2);
+constexpr int far_off(int nmax) { return nmax * (int)sizeof(float2); }
 constexpr float kFarCoord = 3.0e18f;      // (3e18)^2 * 2 is finite in FP32
 
 // Whole-instance descent: row length of the Gram ring in LDS.  Row r (the
@@ -52,26 +50,28 @@ constexpr float kFarCoord = 3.0e18f;      // (3e18)^2 * 2 is finite in FP32
 // j at storage (hd + j) mod 10) is contiguous from offset hd.
 constexpr int kRS = 4 * kMM + 1;
 
-// ALL: every wave decides (the dense batch descent, which also lends the list
-// build its pass buffer for the sorted positions).
-template <int ELL, bool ALL>
+// NMAX: circles the workgroup can hold; NW: its waves; ALL: every wave
+// decides (the dense batch descent), on the double-buffered Gram matrix; it
+// also lends the list build its pass buffer for the sorted positions.
+template <int ELL, int NMAX, int NW, bool ALL>
 struct DescentShared {
-    float2 pos[kMaxN + 1];         // pos[kMaxN]: the far point
+    static constexpr int kBm = ALL ? kNB * kNB : 1;
+    float2 pos[NMAX + 1];         // pos[NMAX]: the far point
     int cell_start[kMaxCells + 1];
-    uint16_t cell_circ[kMaxN];
-    uint16_t slot_tmp[kMaxN];
-    float2 psort[ALL ? 1 : kMaxN + 4];   // positions in cell order (see build_lists)
-    uint16_t list[ELL][kMaxN];     // slot-major: lanes read consecutive entries; byte offsets into pos
-    uint8_t  list_n[kMaxN];
-    float red[2][kDW][kWave];
-    double red64[2][kDW][2];
-    float Bm[2][kNB * kNB];
-    float Bring[kNB * kRS];        // whole-instance descent: Gram ring, rows as above
+    uint16_t cell_circ[NMAX];
+    uint16_t slot_tmp[NMAX];
+    float2 psort[ALL ? 1 : NMAX + 4];    // positions in cell order (see build_lists)
+    uint16_t list[ELL][NMAX];     // slot-major: lanes read consecutive entries; byte offsets into pos
+    uint8_t  list_n[NMAX];
+    float red[2][NW][kWave];
+    double red64[2][NW][2];
+    float Bm[2][kBm];
+    float Bring[ALL ? 1 : kNB * kRS];        // whole-instance descent: Gram ring, rows as above
     uint32_t bperm[kWave];         // source slots of the Gram update per lane (byte addresses)
     float tot_s[2][kWave];
     float rho[2][kMM];             // 1 / s_j'y_j of the Gram buffer of the same index
-    uint16_t bsrc[2][kNB * kNB];   // Gram update sources, see gram_source
-    int scan_tmp[kDW + 1];
+    uint16_t bsrc[2][kBm];   // Gram update sources, see gram_source
+    int scan_tmp[NW + 1];
     int flag[2];
     int over;                      // a circle had more than ELL neighbors
     int work;
@@ -113,8 +113,8 @@ struct DenseShared {
     int hoff[kMaxSeqBatches + 1];
     int voff[kMaxSeqBatches + 1];
     float4 vr[2 * kMaxN];       // (g, y_Q, s_K, w_K) by row of the batch matrix
-    float wpart[4][kDB / kWave];
-    float4 part[2 * kDB];
+    float wpart[4][kFullBlock / kWave];
+    float4 part[2 * kFullBlock];
 };
 
 // Per-batch state of the dense descent (bits of a lane-indexed word): the
@@ -302,14 +302,30 @@ enum : int { kDecAccept = 1, kDecPush = 2, kDecStop = 4, kDecNext = 8, kDecSteep
 // ones -- different: rebuild, len = 1; equal: len doubles.  With one
 // non-empty batch the descent is the whole-instance one (ANM after every
 // iteration, the point re-evaluated when the lists change).
-template <int MODE>
-__global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
+//
+// BLOCK threads, CPT circles per thread: the instance sizes n <= BLOCK * CPT
+// a launch serves (see descend_shape for the choice).  Circle i sits in the
+// same lane of the same wave in every shape, and the waves and circles a
+// smaller shape leaves out contribute exact zeros in the larger one, so an
+// instance's results have the same bits in all of them.
+// Waves per SIMD the registers are limited to.  Two is what the history of
+// two circles per thread leaves (one workgroup of 512 per CU); with one
+// circle per thread two workgroups of 512 fit at 128 registers, three of 256.
+constexpr int descend_waves(int mode, int block, int cpt)
+{
+    return cpt == 2 || mode == kModeSeq || block < 256 ? 2 : block == 256 ? 3 : 4;
+}
+
+template <int MODE, int BLOCK, int CPT>
+__global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_descend_kernel(
     const int32_t *__restrict__ offset, const float *__restrict__ Rv,
     const double *__restrict__ Rv64, float *__restrict__ xy,
     int B, int64_t total_n, DescentArgs A, DescentResultDev *__restrict__ out,
     int32_t *__restrict__ queue, float *__restrict__ Rout, const int32_t *__restrict__ part,
     float *__restrict__ Hws)
 {
+    constexpr int kDB = BLOCK, kDW = BLOCK / kWave, kCPT = CPT, kNM = BLOCK * CPT;
+    constexpr int kFarOff = far_off(kNM);
     constexpr bool ADJ = MODE == kModeAdj;
     constexpr bool DENSE = MODE == kModeDense;
     constexpr bool SEQ = MODE == kModeSeq || DENSE;
@@ -318,22 +334,27 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
     // every wave decides only in the dense mode
     static_assert(SOLO || DENSE, "the limited-memory modes decide on one wave");
     constexpr int ELL = SEQ ? kEllSeq : kEll;
-    __shared__ DescentShared<ELL, DENSE> sh;
+    __shared__ DescentShared<ELL, kNM, kDW, DENSE> sh;
     __shared__ std::conditional_t<DENSE, DenseShared, std::conditional_t<SEQ, SeqShared, NoShared>> sq;
     const int tid = threadIdx.x;
     // (lane ids are recomputed per evaluation from an opaque copy of tid)
     // wave index, wave-uniform to the compiler (branches on it stay scalar)
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-    for (int q = tid; q < 2 * kNB * kNB; q += kDB)
-        sh.bsrc[q / (kNB * kNB)][q % (kNB * kNB)] = gram_source(q % (kNB * kNB), q >= kNB * kNB);
+    if constexpr (DENSE)
+        for (int q = tid; q < 2 * kNB * kNB; q += kDB)
+            sh.bsrc[q / (kNB * kNB)][q % (kNB * kNB)] = gram_source(q % (kNB * kNB), q >= kNB * kNB);
     if constexpr (SOLO)
         if (tid < kWave) sh.bperm[tid] = gram_perm_bytes(tid);
     const float c2lo = (float)(A.c2 * (1.0 - 1e-5)), c2hi = (float)(A.c2 * (1.0 + 1e-5));
 
+    bool taken = false;
     for (;;) {
         // ---- next instance from the queue ------------------------------------
         __syncthreads();
-        if (tid == 0) sh.work = atomicAdd(&queue[0], 1);
+        // (no queue: the grid holds a workgroup for every instance, which
+        // takes the instance of its index and ends)
+        if (tid == 0) sh.work = queue ? atomicAdd(&queue[0], 1) : taken ? B : (int)blockIdx.x;
+        taken = true;
         __syncthreads();
         const int slot = sh.work;
         if (slot >= B) break;
@@ -342,9 +363,9 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
         int tid_i = (int)threadIdx.x;
         asm volatile("" : "+v"(tid_i));
         const int tid = tid_i;
-        const int b = queue[1 + slot];
+        const int b = queue ? queue[1 + slot] : slot;
         const int off = offset[b], n = offset[b + 1] - off;
-        if (!(off >= 0 && n >= 0 && n <= kMaxN && (int64_t)off + n <= total_n)) {
+        if (!(off >= 0 && n >= 0 && n <= kNM && (int64_t)off + n <= total_n)) {
             if (tid == 0) {
                 store_bad_instance(out, b);   // BAD_INSTANCE
             }
@@ -446,7 +467,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
         // ---- per-thread state (circle c of this thread is tid + c*kDB) ----
         bool act[kCPT];
         float2 x[kCPT], g[kCPT], xr[kCPT], p[kCPT];
-        double S[kMM][kCPT], Y[kMM][kCPT];      // curvature pairs (float2 bits), newest at kMM-1
+        double S[kCPT][kMM], Y[kCPT][kMM];      // curvature pairs (float2 bits), newest at kMM-1
 #pragma unroll
         for (int c = 0; c < kCPT; ++c) {
             const int i = tid + c * kDB;
@@ -456,7 +477,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
             xr[c] = x[c];
             p[c] = make_float2(0.f, 0.f);
 #pragma unroll
-            for (int j = 0; j < kMM; ++j) { S[j][c] = 0.0; Y[j][c] = 0.0; }
+            for (int j = 0; j < kMM; ++j) { S[c][j] = 0.0; Y[c][j] = 0.0; }
         }
         // ---- uniform state ---------------------------------------------------
         int k = 0;                     // valid pairs, slots kMM-k .. kMM-1
@@ -904,13 +925,14 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
             return two_loop_core(lane, Bc, rho_v, cs_out, alph_out, gam_out);
         };
 
-        for (int q = tid; q < kNB * kNB; q += kDB) { sh.Bm[0][q] = 0.f; sh.Bm[1][q] = 0.f; }
+        if constexpr (DENSE)
+            for (int q = tid; q < kNB * kNB; q += kDB) { sh.Bm[0][q] = 0.f; sh.Bm[1][q] = 0.f; }
         if constexpr (SOLO)
             for (int q = tid; q < kNB * kRS; q += kDB) sh.Bring[q] = 0.f;
         for (int q = tid; q < 2 * kMM; q += kDB) sh.rho[q / kMM][q % kMM] = 0.f;
         if (tid == 0) {
             sh.flag[0] = 1; sh.flag[1] = 0; sh.cell_evals = 0;
-            sh.pos[kMaxN] = make_float2(kFarCoord, kFarCoord);
+            sh.pos[kNM] = make_float2(kFarCoord, kFarCoord);
             sh.dk.tau64 = A.tau64; sh.dk.e_feasible = A.e_feasible;
             sh.dk.c1 = A.c1; sh.dk.eps_curv = A.eps_curv; sh.dk.ftol = A.ftol; sh.dk.g_tol_sq = A.g_tol_sq;
             sh.dk.m = A.m; sh.dk.max_halvings = A.max_halvings; sh.dk.max_iter = A.max_iter;
@@ -929,7 +951,6 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
             // fresh minimisation of U at this lambda; every wave has left
             // the previous round's reads of B before it is cleared
             __syncthreads();
-            for (int q = tid; q < kNB * kNB; q += kDB) { sh.Bm[0][q] = 0.f; sh.Bm[1][q] = 0.f; }
             for (int q = tid; q < kNB * kRS; q += kDB) sh.Bring[q] = 0.f;
             for (int q = tid; q < 2 * kMM; q += kDB) sh.rho[q / kMM][q % kMM] = 0.f;
             k = 0; cur = 0; it = 0; itw = 0; hd = 0; h = 0; status = 0;
@@ -990,7 +1011,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                 // every circle writes its neighbors into its own ELL slots;
                 // more than ELL switches this list epoch to sweeping the
                 // cell grid instead
-                mlist = build_lists<kDB, kCPT, ELL, kMaxN>(
+                mlist = build_lists<kDB, kCPT, ELL, kNM>(
                     tid, xt, act, own, grid, sh.cell_start, sh.cell_circ, psort, A.c2,
                     &sh.list[0][0], sh.list_n, kFarOff, up_c, &sh.over);
 #pragma unroll
@@ -1000,7 +1021,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                 // integer add per wave (the same totals in any order): in all,
                 // and per batch for the batch descent
                 {
-                    const int wsum = wave_sum_int(up_c[0] + up_c[1]);
+                    const int wsum = wave_sum_int(kCPT == 2 ? up_c[0] + up_c[kCPT - 1] : up_c[0]);
                     if (lane == 0) atomicAdd(&sh.npair[kMaxSeqBatches], wsum);
                     if constexpr (SEQ) {
                         for (int q = 0; q < A.nbat; ++q) {
@@ -1087,7 +1108,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                             bool hf = jb > i * (int)sizeof(float2);
                             if constexpr (SEQ) {
                                 const int jj = jb / (int)sizeof(float2);
-                                if (masked) hf = hf || sq.bat[jj < kMaxN ? jj : kMaxN - 1] != cb;
+                                if (masked) hf = hf || sq.bat[jj < kNM ? jj : kNM - 1] != cb;
                             }
                             float l2;
                             const float il = pair_term32s(q, pj[c], hf, two_r, four_r2, four_r2_band,
@@ -1146,7 +1167,9 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                     // containment (branch-free, as the pair term)
                     const float r2 = q.x * q.x + q.y * q.y;
                     const float ir = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
-                    const float d0 = fmaxf(r2 * ir + rad - Rt, 0.f);
+                    // |c_i| rounded on its own: the same bits in every workgroup shape
+                    const float rho = mul_rounded(r2, ir);
+                    const float d0 = fmaxf(rho + rad - Rt, 0.f);
                     e += d0 * d0;
                     if constexpr (ADJ) {
                         e1 += d0;                     // sum of d_i0: dU/dR
@@ -1159,7 +1182,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                     gy += kc * q.y;
                     if (want64) {
                         const double r64 =
-                            sqrt64_from32((double)q.x * q.x + (double)q.y * q.y, r2 * ir, ir);
+                            sqrt64_from32((double)q.x * q.x + (double)q.y * q.y, rho, ir);
                         const double c0 = r64 + rad64 - R64;
                         if (c0 > 0.0) eo += c0 * c0;
                         const double ct = r64 + 1.0 - R64;
@@ -1209,17 +1232,23 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                     for (int w = 0; w < kDW; ++w) tot += sh.red[par][w][lane];
                     double so = 0.0, st = 0.0;
                     if (want64) {
-                        // lane w of every group of eight holds wave w's FP64
-                        // sums; a fixed tree over the eight (pairs, quads,
+                        // lane w of every group of kDW holds wave w's FP64
+                        // sums; a fixed tree over them (pairs, quads,
                         // halves), read from lane 0
                         const int wl = lane & (kDW - 1);
                         double vo = sh.red64[par][wl][0], vt = sh.red64[par][wl][1];
-                        vo += dpp64<kDppXor1>(vo);
-                        vt += dpp64<kDppXor1>(vt);
-                        vo += dpp64<kDppXor2>(vo);
-                        vt += dpp64<kDppXor2>(vt);
-                        vo += dpp64<kDppHalfMirror>(vo);
-                        vt += dpp64<kDppHalfMirror>(vt);
+                        if constexpr (kDW > 1) {
+                            vo += dpp64<kDppXor1>(vo);
+                            vt += dpp64<kDppXor1>(vt);
+                        }
+                        if constexpr (kDW > 2) {
+                            vo += dpp64<kDppXor2>(vo);
+                            vt += dpp64<kDppXor2>(vt);
+                        }
+                        if constexpr (kDW > 4) {
+                            vo += dpp64<kDppHalfMirror>(vo);
+                            vt += dpp64<kDppHalfMirror>(vt);
+                        }
                         so = lane_value64(vo, 0);
                         st = lane_value64(vt, 0);
                     }
@@ -1523,10 +1552,8 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                     for (int c = 0; c < kCPT; ++c) {
                         // a batch visit's pair belongs to the batch's circles
                         if (push && inb[c]) {
-#pragma unroll
-                            for (int j = 0; j < kMM - 1; ++j) { S[j][c] = S[j + 1][c]; Y[j][c] = Y[j + 1][c]; }
-                            S[kMM - 1][c] = __builtin_bit_cast(double, sc[c]);
-                            Y[kMM - 1][c] = __builtin_bit_cast(double, yc[c]);
+                            push_history(S[c], as_f64(sc[c]));
+                            push_history(Y[c], as_f64(yc[c]));
                         }
                         x[c] = xt[c];
                         g[c] = gt[c];
@@ -1551,8 +1578,8 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
 #pragma unroll
                         for (int j = 0; j < kMM; ++j) {
                             const float csj = sh.coef[0][j], cyj = sh.coef[1][j];
-                            px -= csj * as_f2(S[j][c]).x + cyj * as_f2(Y[j][c]).x;
-                            py -= csj * as_f2(S[j][c]).y + cyj * as_f2(Y[j][c]).y;
+                            px -= csj * as_f2(S[c][j]).x + cyj * as_f2(Y[c][j]).x;
+                            py -= csj * as_f2(S[c][j]).y + cyj * as_f2(Y[c][j]).y;
                         }
                         p[c] = (!SEQ || !visits || batc_of(c) == cb) ? make_float2(px, py)
                                                                   : make_float2(0.f, 0.f);
@@ -1626,12 +1653,6 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
                 gram_update(tot, par, push, lane);
 #pragma unroll
                 for (int c = 0; c < kCPT; ++c) {
-                    if (!DENSE && push && inb[c]) {
-#pragma unroll
-                        for (int j = 0; j < kMM - 1; ++j) { S[j][c] = S[j + 1][c]; Y[j][c] = Y[j + 1][c]; }
-                        S[kMM - 1][c] = __builtin_bit_cast(double, sc[c]);
-                        Y[kMM - 1][c] = __builtin_bit_cast(double, yc[c]);
-                    }
                     x[c] = xt[c];
                     g[c] = gt[c];
                 }
@@ -1710,8 +1731,8 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
     #pragma unroll
                         for (int j = 0; j < kMM; ++j) {
                             const float csj = lane_value(cs_v, j), cyj = lane_value(cy_v, j);
-                            px -= csj * as_f2(S[j][c]).x + cyj * as_f2(Y[j][c]).x;
-                            py -= csj * as_f2(S[j][c]).y + cyj * as_f2(Y[j][c]).y;
+                            px -= csj * as_f2(S[c][j]).x + cyj * as_f2(Y[c][j]).x;
+                            py -= csj * as_f2(S[c][j]).y + cyj * as_f2(Y[c][j]).y;
                         }
                         p[c] = (!SEQ || !visits || batc_of(c) == cb) ? make_float2(px, py)
                                                                   : make_float2(0.f, 0.f);
@@ -1752,7 +1773,7 @@ __global__ __launch_bounds__(kDB) void lbfgs_descend_kernel(
             // with the radius as a variable, E reports the energy without
             // the penalty (the last lambda was halved once more after the round)
             r.E32 = (ADJ && A.rounds > 0) ? E - 2.f * lam * Rz * Rz : E;
-            r.gnorm = sqrtf(fmaxf(SOLO ? sh.Bring[kG * kRS + 4 * kMM] : sh.Bm[cur][kG * kNB + kG], 0.f));
+            r.gnorm = sqrtf(fmaxf(SOLO ? sh.Bring[SOLO ? kG * kRS + 4 * kMM : 0] : sh.Bm[cur][SOLO ? 0 : kG * kNB + kG], 0.f));
             r.E64 = fp64 ? E64t : -1.0;
             if (SEQ && visits) {
                 // outer iterations; whole-instance energies; the sum of the
@@ -1797,11 +1818,46 @@ __global__ __launch_bounds__(kQB) void queue_init_kernel(const int32_t *__restri
     if (threadIdx.x == 0) queue[0] = 0;
 }
 
-int descend_grid(int B)
+// Workgroup shape for instances of at most max_n circles (threads x circles
+// per thread): the smallest that holds them.  A smaller shape has fewer
+// waves to reduce over and wait for (one wave has no barrier at all) and
+// leaves room for more workgroups per CU.  Against 512 x 2 for every size
+// (us, random starts to convergence, one start / 1024 starts): n = 20 1411 ->
+// 1045 / 8045 -> 2776, n = 100 4542 -> 3523 / 17.9k -> 6.7k, n = 200 6074 ->
+// 5050 / 31.3k -> 19.3k, n = 500 3720 -> 2905 / 19.8k -> 13.5k.
+template <typename F>
+hipError_t descend_shape(int max_n, F &&f)
+{
+    if (max_n <= 64) return f(std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{});
+    if (max_n <= 128) return f(std::integral_constant<int, 128>{}, std::integral_constant<int, 1>{});
+    if (max_n <= 256) return f(std::integral_constant<int, 256>{}, std::integral_constant<int, 1>{});
+    if (max_n <= 512) return f(std::integral_constant<int, 512>{}, std::integral_constant<int, 1>{});
+    return f(std::integral_constant<int, kFullBlock>{}, std::integral_constant<int, 2>{});
+}
+
+// One launch over B instances: a resident workgroup per instance where they
+// all fit on the device, which needs no work queue (and no launch to set it
+// up); else as many workgroups as stay resident, fed by the queue.
+template <int MODE, int BLOCK, int CPT, typename Q>
+hipError_t launch_shape(const int32_t *offset, const float *R, const double *R64, float *xy, int B,
+                        int64_t total_n, const DescentArgs &a, void *out, Q &&get_queue,
+                        float *Rout, const int32_t *batch_of, float *H, hipStream_t s)
 {
     static std::atomic<int> per_cu[kMaxDevices];
-    const int cap = current_device_cus() * resident_per_cu(lbfgs_descend_kernel<kModeWhole>, kDB, per_cu);
-    return B < cap ? B : cap;
+    const int cap = current_device_cus() *
+                    resident_per_cu(lbfgs_descend_kernel<MODE, BLOCK, CPT>, BLOCK, per_cu);
+    int grid = B;
+    int32_t *queue = nullptr;
+    if (B > cap) {
+        const hipError_t e = get_queue(&queue);
+        if (e != hipSuccess) return e;
+        queue_init_kernel<<<1, kQB, 0, s>>>(offset, B, queue);
+        grid = cap;
+    }
+    lbfgs_descend_kernel<MODE, BLOCK, CPT><<<grid, BLOCK, 0, s>>>(
+        offset, R, R64, xy, B, total_n, a, reinterpret_cast<DescentResultDev *>(out), queue, Rout,
+        batch_of, H);
+    return hipGetLastError();
 }
 
 hipError_t launch_queue_init(const int32_t *offset, int B, int32_t *queue, hipStream_t s)
@@ -1811,15 +1867,14 @@ hipError_t launch_queue_init(const int32_t *offset, int B, int32_t *queue, hipSt
 }
 
 hipError_t launch_descend(const int32_t *offset, const float *R, const double *R64, float *xy,
-                          int B, int64_t total_n, const DescentArgs &a, void *out,
-                          int32_t *queue, int grid, hipStream_t s)
+                          int B, int max_n, int64_t total_n, const DescentArgs &a, void *out,
+                          int32_t *queue, hipStream_t s)
 {
-    queue_init_kernel<<<1, kQB, 0, s>>>(offset, B, queue);
-    if (grid < 1) grid = 1;
-    lbfgs_descend_kernel<kModeWhole><<<grid, kDB, 0, s>>>(offset, R, R64, xy, B, total_n, a,
-                                                          reinterpret_cast<DescentResultDev *>(out),
-                                                          queue, nullptr, nullptr, nullptr);
-    return hipGetLastError();
+    return descend_shape(max_n, [&](auto block, auto cpt) {
+        return launch_shape<kModeWhole, block(), cpt()>(
+            offset, R, R64, xy, B, total_n, a, out,
+            [&](int32_t **q) { *q = queue; return hipSuccess; }, nullptr, nullptr, nullptr, s);
+    });
 }
 
 // The descent's only scratch memory is its work queue (a counter and the
@@ -1857,50 +1912,47 @@ hipError_t noalloc_queue(int32_t **queue)
 }  // namespace
 
 hipError_t launch_descend_noalloc(const int32_t *offset, const float *R, const double *R64,
-                                  float *xy, int B, int64_t total_n, const DescentArgs &a,
-                                  void *out, int grid, hipStream_t s)
+                                  float *xy, int B, int max_n, int64_t total_n,
+                                  const DescentArgs &a, void *out, hipStream_t s)
 {
     if (B > kNoAllocMaxInstances) return hipErrorInvalidValue;
-    int32_t *queue = nullptr;
-    const hipError_t e = noalloc_queue(&queue);
-    if (e != hipSuccess) return e;
-    return launch_descend(offset, R, R64, xy, B, total_n, a, out, queue, grid, s);
+    return descend_shape(max_n, [&](auto block, auto cpt) {
+        return launch_shape<kModeWhole, block(), cpt()>(offset, R, R64, xy, B, total_n, a, out,
+                                                        noalloc_queue, nullptr, nullptr, nullptr,
+                                                        s);
+    });
 }
 
-hipError_t launch_adjust(const int32_t *offset, const float *R, float *xy, int B,
+hipError_t launch_adjust(const int32_t *offset, const float *R, float *xy, int B, int max_n,
                          int64_t total_n, const DescentArgs &a, float *Rout, void *out,
-                         int32_t *queue, int grid, hipStream_t s)
+                         int32_t *queue, hipStream_t s)
 {
-    queue_init_kernel<<<1, kQB, 0, s>>>(offset, B, queue);
-    if (grid < 1) grid = 1;
-    lbfgs_descend_kernel<kModeAdj><<<grid, kDB, 0, s>>>(offset, R, nullptr, xy, B, total_n, a,
-                                                        reinterpret_cast<DescentResultDev *>(out),
-                                                        queue, Rout, nullptr, nullptr);
-    return hipGetLastError();
+    return descend_shape(max_n, [&](auto block, auto cpt) {
+        return launch_shape<kModeAdj, block(), cpt()>(
+            offset, R, nullptr, xy, B, total_n, a, out,
+            [&](int32_t **q) { *q = queue; return hipSuccess; }, Rout, nullptr, nullptr, s);
+    });
 }
 
 hipError_t launch_seq(const int32_t *offset, const float *R, const double *R64, float *xy, int B,
-                      int64_t total_n, const DescentArgs &a, const int32_t *batch_of, void *out,
-                      int32_t *queue, int grid, hipStream_t s)
+                      int max_n, int64_t total_n, const DescentArgs &a, const int32_t *batch_of,
+                      void *out, int32_t *queue, hipStream_t s)
 {
-    queue_init_kernel<<<1, kQB, 0, s>>>(offset, B, queue);
-    if (grid < 1) grid = 1;
-    lbfgs_descend_kernel<kModeSeq><<<grid, kDB, 0, s>>>(offset, R, R64, xy, B, total_n, a,
-                                                        reinterpret_cast<DescentResultDev *>(out),
-                                                        queue, nullptr, batch_of, nullptr);
-    return hipGetLastError();
+    const auto q = [&](int32_t **p) { *p = queue; return hipSuccess; };
+    if (max_n <= kFullBlock)
+        return launch_shape<kModeSeq, kFullBlock, 1>(offset, R, R64, xy, B, total_n, a, out, q,
+                                                     nullptr, batch_of, nullptr, s);
+    return launch_shape<kModeSeq, kFullBlock, 2>(offset, R, R64, xy, B, total_n, a, out, q,
+                                                 nullptr, batch_of, nullptr, s);
 }
 
 hipError_t launch_dense(const int32_t *offset, const float *R, const double *R64, float *xy,
                         int B, int64_t total_n, const DescentArgs &a, const int32_t *batch_of,
-                        float *H, void *out, int32_t *queue, int grid, hipStream_t s)
+                        float *H, void *out, int32_t *queue, hipStream_t s)
 {
-    queue_init_kernel<<<1, kQB, 0, s>>>(offset, B, queue);
-    if (grid < 1) grid = 1;
-    lbfgs_descend_kernel<kModeDense><<<grid, kDB, 0, s>>>(offset, R, R64, xy, B, total_n, a,
-                                                          reinterpret_cast<DescentResultDev *>(out),
-                                                          queue, nullptr, batch_of, H);
-    return hipGetLastError();
+    return launch_shape<kModeDense, kFullBlock, 2>(
+        offset, R, R64, xy, B, total_n, a, out,
+        [&](int32_t **q) { *q = queue; return hipSuccess; }, nullptr, batch_of, H, s);
 }
 
 }  // namespace pecc

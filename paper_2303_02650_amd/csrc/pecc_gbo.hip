@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                     bool act[kGCPB];
                     int ci[kGCPB];
                     float2 x[kGCPB], g[kGCPB], pd[kGCPB];
-                    float2 S[kMM][kGCPB], Y[kMM][kGCPB];
+                    float2 S[kGCPB][kMM], Y[kGCPB][kMM];
                     float2 *hS = histS + (size_t)p * kMM * kMaxGboBatch;
                     float2 *hY = histY + (size_t)p * kMM * kMaxGboBatch;
 #pragma unroll
@@ -385,8 +385,8 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                             // logical j (newest at kMM-1) is ring slot head - (kMM-1-j)
                             const int sl = (st.head - (kMM - 1 - j) + 2 * kMM) % kMM;
                             const bool valid = act[c] && j >= kMM - k;
-                            S[j][c] = valid ? hS[(size_t)sl * kMaxGboBatch + q] : make_float2(0.f, 0.f);
-                            Y[j][c] = valid ? hY[(size_t)sl * kMaxGboBatch + q] : make_float2(0.f, 0.f);
+                            S[c][j] = valid ? hS[(size_t)sl * kMaxGboBatch + q] : make_float2(0.f, 0.f);
+                            Y[c][j] = valid ? hY[(size_t)sl * kMaxGboBatch + q] : make_float2(0.f, 0.f);
                         }
                     }
                     float *Bwc[2] = {sh.Bw[wv][0], sh.Bw[wv][1]};
@@ -571,8 +571,8 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                             float px = -gam * g[c].x, py = -gam * g[c].y;
 #pragma unroll
                             for (int j = 0; j < kMM; ++j) {
-                                px -= cs[j] * S[j][c].x + cy[j] * Y[j][c].x;
-                                py -= cs[j] * S[j][c].y + cy[j] * Y[j][c].y;
+                                px -= cs[j] * S[c][j].x + cy[j] * Y[c][j].x;
+                                py -= cs[j] * S[c][j].y + cy[j] * Y[c][j].y;
                             }
                             pd[c] = make_float2(px, py);
                         }

@@ -44,36 +44,37 @@ constexpr int kMaxSeqBatches = 16;   // batches of the batch descent at most
 
 struct DescentResultDev;  // layout-identical to pecc_descent_result
 
+// Descent of every instance.  max_n bounds every instance's circles and picks
+// the workgroup shape (a larger instance reports BAD_INSTANCE); queue: B + 1
+// int32, used when the instances do not all fit on the device at once.
 hipError_t launch_descend(const int32_t *offset, const float *R, const double *R64, float *xy,
-                          int B, int64_t total_n, const DescentArgs &a, void *out,
-                          int32_t *queue, int grid, hipStream_t s);
-
-int descend_grid(int B);   // persistent workgroups to launch for B instances
+                          int B, int max_n, int64_t total_n, const DescentArgs &a, void *out,
+                          int32_t *queue, hipStream_t s);
 
 // The same descent with its work queue in a library-held array (no
 // allocation anywhere): at most kNoAllocMaxInstances instances.
 constexpr int kNoAllocMaxInstances = 65536;
 hipError_t launch_descend_noalloc(const int32_t *offset, const float *R, const double *R64,
-                                  float *xy, int B, int64_t total_n, const DescentArgs &a,
-                                  void *out, int grid, hipStream_t s);
+                                  float *xy, int B, int max_n, int64_t total_n,
+                                  const DescentArgs &a, void *out, hipStream_t s);
 
 // Container adjustment: the descent with the radius as a variable (Rout[B]
 // receives the final radii; the initial ones come from R).
-hipError_t launch_adjust(const int32_t *offset, const float *R, float *xy, int B,
+hipError_t launch_adjust(const int32_t *offset, const float *R, float *xy, int B, int max_n,
                          int64_t total_n, const DescentArgs &a, float *Rout, void *out,
-                         int32_t *queue, int grid, hipStream_t s);
+                         int32_t *queue, hipStream_t s);
 
 // Batch descent of Alg. 1 over a given partition (batch_of: global circle
 // index -> batch in [0, a.nbat)), batches visited in order.
 hipError_t launch_seq(const int32_t *offset, const float *R, const double *R64, float *xy, int B,
-                      int64_t total_n, const DescentArgs &a, const int32_t *batch_of, void *out,
-                      int32_t *queue, int grid, hipStream_t s);
+                      int max_n, int64_t total_n, const DescentArgs &a, const int32_t *batch_of,
+                      void *out, int32_t *queue, hipStream_t s);
 
 // Dense batch descent (the paper's per-batch inverse-Hessian matrices,
 // Eq. 8-11): H holds a.hstride floats per instance.
 hipError_t launch_dense(const int32_t *offset, const float *R, const double *R64, float *xy,
                         int B, int64_t total_n, const DescentArgs &a, const int32_t *batch_of,
-                        float *H, void *out, int32_t *queue, int grid, hipStream_t s);
+                        float *H, void *out, int32_t *queue, hipStream_t s);
 
 // k-batch partitions of Sec. 4.1 (kind: 0 sector, 1 annulus, 2 fence, 3 random).
 hipError_t launch_partition(const int32_t *offset, const float *xy, int B, int64_t total_n,

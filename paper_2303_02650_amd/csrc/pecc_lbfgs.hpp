@@ -78,6 +78,29 @@ __device__ __forceinline__ void store_bad_instance(DescentResultDev *out, int b)
 // aligned register pair, so that shifting the history moves pairs).
 __device__ __forceinline__ float2 as_f2(float2 v) { return v; }
 __device__ __forceinline__ float2 as_f2(double v) { return __builtin_bit_cast(float2, v); }
+__device__ __forceinline__ double as_f64(float2 v) { return __hiloint2double(__float_as_int(v.y), __float_as_int(v.x)); }
+
+// A circle's history pushed by one pair, in place (the value moves of the
+// plain assignments are otherwise allocated to a second set of registers and
+// copied back at the end of the loop body).
+__device__ __forceinline__ void push_history(double (&H)[kMM], double v)
+{
+    asm("v_mov_b64 %0, %1\n\tv_mov_b64 %1, %2\n\tv_mov_b64 %2, %3\n\tv_mov_b64 %3, %4\n\t"
+        "v_mov_b64 %4, %5\n\tv_mov_b64 %5, %6\n\tv_mov_b64 %6, %7\n\tv_mov_b64 %7, %8\n\t"
+        "v_mov_b64 %8, %9\n\tv_mov_b64 %9, %10"
+        : "+v"(H[0]), "+v"(H[1]), "+v"(H[2]), "+v"(H[3]), "+v"(H[4]), "+v"(H[5]), "+v"(H[6]),
+          "+v"(H[7]), "+v"(H[8]), "+v"(H[9])
+        : "v"(v));
+}
+
+// a * b rounded on its own: never the product of a fused multiply-add (which
+// of several sums a product fuses into is the compiler's choice, and it
+// differs between instantiations of one kernel).
+__device__ __forceinline__ float mul_rounded(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
 
 // Value of reduction slot v summed over this thread's circles (v is a
 // constant after unrolling, so the branches fold away): one FMA chain over
@@ -85,8 +108,8 @@ __device__ __forceinline__ float2 as_f2(double v) { return __builtin_bit_cast(fl
 template <int CPT, typename HV>
 __device__ __forceinline__ float slot_value(int v, const float2 (&gt)[CPT], const float2 (&sc)[CPT],
                                             const float2 (&yc)[CPT],
-                                            const HV (&S)[kMM][CPT],
-                                            const HV (&Y)[kMM][CPT], float e, float e1)
+                                            const HV (&S)[CPT][kMM],
+                                            const HV (&Y)[CPT][kMM], float e, float e1)
 {
     if (v == sE) return e;
     if (v == sE1) return e1;
@@ -94,12 +117,12 @@ __device__ __forceinline__ float slot_value(int v, const float2 (&gt)[CPT], cons
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
         float2 a, b;
-        if (v < kMM) { a = gt[c]; b = as_f2(S[v][c]); }
-        else if (v < 2 * kMM) { a = gt[c]; b = as_f2(Y[v - kMM][c]); }
-        else if (v < 3 * kMM - 1) { a = sc[c]; b = as_f2(S[v - 2 * kMM + 1][c]); }
-        else if (v < 4 * kMM - 2) { a = sc[c]; b = as_f2(Y[v - (3 * kMM - 1) + 1][c]); }
-        else if (v < 5 * kMM - 3) { a = yc[c]; b = as_f2(S[v - (4 * kMM - 2) + 1][c]); }
-        else if (v < 6 * kMM - 4) { a = yc[c]; b = as_f2(Y[v - (5 * kMM - 3) + 1][c]); }
+        if (v < kMM) { a = gt[c]; b = as_f2(S[c][v]); }
+        else if (v < 2 * kMM) { a = gt[c]; b = as_f2(Y[c][v - kMM]); }
+        else if (v < 3 * kMM - 1) { a = sc[c]; b = as_f2(S[c][v - 2 * kMM + 1]); }
+        else if (v < 4 * kMM - 2) { a = sc[c]; b = as_f2(Y[c][v - (3 * kMM - 1) + 1]); }
+        else if (v < 5 * kMM - 3) { a = yc[c]; b = as_f2(S[c][v - (4 * kMM - 2) + 1]); }
+        else if (v < 6 * kMM - 4) { a = yc[c]; b = as_f2(Y[c][v - (5 * kMM - 3) + 1]); }
         else if (v == sGG) { a = gt[c]; b = gt[c]; }
         else if (v == sScSc) { a = sc[c]; b = sc[c]; }
         else if (v == sScYc) { a = sc[c]; b = yc[c]; }
@@ -261,8 +284,8 @@ template <int CPT, typename HV>
 __device__ __forceinline__ float wave_reduce_scatter(const float2 (&gt)[CPT],
                                                      const float2 (&sc)[CPT],
                                                      const float2 (&yc)[CPT],
-                                                     const HV (&S)[kMM][CPT],
-                                                     const HV (&Y)[kMM][CPT], float e,
+                                                     const HV (&S)[CPT][kMM],
+                                                     const HV (&Y)[CPT][kMM], float e,
                                                      float e1)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -615,6 +638,7 @@ __device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], cons
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
             const int i = tid + c * BLOCK;
+#pragma unroll
             for (int r = 0; r < 3; ++r) {
                 for (int t = ra[c][r]; t < ra[c][r] + rl[c][r]; ++t) {
                     if (t != own[c] && near64(x[c], psort[t], c2)) {
