@@ -1,22 +1,23 @@
 // Persistent L-BFGS descent of the elastic energy at fixed container radius.
 //
-// Mapping (one workgroup of 512 threads per instance, n <= 1024):
+// Mapping (one workgroup per instance, n <= 1024; 512 threads with two
+// circles each, or fewer threads with one circle each for n <= 512, see
+// descend_shape):
 //   * thread t owns circles t and t + 512: their positions, gradients, search
 //     directions and their coordinates of every stored curvature pair
 //     (s_j, y_j) live in registers, so the L-BFGS history never leaves the
 //     chip (two circles per thread leave a 256-register budget, enough for
 //     the 80 history registers without spilling);
 //   * positions of the instance sit in LDS (the pair sweep reads them), next
-//     to the cell grid and a CSR neighbor list of 16-bit local indices;
+//     to the cell grid and the neighbor lists;
 //   * the inverse-Hessian product is formed without per-vector dot products
-//     (vector-free two-loop): every wave keeps the Gram matrix B of the basis
-//     {s_0..s_{m-1}, y_0..y_{m-1}, g} (double-buffered in LDS), runs the
-//     two-loop recursion on B's entries with lanes as columns and obtains the
-//     direction as a combination of the basis.  All new entries of B come
-//     from ONE fused reduction per line-search trial (63 dot products plus
-//     the energy), so a trial costs two workgroup barriers.
-// Workgroups take instances from a queue, largest n first, until the queue
-// is empty (the launch is sized to the resident capacity of the device).
+//     (vector-free two-loop): one wave keeps the Gram matrix B of the basis
+//     {s_0..s_{m-1}, y_0..y_{m-1}, g} in LDS, runs the two-loop recursion on
+//     B's entries with lanes as columns and obtains the direction as a
+//     combination of the basis.  All new entries of B come from ONE fused
+//     reduction per line-search trial (63 dot products plus the energy).
+// More instances than fit on the device are taken from a queue, largest n
+// first, until it is empty (the launch is sized to the resident capacity).
 //
 // Three instantiations share this code: the whole-instance descent, the
 // container adjustment (the radius as a variable) and the batch descent of
@@ -57,16 +58,11 @@ template <int ELL, int NMAX, int NW, bool ALL>
 struct DescentShared {
     static constexpr int kBm = ALL ? kNB * kNB : 1;
     float2 pos[NMAX + 1];         // pos[NMAX]: the far point
-    int cell_start[kMaxCells + 1];
-    uint16_t cell_circ[NMAX];
-    uint16_t slot_tmp[NMAX];
-    float2 psort[ALL ? 1 : NMAX + 4];    // positions in cell order (see build_lists)
-    uint16_t list[ELL][NMAX];     // slot-major: lanes read consecutive entries; byte offsets into pos
-    uint8_t  list_n[NMAX];
     float red[2][NW][kWave];
     double red64[2][NW][2];
     float Bm[2][kBm];
-    float Bring[ALL ? 1 : kNB * kRS];        // whole-instance descent: Gram ring, rows as above
+    // whole-instance descent: Gram ring, rows as above
+    float Bring[ALL ? 1 : kNB * kRS];
     uint32_t bperm[kWave];         // source slots of the Gram update per lane (byte addresses)
     float tot_s[2][kWave];
     float rho[2][kMM];             // 1 / s_j'y_j of the Gram buffer of the same index
@@ -77,22 +73,34 @@ struct DescentShared {
     int work;
     int cell_evals;                // evaluations over the cell grid (instance)
     int npair[kMaxSeqBatches + 1]; // listed pairs i<j of the current lists: per batch, and in all
-    // whole-instance descent: what the deciding wave leaves for the others
-    int dec_flags;                 // kDec* bits
-    int dec_cb;                    // batch descent: the batch of the next evaluation
-    int dec_req;                   // what the next evaluation is for
-    int dec_fp64;                  // FP64 regime from the next evaluation on
-    float dec_alpha;               // step length of the next trial
-    float dec_gam;                 // gamma of the direction
-    float coef[2][kMM];            // coefficients of s_j and y_j in the direction
+    // what the deciding wave leaves for the others: kDec* bits, what the
+    // next evaluation is for, the FP64 regime and the batch of the next
+    // evaluation (packed, see kDecReq), its step length, gamma of the
+    // direction; the coefficients of s_j, then of y_j in the direction
+    int4 dec;
+    float4 coef[2 * kMM / 4];
     // the constants of the decisions, read where used (kept in registers
     // they would crowd out the loop's scalar state)
-    struct {
+    struct alignas(16) {
         double tau64, e_feasible;
-        float c1, eps_curv, ftol, g_tol_sq, g_tol;
+        float c1, eps_curv, ftol, g_tol_sq;
         int m, max_halvings, max_iter, nbat, anm;
+        float g_tol;
     } dk;
+    uint32_t ringtab[ALL ? 1 : kMM][kWave];   // see ring_entry
+    double R64;
+    Grid grid;                     // of the instance
     float dec_Rz, dec_pR;          // container adjustment: radius and its search component
+    // the large arrays last: the address of everything before the list then
+    // fits the 16-bit offset of an LDS instruction (with the list in front
+    // every scalar and row needed an address register of its own, kept live
+    // across the loop)
+    float2 psort[ALL ? 1 : NMAX + 8];    // positions in cell order (see build_lists)
+    uint16_t list[ELL][NMAX];     // slot-major: lanes read consecutive entries; byte offsets into pos
+    uint16_t cell_circ[NMAX];
+    uint16_t slot_tmp[NMAX];
+    uint8_t  list_n[NMAX];
+    int cell_start[kMaxCells + 1];
 };
 
 // Batch descent only: the saved Gram matrix of every batch, batch ids and
@@ -269,7 +277,26 @@ struct NoShared {
 // Evaluation requests of the descent's state machine.
 enum : int { kReqInit = 0, kReqFp64 = 1, kReqTrial = 2, kReqTotal = 3 };
 // outcome of an evaluation in the whole-instance descent
-enum : int { kDecAccept = 1, kDecPush = 2, kDecStop = 4, kDecNext = 8, kDecSteepest = 16, kDecAnm = 32 };
+enum : int { kDecAccept = 1, kDecPush = 2, kDecStop = 4, kDecNext = 8, kDecSteepest = 16, kDecAnm = 32,
+             kDecFp64 = 64 };
+constexpr int kDecReq = 8, kDecBatch = 16;   // bit positions of the request and the batch
+
+// Gram ring with pair 0 at storage pair hd: where lane l (basis vector l in
+// pair order; lanes past g stand for g) finds its row and its two columns:
+// bits 0-15 the row's byte offset, 16-23 and 24-31 the columns (both the one
+// column of g).
+__device__ __forceinline__ uint32_t ring_entry(int hd, int l)
+{
+    int row = kG, c0 = 4 * kMM, c1 = 4 * kMM;
+    if (l < kG) {
+        const int base = l < kMM ? 0 : kMM;
+        const int q = (l - base + hd) % kMM;
+        row = base + q;
+        c0 = 2 * base + q;
+        c1 = c0 + kMM;
+    }
+    return (uint32_t)(row * kRS * 4) | ((uint32_t)c0 << 16) | ((uint32_t)c1 << 24);
+}
 
 // ADJ: container adjustment (Sec. 4.2, Eq. 12, Alg. 2).  The radius joins
 // the variables, the objective is U = E + lambda R^2 and A.rounds
@@ -309,11 +336,13 @@ enum : int { kDecAccept = 1, kDecPush = 2, kDecStop = 4, kDecNext = 8, kDecSteep
 // smaller shape leaves out contribute exact zeros in the larger one, so an
 // instance's results have the same bits in all of them.
 // Waves per SIMD the registers are limited to.  Two is what the history of
-// two circles per thread leaves (one workgroup of 512 per CU); with one
-// circle per thread two workgroups of 512 fit at 128 registers, three of 256.
+// two circles per thread leaves (one workgroup of 512 per CU).  With one
+// circle per thread the whole-instance descent fits two workgroups of 512 at
+// 128 registers, three of 256 at 168; the adjustment and the batch descent
+// would spill there.
 constexpr int descend_waves(int mode, int block, int cpt)
 {
-    return cpt == 2 || mode == kModeSeq || block < 256 ? 2 : block == 256 ? 3 : 4;
+    return mode != kModeWhole || cpt == 2 || block < 256 ? 2 : block == 256 ? 3 : 4;
 }
 
 template <int MODE, int BLOCK, int CPT>
@@ -334,6 +363,9 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
     // every wave decides only in the dense mode
     static_assert(SOLO || DENSE, "the limited-memory modes decide on one wave");
     constexpr int ELL = SEQ ? kEllSeq : kEll;
+    // list slots per turn of the sweep: two where a lone wave per SIMD has
+    // only one circle per thread (their chains overlap)
+    constexpr int kTrips = CPT == 1 && BLOCK <= 256 ? 2 : 1;
     __shared__ DescentShared<ELL, kNM, kDW, DENSE> sh;
     __shared__ std::conditional_t<DENSE, DenseShared, std::conditional_t<SEQ, SeqShared, NoShared>> sq;
     const int tid = threadIdx.x;
@@ -343,9 +375,11 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
     if constexpr (DENSE)
         for (int q = tid; q < 2 * kNB * kNB; q += kDB)
             sh.bsrc[q / (kNB * kNB)][q % (kNB * kNB)] = gram_source(q % (kNB * kNB), q >= kNB * kNB);
-    if constexpr (SOLO)
+    if constexpr (SOLO) {
         if (tid < kWave) sh.bperm[tid] = gram_perm_bytes(tid);
-    const float c2lo = (float)(A.c2 * (1.0 - 1e-5)), c2hi = (float)(A.c2 * (1.0 + 1e-5));
+        for (int q = tid; q < kMM * kWave; q += kDB)
+            sh.ringtab[q / kWave][q % kWave] = ring_entry(q / kWave, q % kWave);
+    }
 
     bool taken = false;
     for (;;) {
@@ -372,13 +406,28 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
             continue;
         }
         const float R = Rv[b];
-        const float rad = A.rad, two_r = 2.0f * rad, four_r2 = two_r * two_r;
-        const float four_r2_band = four_r2 * (1.0f + 1e-5f);
-        const double rad64 = (double)rad, two_r64 = 2.0 * rad64, four_r2_64 = two_r64 * two_r64;
+        const float rad = A.rad;
+        const float two_r = uniform_first(2.0f * rad), four_r2 = uniform_first(two_r * two_r);
+        const float four_r2_band = uniform_first(four_r2 * (1.0f + 1e-5f));
+        // (the constants of the rare parts -- list rebuild, FP64 regime, list
+        // overflow -- are made where they are used: kept across the loop
+        // they cost some 20 registers, which the 128-register shape spills)
+        auto opaque = [](auto v) { asm volatile("" : "+s"(v)); return v; };
         // FP64 decisions (feasibility, the near-zero line search) use the
         // caller's FP64 radius when there is one, as pecc_verify does
-        const double R64 = Rv64 ? Rv64[b] : (double)R;
-        const Grid grid = make_grid(R, A.h_req);
+        const double R64_ = Rv64 ? Rv64[b] : (double)R;
+        if (tid == 0) sh.R64 = R64_;
+        {
+            const Grid grid = make_grid(R, A.h_req);
+            if (tid == 0) sh.grid = grid;      // read after B1's barrier at the earliest
+        }
+        auto the_grid = [&]() -> Grid {
+            Grid g;
+            g.lo = uniform_first(sh.grid.lo);
+            g.inv_h = uniform_first(sh.grid.inv_h);
+            g.nc = __builtin_amdgcn_readfirstlane(sh.grid.nc);
+            return g;
+        };
 
         // ---- batch descent: batch of every circle, batch sizes --------------
         // batch of circle tid + c * kDB (read from LDS where needed, so no
@@ -535,6 +584,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
             for (int c = 0; c < kCPT; ++c)
                 if (act[c]) sh.pos[t0 + c * kDB] = x[c];
             __syncthreads();
+            const Grid grid = the_grid();
             bin_circles<kDB>(sh.pos, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp,
                              sh.scan_tmp);
             int diff = overflow ? 1 : 0;
@@ -545,7 +595,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     const int old = sh.list_n[i];
                     int m = 0;
                     for_each_candidate(i, x[c], grid, sh.cell_start, sh.cell_circ, [&](int j) {
-                        if (near_cut(x[c], sh.pos[j], c2lo, c2hi, A.c2)) {
+                        if (near64(x[c], sh.pos[j], A.c2)) {
                             bool found = false;
                             for (int t = 0; t < old; ++t) found = found || sh.list[t][i] == j * (int)sizeof(float2);
                             if (!found) diff = 1;
@@ -859,24 +909,16 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         // vector c is one FMA per lane per step: q = g - sum_i a_i y_i gives
         // acc -= a_j B[l][y_j], r = gamma q + sum_j (a_j - b_j) s_j gives
         // acc += (a_j - b_j) B[l][s_j].  s_j'q and y_j'r are then single lanes
-        // of acc (one readlane per step).  The per-pair scalars stay
-        // lane-indexed in VGPRs (lane j: rho_j, a_j, the s_j coefficient; lane
-        // 10 + j: rho_j and a_j again).  Returns g'p with p = -r; cs_v: the
-        // coefficient of s_j at lane j; alph_v: a_j at lane j.
-        auto two_loop_core = [&](int lane, const float (&Bc)[kNB], float rho_v, float &cs_out,
-                                 float &alph_out, float &gam_out) -> float {
-            const int jp = lane < kMM ? lane : lane - kMM;        // pair index of lanes 0..19
+        // of acc (one readlane per step), and a step's scalar goes to the one
+        // lane that needs it by a lane write.  Returns g'p with p = -r; cf:
+        // lane j the coefficient of s_j, lane 10 + j a_j.
+        auto two_loop = [&](const float (&Bc)[kNB], float rho_v, float &cf, float &gam_out) -> float {
             float acc = Bc[kG];                                   // (B q)_l with q = g
-            float alph_v = 0.f;                                   // a_j at lanes j and 10 + j
+            cf = 0.f;
             // every pair slot in straight-line code: a slot without a pair
             // has rho = 0, so its a_j and coefficient are 0 and acc keeps its
             // bits (acc - 0 * B = acc for finite B)
-#pragma unroll
-            for (int j = kMM - 1; j >= 0; --j) {
-                const float a = lane_value(rho_v * acc, j);         // rho_j s_j'q
-                if (jp == j) alph_v = a;
-                acc -= a * Bc[kMM + j];
-            }
+            two_loop_down(Bc + kMM, rho_v, acc, cf);              // a_j = rho_j s_j'q
             float gam = 1.f;
             if (k > 0) {
                 const float sy = lane_value(Bc[kMM - 1], 2 * kMM - 1);
@@ -884,45 +926,9 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 gam = sy / yy;
             }
             acc *= gam;                                           // (B r)_l with r = gamma q
-            float cs_v = 0.f;                                     // coefficient of s_j at lane j
-#pragma unroll
-            for (int j = 0; j < kMM; ++j) {
-                const float c = lane_value(alph_v - rho_v * acc, kMM + j);   // a_j - rho_j y_j'r
-                if (lane == j) cs_v = c;
-                acc += c * Bc[j];
-            }
-            cs_out = cs_v;
-            alph_out = alph_v;
+            two_loop_up(Bc, rho_v, acc, cf);                      // a_j - rho_j y_j'r
             gam_out = gam;
             return -lane_value(acc, kG);                          // g'p = -g'r
-        };
-        // Loads this lane's row of B (pair order through the storage map at,
-        // double-buffered form: hd = 0) and rho, then the recursion above.
-        auto two_loop = [&](int lane, int hd, float &cs_out, float &alph_out, float &gam_out) -> float {
-            // storage index of basis vector a
-            auto at = [&](int a) -> int {
-                if (a == kG) return kG;
-                const int base = a < kMM ? 0 : kMM;
-                int q = a - base + hd;
-                if (q >= kMM) q -= kMM;
-                return base + q;
-            };
-            // lanes past row 20 read row 20 again: their values are never read
-            float Bc[kNB];
-            const int lr = at(lane < kNB ? lane : kNB - 1);
-#pragma unroll
-            for (int a2 = 0; a2 < kNB; ++a2) Bc[a2] = sh.Bm[cur][at(a2) * kNB + lr];
-            const int jp = lane < kMM ? lane : lane - kMM;        // pair index of lanes 0..19
-            const bool live = lane < 2 * kMM && jp >= kMM - k;
-            const int jq = lane < 2 * kMM ? jp : 0;               // in-range index on every lane
-            float rho_v;
-            if constexpr (SEQ) {
-                rho_v = live ? 1.f / sh.Bm[cur][jq * kNB + kMM + jq] : 0.f;
-            } else {
-                rho_v = sh.rho[cur][at(jq)];
-                rho_v = live ? rho_v : 0.f;
-            }
-            return two_loop_core(lane, Bc, rho_v, cs_out, alph_out, gam_out);
         };
 
         if constexpr (DENSE)
@@ -990,7 +996,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     sh.pos[tid + c * kDB] = xt[c];
                     const double dx = (double)xt[c].x - (double)xr[c].x;
                     const double dy = (double)xt[c].y - (double)xr[c].y;
-                    if (!(SEQ && A.anm) && dx * dx + dy * dy > A.skin2) sh.flag[par] = 1;
+                    if (!(SEQ && A.anm) && dot2(dx, dx, dy, dy) > A.skin2) sh.flag[par] = 1;
                 }
             }
             __syncthreads();                                            // B1
@@ -1005,14 +1011,15 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 float2 *psort;
                 if constexpr (DENSE) psort = reinterpret_cast<float2 *>(sq.part);
                 else psort = sh.psort;
+                const Grid grid = the_grid();
                 int own[kCPT], up_c[kCPT];
                 sort_cells<kDB, kCPT>(tid, xt, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp,
                                       psort, sh.scan_tmp, own);
                 // every circle writes its neighbors into its own ELL slots;
                 // more than ELL switches this list epoch to sweeping the
                 // cell grid instead
-                mlist = build_lists<kDB, kCPT, ELL, kNM>(
-                    tid, xt, act, own, grid, sh.cell_start, sh.cell_circ, psort, A.c2,
+                mlist = build_lists<kDB, kCPT, ELL, kNM, kTrips>(
+                    tid, xt, act, own, grid, sh.cell_start, sh.cell_circ, psort, opaque(A.c2),
                     &sh.list[0][0], sh.list_n, kFarOff, up_c, &sh.over);
 #pragma unroll
                 for (int c = 0; c < kCPT; ++c)
@@ -1077,47 +1084,57 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 // two in a chain.
                 auto sweep = [&](auto e1_tag, auto w64_tag) {
                     constexpr bool kE1 = decltype(e1_tag)::value, kW64 = decltype(w64_tag)::value;
-                    int jn[kCPT];                      // byte offsets into pos, next slot
+                    const double two_r64 = 2.0 * (double)opaque(rad), four_r2_64 = two_r64 * two_r64;
+                    int jn[kTrips][kCPT];              // byte offsets into pos, next turn
 #pragma unroll
-                    for (int c = 0; c < kCPT; ++c) jn[c] = sh.list[0][tid + c * kDB];
-                    for (int t = 0; t < mm; ++t) {
-                        int jv[kCPT];
-                        float2 pj[kCPT];
-                        const int tn = t + 1 < ELL ? t + 1 : ELL - 1;
+                    for (int q = 0; q < kTrips; ++q)
 #pragma unroll
-                        for (int c = 0; c < kCPT; ++c) {
-                            if constexpr (SEQ) {
-                                // batch visit: circles outside the batch take the far point
-                                jv[c] = sh.list[t][tid + c * kDB];
-                                if (masked) jv[c] = use[c] ? jv[c] : kFarOff;
-                            } else {
-                                jv[c] = jn[c];
-                                jn[c] = sh.list[tn][tid + c * kDB];
+                        for (int c = 0; c < kCPT; ++c) jn[q][c] = sh.list[q][tid + c * kDB];
+                    for (int t = 0; t < mm; t += kTrips) {
+                        int jv[kTrips][kCPT];
+                        float2 pj[kTrips][kCPT];
+                        const int tn = t + kTrips < ELL ? t + kTrips : ELL - kTrips;
+#pragma unroll
+                        for (int q = 0; q < kTrips; ++q)
+#pragma unroll
+                            for (int c = 0; c < kCPT; ++c) {
+                                if constexpr (SEQ) {
+                                    // batch visit: circles outside the batch take the far point
+                                    jv[q][c] = sh.list[t + q][tid + c * kDB];
+                                    if (masked) jv[q][c] = use[c] ? jv[q][c] : kFarOff;
+                                } else {
+                                    jv[q][c] = jn[q][c];
+                                    jn[q][c] = sh.list[tn + q][tid + c * kDB];
+                                }
                             }
-                        }
 #pragma unroll
-                        for (int c = 0; c < kCPT; ++c)
-                            pj[c] = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(sh.pos) + jv[c]);
+                        for (int q = 0; q < kTrips; ++q)
 #pragma unroll
-                        for (int c = 0; c < kCPT; ++c) {
-                            const int i = tid + c * kDB;
-                            const int jb = jv[c];
-                            const float2 q = xt[c];
-                            // each pair once: from its lower index, or (batch
-                            // energy, Eq. 7) from the batch's end
-                            bool hf = jb > i * (int)sizeof(float2);
-                            if constexpr (SEQ) {
-                                const int jj = jb / (int)sizeof(float2);
-                                if (masked) hf = hf || sq.bat[jj < kNM ? jj : kNM - 1] != cb;
+                            for (int c = 0; c < kCPT; ++c)
+                                pj[q][c] = *reinterpret_cast<const float2 *>(
+                                    reinterpret_cast<const char *>(sh.pos) + jv[q][c]);
+#pragma unroll
+                        for (int q = 0; q < kTrips; ++q)
+#pragma unroll
+                            for (int c = 0; c < kCPT; ++c) {
+                                const int i = tid + c * kDB;
+                                const int jb = jv[q][c];
+                                const float2 xq = xt[c];
+                                // each pair once: from its lower index, or (batch
+                                // energy, Eq. 7) from the batch's end
+                                bool hf = jb > i * (int)sizeof(float2);
+                                if constexpr (SEQ) {
+                                    const int jj = jb / (int)sizeof(float2);
+                                    if (masked) hf = hf || sq.bat[jj < kNM ? jj : kNM - 1] != cb;
+                                }
+                                float l2;
+                                const float il = pair_term32s(xq, pj[q][c], hf, two_r, four_r2, four_r2_band,
+                                                              ecA[c], e1cA[c], gxA[c], gyA[c], l2, kE1);
+                                // FP64 energies only where FP32 sees (nearly) an overlap:
+                                // outside a 1e-5 band the FP64 terms are zero
+                                if (kW64 && hf && l2 < four_r2_band)
+                                    pair_term64s(xq, pj[q][c], l2 * il, il, two_r64, four_r2_64, eocA[c], etcA[c]);
                             }
-                            float l2;
-                            const float il = pair_term32s(q, pj[c], hf, two_r, four_r2, four_r2_band,
-                                                          ecA[c], e1cA[c], gxA[c], gyA[c], l2, kE1);
-                            // FP64 energies only where FP32 sees (nearly) an overlap:
-                            // outside a 1e-5 band the FP64 terms are zero
-                            if (kW64 && hf && l2 < four_r2_band)
-                                pair_term64s(q, pj[c], l2 * il, il, two_r64, four_r2_64, eocA[c], etcA[c]);
-                        }
                     }
                 };
                 using T_ = std::true_type;
@@ -1139,6 +1156,8 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     double eoc = eocA[c], etc = etcA[c];
                     if (overflow) {
                         // list overflow: every circle of the 3 x 3 cells
+                        const Grid grid = the_grid();
+                        const double two_r64 = 2.0 * (double)opaque(rad), four_r2_64 = two_r64 * two_r64;
                         const int cx = cell_coord(q.x, grid), cy = cell_coord(q.y, grid);
                         const int y0 = cy > 0 ? cy - 1 : 0, y1 = cy < grid.nc - 1 ? cy + 1 : grid.nc - 1;
                         const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < grid.nc - 1 ? cx + 1 : grid.nc - 1;
@@ -1154,7 +1173,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                                 pair_term32(q, pj, hf, two_r, four_r2, ec, e1c, gx, gy);
                                 if (want64 && hf) {
                                     const float dx = q.x - pj.x, dy = q.y - pj.y;
-                                    if (dx * dx + dy * dy < four_r2_band)
+                                    if (dot2(dx, dx, dy, dy) < four_r2_band)
                                         pair_term64(q, pj, two_r64, four_r2_64, eoc, etc);
                                 }
                             }
@@ -1165,9 +1184,8 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     eo += eoc;
                     et += etc;
                     // containment (branch-free, as the pair term)
-                    const float r2 = q.x * q.x + q.y * q.y;
+                    const float r2 = dot2(q.x, q.x, q.y, q.y);
                     const float ir = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
-                    // |c_i| rounded on its own: the same bits in every workgroup shape
                     const float rho = mul_rounded(r2, ir);
                     const float d0 = fmaxf(rho + rad - Rt, 0.f);
                     e += d0 * d0;
@@ -1182,10 +1200,10 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     gy += kc * q.y;
                     if (want64) {
                         const double r64 =
-                            sqrt64_from32((double)q.x * q.x + (double)q.y * q.y, rho, ir);
-                        const double c0 = r64 + rad64 - R64;
+                            sqrt64_from32(dot2((double)q.x, (double)q.x, (double)q.y, (double)q.y), rho, ir);
+                        const double c0 = r64 + (double)opaque(rad) - sh.R64;
                         if (c0 > 0.0) eo += c0 * c0;
-                        const double ct = r64 + 1.0 - R64;
+                        const double ct = r64 + 1.0 - sh.R64;
                         if (ct > 0.0) et += ct * ct;
                     }
                     // E sums over every circle: a non-finite position makes it NaN
@@ -1198,19 +1216,21 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 yc[c] = inb[c] ? make_float2(gx - g[c].x, gy - g[c].y) : make_float2(0.f, 0.f);
             }
             // ---- fused reduction: 63 dot products and E in one pass ----------
-            const float wsum = wave_reduce_scatter(gt, sc, yc, S, Y, e, e1);
+            const float wsum = wave_reduce_scatter<(kDB > 256)>(gt, sc, yc, S, Y, e, e1);
             sh.red[par][wv][lane_slot(lane)] = wsum;
             if (want64) {
                 const double wo = wave_sum_dpp(eo), wt = wave_sum_dpp(et);
                 if (lane == 0) { sh.red64[par][wv][0] = wo; sh.red64[par][wv][1] = wt; }
             }
-            __syncthreads();                                            // B2
+            // What the deciding wave needs beside the totals is read before the
+            // barrier, while it waits for the others: the constants, the
+            // source slots of its lanes' Gram update, and the lanes' places in
+            // the ring with and without a pushed pair.
+            float c1 = 0.f, eps_curv = 0.f, ftol = 0.f, g_tol_sq = 0.f, rho_0 = 0.f, rho_1 = 0.f;
+            double tau64 = 0.0, e_feasible = 0.0;
+            int mm = 0, max_halvings = 0, max_iter = 0, hd_1 = 0;
+            uint32_t pa = 0, rt_0 = 0, rt_1 = 0;
             if constexpr (SOLO) {
-                // ---- one wave decides ----------------------------------------
-                // The uniform chain (slot totals, line search, Gram matrix,
-                // stop tests, two-loop) runs on wave 0 alone: on every wave it
-                // would share each SIMD with a copy of itself.  The outcome
-                // reaches the other waves through LDS behind one barrier.
                 if (wv == 0) {
                     auto ufl = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
                     auto udb = [](double v) {
@@ -1219,14 +1239,43 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                         const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
                         return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
                     };
-                    const float c1 = ufl(sh.dk.c1), eps_curv = ufl(sh.dk.eps_curv), ftol = ufl(sh.dk.ftol);
-                    const float g_tol_sq = ufl(sh.dk.g_tol_sq);
-                    const double tau64 = udb(sh.dk.tau64), e_feasible = udb(sh.dk.e_feasible);
-                    const int mm = __builtin_amdgcn_readfirstlane(sh.dk.m);
-                    const int max_halvings = __builtin_amdgcn_readfirstlane(sh.dk.max_halvings);
-                    const int max_iter = __builtin_amdgcn_readfirstlane(sh.dk.max_iter);
-                    // source slots of this lane's Gram update (read early)
-                    const uint32_t pa = sh.bperm[lane];
+                    c1 = ufl(sh.dk.c1);
+                    eps_curv = ufl(sh.dk.eps_curv);
+                    ftol = ufl(sh.dk.ftol);
+                    g_tol_sq = ufl(sh.dk.g_tol_sq);
+                    tau64 = udb(sh.dk.tau64);
+                    e_feasible = udb(sh.dk.e_feasible);
+                    mm = __builtin_amdgcn_readfirstlane(sh.dk.m);
+                    max_halvings = __builtin_amdgcn_readfirstlane(sh.dk.max_halvings);
+                    max_iter = __builtin_amdgcn_readfirstlane(sh.dk.max_iter);
+                    pa = sh.bperm[lane];
+                    hd_1 = hd == kMM - 1 ? 0 : hd + 1;
+                    rt_0 = sh.ringtab[hd][lane];
+                    rt_1 = sh.ringtab[hd_1][lane];
+                    if constexpr (!SEQ) {
+                        // 1 / s_j'y_j of the lane's pair without and with a
+                        // pushed pair (that pair's own is put in below)
+                        const int jp = lane < kMM ? lane : lane < 2 * kMM ? lane - kMM : 0;
+                        const int q0 = jp + hd, q1 = jp + hd_1;
+                        rho_0 = sh.rho[0][q0 >= kMM ? q0 - kMM : q0];
+                        rho_1 = sh.rho[0][q1 >= kMM ? q1 - kMM : q1];
+                    }
+                }
+            }
+            __syncthreads();                                            // B2
+            if constexpr (SOLO) {
+                // ---- one wave decides ----------------------------------------
+                // The uniform chain (slot totals, line search, Gram matrix,
+                // stop tests, two-loop) runs on wave 0 alone: on every wave it
+                // would share each SIMD with a copy of itself.  The outcome
+                // reaches the other waves through LDS behind one barrier.  The
+                // chain is bound by latency (a lone wave, one dependent step
+                // after another), so its LDS reads are issued as early as
+                // their addresses are known and the selects of the two-loop
+                // are lane writes: 4.1k -> 3.0k cycles of an evaluation's
+                // 16.4k at n = 1000.
+                if (wv == 0) {
+                    auto ufl = [](float v) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
                     float tot = 0.f;
 #pragma unroll
                     for (int w = 0; w < kDW; ++w) tot += sh.red[par][w][lane];
@@ -1283,13 +1332,22 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                         else if (L == sE1) corr = 0.f;
                         tot += corr;
                     }
+                    // the lane's new Gram entries should the step be taken
+                    // and its pair pushed: <g, b_l>, <s, b_l>, <y, b_l>
+                    const int ti = __builtin_bit_cast(int, tot);
+                    const int vg_1 = __builtin_amdgcn_ds_bpermute((int)__builtin_amdgcn_ubfe(pa, 8u, 8u), ti);
+                    const int vs_1 = __builtin_amdgcn_ds_bpermute((int)__builtin_amdgcn_ubfe(pa, 16u, 8u), ti);
+                    const int vy_1 = __builtin_amdgcn_ds_bpermute((int)__builtin_amdgcn_ubfe(pa, 24u, 8u), ti);
                     const float Et = lane_value(tot, sE);
                     const float E1t = lane_value(tot, sE1);
                     // batch descent: more than one batch, visited in turn
                     const bool vis = SEQ && visits;
                     int fl = 0;
+                    float gam_dec = 1.f;
                     bool accept = false, push = false;
                     bool vend = false;         // batch descent: the visit ends with this evaluation
+                    float rho_l = rho_0;       // 1 / s_j'y_j of the lane's pair
+                    uint32_t row_off = rt_0 & 0xffffu;   // byte offset of the lane's row in the ring
                     if (vis && req == kReqTotal) {
                         // ---- top of an outer iteration: stop tests on the
                         // whole instance (FP64 energies of every circle), then
@@ -1350,40 +1408,40 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                             // Lane l (pair order of the updated basis) takes its
                             // entries <g, b_l> and, on a push, <s, b_l> and
                             // <y, b_l> of the new pair from the slot totals.
-                            const int hd_old = hd;
+                            float *ring = sh.Bring;
+                            const uint32_t rt = push ? rt_1 : rt_0;
+                            float *rowl = reinterpret_cast<float *>(reinterpret_cast<char *>(ring) + (rt & 0xffffu));
+                            const int c0 = (int)__builtin_amdgcn_ubfe(rt, 16u, 8u), c1c = (int)(rt >> 24);
+                            rho_l = push ? rho_1 : rho_0;
+                            // (lanes past g write what g's lane writes: no
+                            // slower than leaving them out)
+                            float vg;
                             if (push) {
-                                hd = hd == kMM - 1 ? 0 : hd + 1;
-                                k = k + 1 > mm ? mm : k + 1;
-                            }
-                            const int ti = __builtin_bit_cast(int, tot);
-                            const float vg = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(
-                                                 (int)__builtin_amdgcn_ubfe(pa, push ? 8u : 0u, 8u), ti));
-                            const int sto = ring_at(lane < kNB ? lane : kG);      // storage slot of b_l
-                            const int c0 = ring_col(sto);
-                            const int c1c = sto < kG ? c0 + kMM : c0;             // its two columns
-                            float *rowl = &sh.Bring[sto * kRS];
-                            if (lane < kNB) {
-                                sh.Bring[kG * kRS + c0] = vg;
-                                sh.Bring[kG * kRS + c1c] = vg;
-                                rowl[4 * kMM] = vg;
-                            }
-                            if (push) {
-                                const float vs = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(
-                                                     (int)__builtin_amdgcn_ubfe(pa, 16u, 8u), ti));
-                                const float vy = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(
-                                                     (int)__builtin_amdgcn_ubfe(pa, 24u, 8u), ti));
-                                if (lane < kNB) {
-                                    sh.Bring[hd_old * kRS + c0] = vs;
-                                    sh.Bring[hd_old * kRS + c1c] = vs;
-                                    sh.Bring[(kMM + hd_old) * kRS + c0] = vy;
-                                    sh.Bring[(kMM + hd_old) * kRS + c1c] = vy;
-                                    rowl[hd_old] = vs;
-                                    rowl[kMM + hd_old] = vs;
-                                    rowl[2 * kMM + hd_old] = vy;
-                                    rowl[3 * kMM + hd_old] = vy;
+                                const float vs = __builtin_bit_cast(float, vs_1), vy = __builtin_bit_cast(float, vy_1);
+                                vg = __builtin_bit_cast(float, vg_1);
+                                ring[hd * kRS + c0] = vs;
+                                ring[hd * kRS + c1c] = vs;
+                                ring[(kMM + hd) * kRS + c0] = vy;
+                                ring[(kMM + hd) * kRS + c1c] = vy;
+                                rowl[hd] = vs;
+                                rowl[kMM + hd] = vs;
+                                rowl[2 * kMM + hd] = vy;
+                                rowl[3 * kMM + hd] = vy;
+                                if constexpr (!SEQ) {
+                                    const float r = 1.f / lane_value(tot, sScYc);
+                                    sh.rho[0][hd] = r;
+                                    rho_l = (lane == kMM - 1 || lane == 2 * kMM - 1) ? r : rho_l;
                                 }
-                                if (!SEQ && lane == 0) sh.rho[0][hd_old] = 1.f / lane_value(tot, sScYc);
+                                hd = hd_1;
+                                k = k + 1 > mm ? mm : k + 1;
+                            } else {
+                                vg = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(
+                                         (int)__builtin_amdgcn_ubfe(pa, 0u, 8u), ti));
                             }
+                            ring[kG * kRS + c0] = vg;
+                            ring[kG * kRS + c1c] = vg;
+                            rowl[4 * kMM] = vg;
+                            row_off = rt & 0xffffu;
                             if constexpr (ADJ) {
                                 if (push) {             // shift the radius components like S and Y
                                     const int L = lane;
@@ -1446,6 +1504,27 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                         }
                         if (!(fl & (kDecNext | kDecStop))) {
                             // ---- top of an iteration: stop tests, direction
+                            // this lane's row of the updated B in pair order:
+                            // contiguous from offset hd in the ring row (read
+                            // here, so that the stop tests run meanwhile)
+                            float Bc[kNB];
+                            {
+                                const float *row = reinterpret_cast<const float *>(
+                                    reinterpret_cast<const char *>(sh.Bring) + row_off) + hd;
+#pragma unroll
+                                for (int j = 0; j < kMM; ++j) {
+                                    Bc[j] = row[j];
+                                    Bc[kMM + j] = row[2 * kMM + j];
+                                }
+                                Bc[kG] = row[4 * kMM - hd];
+                                if constexpr (SEQ) {
+                                    // 1 / s_j'y_j from the row (no store of it per batch):
+                                    // lane j reads <s_j, y_j>, lane 10 + j <y_j, s_j>
+                                    rho_l = 1.f / row[lane < kMM ? 2 * kMM + lane : (lane < 2 * kMM ? lane - kMM : 0)];
+                                }
+                            }
+                            const int jp = lane < kMM ? lane : lane - kMM;
+                            const bool live = lane < 2 * kMM && jp >= kMM - k;
                             // |g| <= g_tol and |g| finite, decided on |g|^2 (no
                             // square root: g_tol_sq is the largest value whose
                             // square root is at most g_tol).  The tests are
@@ -1462,50 +1541,30 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                             } else {
                                 const double Eacc = fp64 ? E64o : (double)E;
                                 const int itn = itw == W ? 0 : itw + 1;       // (it + 1) mod (W + 1)
-                                const bool dtl = ftol > 0.f && it >= W && decreased_too_little(Eacc, itn, ftol);
-                                status = (!isfinite(E) || !isfinite(gg0)) ? 6
-                                       : (fp64 && E64t < e_feasible)      ? 1
-                                       : gg0 <= g_tol_sq                   ? 2
-                                       : dtl                               ? 3
-                                       : it >= max_iter                    ? 5 : 0;
+                                // every test evaluated, one branch on all of them
+                                const bool t6 = !isfinite(E + gg0) && !(isfinite(E) && isfinite(gg0));
+                                const bool t1 = fp64 & (E64t < e_feasible);
+                                const bool t2 = gg0 <= g_tol_sq;
+                                const bool t3 = (ftol > 0.f) & (it >= W) & decreased_too_little(Eacc, itn, ftol);
+                                const bool t5 = it >= max_iter;
+                                status = 0;
+                                if (t6 | t1 | t2 | t3 | t5) status = t6 ? 6 : t1 ? 1 : t2 ? 2 : t3 ? 3 : 5;
                                 if (lane == itw) ehist = Eacc;                // read above before written
                             }
-                            // this lane's row of the updated B in pair order:
-                            // contiguous from offset hd in the ring row
-                            float Bc[kNB];
-                            const int jp = lane < kMM ? lane : lane - kMM;
-                            const bool live = lane < 2 * kMM && jp >= kMM - k;
-                            float rho_l;
-                            {
-                                const float *row = &sh.Bring[ring_at(lane < kNB ? lane : kG) * kRS + hd];
-#pragma unroll
-                                for (int j = 0; j < kMM; ++j) {
-                                    Bc[j] = row[j];
-                                    Bc[kMM + j] = row[2 * kMM + j];
-                                }
-                                Bc[kG] = row[4 * kMM - hd];
-                                if constexpr (SEQ) {
-                                    // 1 / s_j'y_j from the row (no store of it per batch):
-                                    // lane j reads <s_j, y_j>, lane 10 + j <y_j, s_j>
-                                    rho_l = 1.f / row[lane < kMM ? 2 * kMM + lane : (lane < 2 * kMM ? lane - kMM : 0)];
-                                } else {
-                                    rho_l = sh.rho[0][ring_at(lane < 2 * kMM ? jp : 0)];
-                                }
-                            }
-                            float cs_v, alph_v, gam;
-                            const float gpv = two_loop_core(lane, Bc, live ? rho_l : 0.f, cs_v, alph_v, gam);
+                            float cf, gam;
+                            const float gpv = two_loop(Bc, live ? rho_l : 0.f, cf, gam);
                             if (status != 0) {
                                 fl |= kDecStop;
                             } else {
                                 gp = gpv;
                                 if constexpr (ADJ) {
                                     // radius component of the direction
-                                    const float cy_v = -gam * alph_v;
+                                    const float cy_v = -gam * cf;
                                     float pr = -gam * gR;
 #pragma unroll
                                     for (int j = 0; j < kMM; ++j)
-                                        pr -= lane_value(cs_v, j) * lane_value(hR_v, j) +
-                                              lane_value(cy_v, j) * lane_value(hR_v, kMM + j);
+                                        pr -= lane_value(cf, j) * lane_value(hR_v, j) +
+                                              lane_value(cy_v, kMM + j) * lane_value(hR_v, kMM + j);
                                     pR = pr;
                                 }
                                 if (k > 0 && !(gp < 0.f)) {
@@ -1518,30 +1577,30 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                                 else alpha = 1.f / fmaxf(1.f, sqrtf(gg0));
                                 h = 0;
                                 req = kReqTrial;
-                                if (lane < kMM) {
-                                    sh.coef[0][lane] = cs_v;
-                                    sh.coef[1][lane] = -gam * alph_v;
-                                }
-                                if (lane == 0) sh.dec_gam = gam;
+                                if (lane < 2 * kMM)
+                                    reinterpret_cast<float *>(sh.coef)[lane] = lane < kMM ? cf : -gam * cf;
+                                gam_dec = gam;
                             }
                         }
                     }
                     if (lane == 0) {
-                        sh.dec_flags = fl;
-                        sh.dec_req = req;
-                        sh.dec_fp64 = fp64 ? 1 : 0;
-                        sh.dec_alpha = alpha;
-                        sh.dec_cb = cb;
+                        sh.dec = make_int4(fl | (fp64 ? kDecFp64 : 0) | (req << kDecReq) | (cb << kDecBatch),
+                                           __builtin_bit_cast(int, alpha),
+                                           __builtin_bit_cast(int, gam_dec), 0);
                         if constexpr (ADJ) { sh.dec_Rz = Rz; sh.dec_pR = pR; }
                     }
                 }
                 __syncthreads();                                        // B3
-                const int fl = __builtin_amdgcn_readfirstlane(sh.dec_flags);
-                req = __builtin_amdgcn_readfirstlane(sh.dec_req);
-                fp64 = __builtin_amdgcn_readfirstlane(sh.dec_fp64) != 0;
-                alpha = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
-                                                      __builtin_bit_cast(int, sh.dec_alpha)));
-                if constexpr (SEQ) cb = __builtin_amdgcn_readfirstlane(sh.dec_cb);
+                const int4 dv = sh.dec;
+                // the direction's coefficients, in flight beside the decision
+                float4 cv[2 * kMM / 4];
+#pragma unroll
+                for (int q = 0; q < 2 * kMM / 4; ++q) cv[q] = sh.coef[q];
+                const int fl = __builtin_amdgcn_readfirstlane(dv.x);
+                req = (fl >> kDecReq) & 0xff;
+                fp64 = (fl & kDecFp64) != 0;
+                alpha = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(dv.y));
+                if constexpr (SEQ) cb = fl >> kDecBatch;
                 if constexpr (ADJ) {
                     Rz = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sh.dec_Rz)));
                     pR = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, sh.dec_pR)));
@@ -1571,15 +1630,19 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                         p[c] = (!SEQ || !visits || batc_of(c) == cb) ? make_float2(-g[c].x, -g[c].y)
                                                                   : make_float2(0.f, 0.f);
                 } else {
-                    const float gam = sh.dec_gam;
+                    const float gam = __builtin_bit_cast(float, dv.z);
+                    const float cf[2 * kMM] = {cv[0].x, cv[0].y, cv[0].z, cv[0].w, cv[1].x, cv[1].y, cv[1].z,
+                                               cv[1].w, cv[2].x, cv[2].y, cv[2].z, cv[2].w, cv[3].x, cv[3].y,
+                                               cv[3].z, cv[3].w, cv[4].x, cv[4].y, cv[4].z, cv[4].w};
 #pragma unroll
                     for (int c = 0; c < kCPT; ++c) {
-                        float px = -gam * g[c].x, py = -gam * g[c].y;
+                        float px = 0.f, py = 0.f;
 #pragma unroll
                         for (int j = 0; j < kMM; ++j) {
-                            const float csj = sh.coef[0][j], cyj = sh.coef[1][j];
-                            px -= csj * as_f2(S[c][j]).x + cyj * as_f2(Y[c][j]).x;
-                            py -= csj * as_f2(S[c][j]).y + cyj * as_f2(Y[c][j]).y;
+                            const float tx = dot2(cf[j], as_f2(S[c][j]).x, cf[kMM + j], as_f2(Y[c][j]).x);
+                            const float ty = dot2(cf[j], as_f2(S[c][j]).y, cf[kMM + j], as_f2(Y[c][j]).y);
+                            px = j == 0 ? fmaf(-gam, g[c].x, -tx) : px - tx;
+                            py = j == 0 ? fmaf(-gam, g[c].y, -ty) : py - ty;
                         }
                         p[c] = (!SEQ || !visits || batc_of(c) == cb) ? make_float2(px, py)
                                                                   : make_float2(0.f, 0.f);
@@ -1700,7 +1763,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
             }
 
             // ================= top of an iteration: stop tests =================
-            const float gg = sh.Bm[cur][kG * kNB + kG];
+            const float gg = sh.Bm[cur][DENSE ? kG * kNB + kG : 0];
             const float gn = sqrtf(fmaxf(gg, 0.f));
             if (SEQ && visits) {
                 // a visit's first evaluation: its gradient norm joins the sum
@@ -1716,29 +1779,8 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 if (it >= A.max_iter) { status = 5; break; }
             }
 
-            if constexpr (DENSE) {
-                // ================= direction: p = -H_p g (Eq. 8) ==================
-                gp = dense_direction();
-            } else {
-                // ================= direction: two-loop recursion on B ===============
-                float cs_v, alph_v, gam;
-                gp = two_loop(lane, 0, cs_v, alph_v, gam);
-                {
-                    const float cy_v = -gam * alph_v;                 // coefficient of y_j at lane j
-    #pragma unroll
-                    for (int c = 0; c < kCPT; ++c) {
-                        float px = -gam * g[c].x, py = -gam * g[c].y;
-    #pragma unroll
-                        for (int j = 0; j < kMM; ++j) {
-                            const float csj = lane_value(cs_v, j), cyj = lane_value(cy_v, j);
-                            px -= csj * as_f2(S[c][j]).x + cyj * as_f2(Y[c][j]).x;
-                            py -= csj * as_f2(S[c][j]).y + cyj * as_f2(Y[c][j]).y;
-                        }
-                        p[c] = (!SEQ || !visits || batc_of(c) == cb) ? make_float2(px, py)
-                                                                  : make_float2(0.f, 0.f);
-                    }
-                }
-            }
+            // ================= direction: p = -H_p g (Eq. 8) ==================
+            gp = dense_direction();
             if (k > 0 && !(gp < 0.f)) {
                 k = 0;
                 if constexpr (DENSE) dense_reset();

@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                     const int K = rl[0] + rl[1] + rl[2];
                     // the wave walks its longest run, four candidates per step with their
                     // reads in flight; FP32 test outside the +-1e-5 band around the
-                    // cutoff, FP64 inside (near_cut), behind one uniform branch
+                    // cutoff, FP64 inside, behind one uniform branch
                     const int kmax = wave_max_dpp(K);
                     int m = 0;
                     for (int k0 = 0; k0 < kmax; k0 += 4) {
@@ -497,7 +497,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                         ++evals;
                         cell_mine += (far || overflow) ? 1 : 0;
                         pair_mine += pe;
-                        return wave_reduce_scatter<kGCPB>(gt, sc, yc, S, Y, e, e1);
+                        return wave_reduce_scatter<true>(gt, sc, yc, S, Y, e, e1);
                     };
 
                     // ---- gradient at the start of the visit (Alg. 1) -----
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                         const int K = rl[0] + rl[1] + rl[2];
                         // the wave walks its longest run, four candidates per step with their
                         // reads in flight; FP32 test outside the +-1e-5 band around the
-                        // cutoff, FP64 inside (near_cut), behind one uniform branch
+                        // cutoff, FP64 inside, behind one uniform branch
                         const int kmax = wave_max_dpp(K);
                         int m = 0;
                         for (int k0 = 0; k0 < kmax; k0 += 4) {

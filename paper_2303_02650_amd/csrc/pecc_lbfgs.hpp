@@ -93,14 +93,19 @@ __device__ __forceinline__ void push_history(double (&H)[kMM], double v)
         : "v"(v));
 }
 
-// a * b rounded on its own: never the product of a fused multiply-add (which
-// of several sums a product fuses into is the compiler's choice, and it
-// differs between instantiations of one kernel).
-__device__ __forceinline__ float mul_rounded(float a, float b)
+// Products and sums of two products with their roundings written out.  Which
+// product of a sum the compiler fuses is its choice, and it differs between
+// instantiations of one kernel; these have the same bits in all of them.
+//   mul_rounded  a * b, never fused
+//   dot2         a b + c d as fma(a, b, c d)
+template <typename T>
+__device__ __forceinline__ T mul_rounded(T a, T b)
 {
 #pragma clang fp contract(off)
     return a * b;
 }
+__device__ __forceinline__ float dot2(float a, float b, float c, float d) { return fmaf(a, b, mul_rounded(c, d)); }
+__device__ __forceinline__ double dot2(double a, double b, double c, double d) { return fma(a, b, mul_rounded(c, d)); }
 
 // Value of reduction slot v summed over this thread's circles (v is a
 // constant after unrolling, so the branches fold away): one FMA chain over
@@ -185,6 +190,67 @@ __device__ __forceinline__ float wave_sum_dpp(float v)
     return lane_value(v, 63);
 }
 
+// The two halves of the two-loop recursion on the Gram matrix (ten pairs,
+// lane l holding row l of it): per step one product, its lane's value to a
+// scalar, one FMA on every lane, and the scalar written into the one lane of
+// cf that keeps it (in the wait state between the product and its lane read).
+//   down, j = 9 .. 0:  a = lane j of rho * acc;         acc -= a * b[j];  lane 10 + j of cf = a
+//   up,   j = 0 .. 9:  a = lane 10 + j of cf - rho acc;  acc += a * b[j];  lane j of cf = a
+// In asm because the language has no lane write here (a compare, a move and
+// a select per step take twice the chain's own instructions).  The wait
+// states are those of a VALU result read by v_readlane (one) and of an SGPR
+// it wrote read by a VALU instruction (two).
+#define PECC_LOOP_STEP(FIRST, FILL, SRC, S, SIGN, J)                                                  \
+    FIRST "\n\t" FILL "\n\tv_readlane_b32 %[" S "], %[t], " #SRC "\n\ts_nop 1\n\tv_fma_f32 %[acc], " SIGN \
+    "%[b" #J "], %[" S "], %[acc]\n\t"
+#define PECC_LOOP_KEEP(S, L) "v_writelane_b32 %[cf], %[" S "], " #L
+#define PECC_DOWN(FILL, S, J) PECC_LOOP_STEP("v_mul_f32 %[t], %[rho], %[acc]", FILL, J, S, "-", J)
+#define PECC_UP(FILL, SRC, S, J) PECC_LOOP_STEP("v_fma_f32 %[t], -%[rho], %[acc], %[cf]", FILL, SRC, S, "", J)
+#define PECC_LOOP_OPERANDS                                                                            \
+    : [acc] "+v"(acc), [cf] "+v"(cf), [t] "=&v"(t), [s0] "=&s"(s0), [s1] "=&s"(s1)                    \
+    : [rho] "v"(rho), [b0] "v"(b[0]), [b1] "v"(b[1]), [b2] "v"(b[2]), [b3] "v"(b[3]), [b4] "v"(b[4]), \
+      [b5] "v"(b[5]), [b6] "v"(b[6]), [b7] "v"(b[7]), [b8] "v"(b[8]), [b9] "v"(b[9])
+__device__ __forceinline__ void two_loop_down(const float *b, float rho, float &acc, float &cf)
+{
+    float t;
+    int s0, s1;
+    asm(PECC_DOWN("s_nop 0", "s0", 9)
+        PECC_DOWN(PECC_LOOP_KEEP("s0", 19), "s1", 8)
+        PECC_DOWN(PECC_LOOP_KEEP("s1", 18), "s0", 7)
+        PECC_DOWN(PECC_LOOP_KEEP("s0", 17), "s1", 6)
+        PECC_DOWN(PECC_LOOP_KEEP("s1", 16), "s0", 5)
+        PECC_DOWN(PECC_LOOP_KEEP("s0", 15), "s1", 4)
+        PECC_DOWN(PECC_LOOP_KEEP("s1", 14), "s0", 3)
+        PECC_DOWN(PECC_LOOP_KEEP("s0", 13), "s1", 2)
+        PECC_DOWN(PECC_LOOP_KEEP("s1", 12), "s0", 1)
+        PECC_DOWN(PECC_LOOP_KEEP("s0", 11), "s1", 0)
+        PECC_LOOP_KEEP("s1", 10) "\n\ts_nop 0"
+        PECC_LOOP_OPERANDS);
+    (void)t;
+    (void)s0;
+    (void)s1;
+}
+__device__ __forceinline__ void two_loop_up(const float *b, float rho, float &acc, float &cf)
+{
+    float t;
+    int s0, s1;
+    asm(PECC_UP("s_nop 0", 10, "s0", 0)
+        PECC_UP(PECC_LOOP_KEEP("s0", 0), 11, "s1", 1)
+        PECC_UP(PECC_LOOP_KEEP("s1", 1), 12, "s0", 2)
+        PECC_UP(PECC_LOOP_KEEP("s0", 2), 13, "s1", 3)
+        PECC_UP(PECC_LOOP_KEEP("s1", 3), 14, "s0", 4)
+        PECC_UP(PECC_LOOP_KEEP("s0", 4), 15, "s1", 5)
+        PECC_UP(PECC_LOOP_KEEP("s1", 5), 16, "s0", 6)
+        PECC_UP(PECC_LOOP_KEEP("s0", 6), 17, "s1", 7)
+        PECC_UP(PECC_LOOP_KEEP("s1", 7), 18, "s0", 8)
+        PECC_UP(PECC_LOOP_KEEP("s0", 8), 19, "s1", 9)
+        PECC_LOOP_KEEP("s1", 9) "\n\ts_nop 0"
+        PECC_LOOP_OPERANDS);
+    (void)t;
+    (void)s0;
+    (void)s1;
+}
+
 // Maximum of a non-negative int over the 64 lanes, returned wave-uniform
 // (lanes a DPP pattern leaves out read 0, which no value is below).
 template <int CTRL, int ROW_MASK = 0xf>
@@ -261,14 +327,19 @@ __device__ __forceinline__ int lane_slot(int L) { return L; }
 // 16-lane rows (a keeps rows 0, 2 and receives b's rows 0, 2 in rows 1, 3; b
 // receives a's rows 1, 3 and keeps its rows 1, 3).  Written as asm because
 // the builtins return one register twice in this compiler; the two wait
-// states cover a VALU write of either operand just before.
-__device__ __forceinline__ void swap32(float &a, float &b)
+// states cover a VALU write of an operand just before, once for all the
+// pairs of a call (the wait states are idle issue cycles: a third of the
+// stage's time while every pair had its own).
+__device__ __forceinline__ void swap32(float (&a)[4], float (&b)[4])
 {
-    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %4\n\tv_permlane32_swap_b32 %1, %5\n\t"
+        "v_permlane32_swap_b32 %2, %6\n\tv_permlane32_swap_b32 %3, %7"
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));
 }
-__device__ __forceinline__ void swap16(float &a, float &b)
+__device__ __forceinline__ void swap16(float &a0, float &b0, float &a1, float &b1)
 {
-    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3"
+        : "+v"(a0), "+v"(b0), "+v"(a1), "+v"(b1));
 }
 
 // Reduce-scatter of the 64 slot values over the wave: afterwards lane L
@@ -280,7 +351,7 @@ __device__ __forceinline__ void swap16(float &a, float &b)
 // whose bit is set keeps the upper slot).  Slots are produced in groups of
 // eight (u + 8k, k = 0..7) that the first three stages consume, so only a
 // few values are live at once.
-template <int CPT, typename HV>
+template <bool STREAM, int CPT, typename HV>
 __device__ __forceinline__ float wave_reduce_scatter(const float2 (&gt)[CPT],
                                                      const float2 (&sc)[CPT],
                                                      const float2 (&yc)[CPT],
@@ -294,24 +365,23 @@ __device__ __forceinline__ float wave_reduce_scatter(const float2 (&gt)[CPT],
     float h[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-        float w[4];
+        float w[4], lo[4], hi[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            float lo = slot_value(u + 8 * k, gt, sc, yc, S, Y, e, e1);
-            float hi = slot_value(u + 8 * k + 32, gt, sc, yc, S, Y, e, e1);
-            swap32(lo, hi);
-            w[k] = lo + hi;            // lanes 0-31: slot u + 8k, lanes 32-63: + 32
+            lo[k] = slot_value(u + 8 * k, gt, sc, yc, S, Y, e, e1);
+            hi[k] = slot_value(u + 8 * k + 32, gt, sc, yc, S, Y, e, e1);
         }
-        float v[2];
+        swap32(lo, hi);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            float lo = w[k], hi = w[k + 2];
-            swap16(lo, hi);
-            v[k] = lo + hi;            // rows 0, 2: slot of w[k]; rows 1, 3: + 16
-        }
+        for (int k = 0; k < 4; ++k) w[k] = lo[k] + hi[k];   // lanes 0-31: slot u + 8k, lanes 32-63: + 32
+        swap16(w[0], w[2], w[1], w[3]);
+        // rows 0, 2: slot of w[k]; rows 1, 3: + 16
+        const float v[2] = {w[0] + w[2], w[1] + w[3]};
         h[u] = (b3 ? v[1] : v[0]) + dpp<kDppRowMirror>(b3 ? v[0] : v[1]);
-        // keep the streaming order: the next group is not hoisted above here
-        __builtin_amdgcn_sched_barrier(0);
+        // STREAM: the next group is not hoisted above here (few values live
+        // at once; without it the groups overlap, which a lone wave per SIMD
+        // needs against the eight cycles of a dependent VALU instruction)
+        if constexpr (STREAM) __builtin_amdgcn_sched_barrier(0);
     }
     float t4[4];
 #pragma unroll
@@ -405,19 +475,6 @@ __device__ __forceinline__ uint32_t gram_perm_bytes(int l)
            ((uint32_t)(4 * slot(1, true)) << 16) | ((uint32_t)(4 * slot(2, true)) << 24);
 }
 
-// FP64 neighbor predicate with an FP32 pre-test.  FP32 evaluation of
-// dx*dx + dy*dy carries a relative error below 3e-7, so outside a band of
-// +-1e-5 around c2 its answer is the FP64 one; inside the band the FP64
-// predicate itself decides.  Same pair set as near64, fewer FP64 ops.
-__device__ __forceinline__ bool near_cut(float2 a, float2 b, float c2lo, float c2hi, double c2)
-{
-    const float dx = a.x - b.x, dy = a.y - b.y;
-    const float l2 = dx * dx + dy * dy;
-    if (l2 < c2lo) return true;
-    if (l2 > c2hi) return false;
-    return near64(a, b, c2);
-}
-
 // ---------------------------------------------------------------------------
 // Counting sort of the n circles of one instance into grid cells, ascending
 // circle index inside every cell, with the positions copied in that order:
@@ -452,10 +509,20 @@ __device__ __forceinline__ void sort_cells(int tid, const float2 (&x)[CPT], int 
         }
     }
     __syncthreads();
+    // a thread's cells: up to four stay in registers (their reads in flight
+    // together), more are read twice
+    constexpr int kReg = 4;
     const int ch = (ncell + BLOCK - 1) / BLOCK;
     const int c0 = tid * ch, c1 = c0 + ch < ncell ? c0 + ch : ncell;
-    int sum = 0;
-    for (int c = c0; c < c1; ++c) sum += cell_start[c];
+    int cnt4[kReg], sum = 0;
+    if (ch <= kReg) {
+#pragma unroll
+        for (int q = 0; q < kReg; ++q) cnt4[q] = q < ch && c0 + q < ncell ? cell_start[c0 + q] : 0;
+#pragma unroll
+        for (int q = 0; q < kReg; ++q) sum += cnt4[q];
+    } else {
+        for (int c = c0; c < c1; ++c) sum += cell_start[c];
+    }
     const int inc = wave_scan_dpp(sum);
     int run = inc - sum;
     if constexpr (NW > 1) {
@@ -465,10 +532,18 @@ __device__ __forceinline__ void sort_cells(int tid, const float2 (&x)[CPT], int 
 #pragma unroll
         for (int q = 0; q < NW - 1; ++q) run += q < w ? scan_tmp[q] : 0;
     }
-    for (int c = c0; c < c1; ++c) {
-        const int v = cell_start[c];
-        cell_start[c] = run;
-        run += v;
+    if (ch <= kReg) {
+#pragma unroll
+        for (int q = 0; q < kReg; ++q) {
+            if (q < ch && c0 + q < ncell) cell_start[c0 + q] = run;
+            run += cnt4[q];
+        }
+    } else {
+        for (int c = c0; c < c1; ++c) {
+            const int v = cell_start[c];
+            cell_start[c] = run;
+            run += v;
+        }
     }
     if (tid == 0) cell_start[ncell] = n;
     __syncthreads();
@@ -485,7 +560,13 @@ __device__ __forceinline__ void sort_cells(int tid, const float2 (&x)[CPT], int 
     for (int u = 0; u < CPT; ++u) {
         const int i = tid + u * BLOCK;
         int r = a[u];
-        for (int t = a[u]; t < z[u]; ++t) r += (int)tmp[t] < i ? 1 : 0;
+        for (int t = a[u]; t < z[u]; t += 4) {       // four reads in flight
+            int v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = tmp[t + q < z[u] ? t + q : t];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) r += (t + q < z[u] && v[q] < i) ? 1 : 0;
+        }
         own[u] = r;
         if (i < n) {
             cell_circ[r] = (uint16_t)i;
@@ -517,6 +598,19 @@ __device__ __forceinline__ void cell_rows(float2 p, bool act, int own, const Gri
     self = cy > y0 ? rl[0] + own - ra[1] : own - ra[0];
 }
 
+// The lowest bit of a candidate mask taken: candidate k of three runs (k < n0:
+// slot k + s0, k < n01: k + s1, else k + s2); j receives its circle.  False
+// (and some circle) when the mask is empty.
+__device__ __forceinline__ bool next_neighbor(unsigned long long &mask, int n0, int n01, int s0, int s1,
+                                              int s2, const uint16_t *cell_circ, int &j)
+{
+    const bool has = mask != 0;
+    const int k = __builtin_ctzll(mask | (1ull << 63));
+    mask &= mask - 1;
+    j = cell_circ[has ? k + (k < n0 ? s0 : k < n01 ? s1 : s2) : 0];
+    return has;
+}
+
 // Neighbor lists of a workgroup's circles (tid + c * BLOCK) into ELL slots,
 // slot-major (list[t * NMAX + i]: byte offset of the t-th neighbor in the
 // position array), in the order of the sorted cells, every list padded with
@@ -532,17 +626,21 @@ __device__ __forceinline__ void cell_rows(float2 p, bool act, int own, const Gri
 // sorted positions -- and everything that only a neighbor needs (its index,
 // the list write) runs over the mask bits, at most 7 or 8 per wave.  The FP64
 // predicate runs for the whole wave when any of its distances falls in the
-// band (at n = 1000 about one wave in a thousand).  The candidate-by-candidate
+// band (at n = 1000 about one wave in a thousand).  PAD: lists are padded to
+// a multiple of it.  The candidate-by-candidate
 // loop this replaces tested, masked and stored about 40 instructions per
 // candidate: a 256 x n = 1000 descent 30.1 -> 28.1 ms, 448 SED candidates of
 // n = 300 .. 1000 17.7 -> 16.8 ms, one start of n = 20 446 -> 405 us.
-template <int BLOCK, int CPT, int ELL, int NMAX>
+template <int BLOCK, int CPT, int ELL, int NMAX, int PAD>
 __device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], const bool (&act)[CPT],
                                            const int (&own)[CPT], const Grid &g,
                                            const int *cell_start, const uint16_t *cell_circ,
                                            const float2 *psort, double c2, uint16_t *list,
                                            uint8_t *list_n, int far_off, int (&up)[CPT], int *over)
 {
+    // candidates of a row per turn: a row has about four, the wave's longest
+    // seven; a lone wave per SIMD reads eight to wait for LDS once
+    constexpr int kCand = CPT == 1 && BLOCK <= 256 ? 8 : 4;
     int ra[CPT][3], rl[CPT][3], self[CPT], cnt[CPT];
     int kmax[3] = {0, 0, 0};
     bool fits = true;              // three runs of at most 32, 64 candidates in all
@@ -567,27 +665,31 @@ __device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], cons
             for (int r = 0; r < 3; ++r) {
 #pragma unroll
                 for (int c = 0; c < CPT; ++c) mr[c][r] = 0;
-                for (int k0 = 0; k0 < kmax[r]; k0 += 4) {
-                    float2 pv[CPT][4];
+                for (int k0 = 0; k0 < kmax[r]; k0 += kCand) {
+                    float px[CPT][kCand], py[CPT][kCand];
                     unsigned bits[CPT];
 #pragma unroll
                     for (int c = 0; c < CPT; ++c) {
                         // past a run's end: any readable position (psort has
-                        // NMAX + 4), its bits are cut off below
+                        // NMAX + 8), its bits are cut off below
                         const float2 *src = psort + min(ra[c][r] + k0, NMAX);
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) pv[c][u] = src[u];
+                        for (int u = 0; u < kCand; ++u) {
+                            const float2 v = src[u];
+                            px[c][u] = v.x;
+                            py[c][u] = v.y;
+                        }
                         bits[c] = 0;
                     }
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
+                    for (int u = 0; u < kCand; ++u)
 #pragma unroll
                         for (int c = 0; c < CPT; ++c) {
                             bool nb;
                             if constexpr (decltype(exact)::value) {
-                                nb = near64(x[c], pv[c][u], c2);
+                                nb = near64(x[c], make_float2(px[c][u], py[c][u]), c2);
                             } else {
-                                const float dx = x[c].x - pv[c][u].x, dy = x[c].y - pv[c][u].y;
+                                const float dx = x[c].x - px[c][u], dy = x[c].y - py[c][u];
                                 const float t = dx * dx + dy * dy - c2f;
                                 nb = t < 0.f;
                                 dmin = fminf(dmin, fabsf(t));
@@ -606,30 +708,49 @@ __device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], cons
                     const unsigned keep = rl[c][r] < 32 ? (1u << rl[c][r]) - 1u : ~0u;
                     mask[c] = (mask[c] << rl[c][r]) | (unsigned long long)(mr[c][r] & keep);
                 }
-                if (act[c]) mask[c] &= ~(1ull << self[c]);
+                mask[c] = act[c] ? mask[c] & ~(1ull << self[c]) : 0ull;
             }
         };
         scan(std::false_type{});
         if (__builtin_amdgcn_ballot_w64(dmin <= band)) scan(std::true_type{});
-        // neighbors: one mask bit of every circle per turn
-        for (;; ++m) {
-            bool any = false;
+        // neighbors: one mask bit of every circle per turn; a turn's index
+        // read is in flight while the next turn's bits are taken (its write
+        // comes one turn later)
+        int cut[CPT], sh1[CPT], sh2[CPT], jv[CPT];
+        bool has[CPT];
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) any = any || mask[c] != 0;
-            if (!__builtin_amdgcn_ballot_w64(any)) break;
+        for (int c = 0; c < CPT; ++c) {
+            cut[c] = rl[c][0] + rl[c][1];
+            sh1[c] = ra[c][1] - rl[c][0];
+            sh2[c] = ra[c][2] - cut[c];
+            up[c] = 0;
+        }
+        // the wave's longest list
+        int longest = 0;
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            cnt[c] = __builtin_popcountll(mask[c]);
+            longest = max(longest, cnt[c]);
+        }
+        m = wave_max_dpp(longest);
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+            has[c] = next_neighbor(mask[c], rl[c][0], cut[c], ra[c][0], sh1[c], sh2[c], cell_circ, jv[c]);
+        for (int q = 0; q < m; ++q) {
+            int jq[CPT];
+            bool hq[CPT];
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) { jq[c] = jv[c]; hq[c] = has[c]; }
+            if (q + 1 < m) {
+#pragma unroll
+                for (int c = 0; c < CPT; ++c)
+                    has[c] = next_neighbor(mask[c], rl[c][0], cut[c], ra[c][0], sh1[c], sh2[c], cell_circ, jv[c]);
+            }
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
                 const int i = tid + c * BLOCK;
-                const bool has = mask[c] != 0;
-                const int k = __builtin_ctzll(has ? mask[c] : 1ull);
-                mask[c] &= mask[c] - 1;
-                const int t = k < rl[c][0]              ? ra[c][0] + k
-                            : k < rl[c][0] + rl[c][1] ? ra[c][1] + (k - rl[c][0])
-                                                      : ra[c][2] + (k - rl[c][0] - rl[c][1]);
-                const int j = cell_circ[has ? t : 0];
-                if (m < ELL) list[m * NMAX + i] = (uint16_t)(has ? j * (int)sizeof(float2) : far_off);
-                cnt[c] += has ? 1 : 0;
-                up[c] += (has && j > i) ? 1 : 0;
+                if (q < ELL) list[q * NMAX + i] = (uint16_t)(hq[c] ? jq[c] * (int)sizeof(float2) : far_off);
+                up[c] += (hq[c] && jq[c] > i) ? 1 : 0;
             }
         }
     } else {
@@ -662,7 +783,14 @@ __device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], cons
             if (cnt[c] > ELL) *over = 1;
             list_n[tid + c * BLOCK] = (uint8_t)min(cnt[c], ELL);
         }
-    return min(m, ELL);
+    m = min(m, ELL);
+    if (PAD > 1 && m % PAD != 0) {       // (ELL is a multiple of PAD)
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+            for (int q = m; q % PAD != 0; ++q) list[q * NMAX + tid + c * BLOCK] = (uint16_t)far_off;
+        m += PAD - m % PAD;
+    }
+    return m;
 }
 
 // FP32 pair term of circle i (at q) with circle j (at pj): energy on the
@@ -675,7 +803,7 @@ __device__ __forceinline__ void pair_term32(float2 q, float2 pj, bool count_e, f
                                             float &gy)
 {
     const float dx = q.x - pj.x, dy = q.y - pj.y;
-    const float l2 = dx * dx + dy * dy;
+    const float l2 = dot2(dx, dx, dy, dy);
     const bool ov = l2 < four_r2;
     const float il = (ov && l2 > 0.f) ? __builtin_amdgcn_rsqf(l2) : 0.f;
     const float d = ov ? two_r - l2 * il : 0.f;
@@ -694,7 +822,7 @@ __device__ __forceinline__ void pair_term64(float2 q, float2 pj, double two_r64,
                                             double &eo, double &et)
 {
     const double ex = (double)q.x - (double)pj.x, ey = (double)q.y - (double)pj.y;
-    const double m2 = ex * ex + ey * ey;
+    const double m2 = dot2(ex, ex, ey, ey);
     if (m2 < four_r2_64) {
         const double l = sqrt(m2);
         const double d = two_r64 - l;
@@ -733,7 +861,7 @@ __device__ __forceinline__ float pair_term32s(float2 q, float2 pj, bool count_e,
 {
     (void)four_r2_band;
     const float dx = q.x - pj.x, dy = q.y - pj.y;
-    const float l2 = dx * dx + dy * dy;
+    const float l2 = dot2(dx, dx, dy, dy);
     const bool ov = l2 < four_r2;
     // + FLT_MIN: a finite inverse for coincident centres; a no-op (exact)
     // for any l2 above 2^-100
@@ -760,7 +888,7 @@ __device__ __forceinline__ void pair_term64s(float2 q, float2 pj, float l32, flo
                                              double &et)
 {
     const double ex = (double)q.x - (double)pj.x, ey = (double)q.y - (double)pj.y;
-    const double m2 = ex * ex + ey * ey;
+    const double m2 = dot2(ex, ex, ey, ey);
     if (m2 < four_r2_64) {
         const double l = sqrt64_from32(m2, l32, il);
         const double d = two_r64 - l;
