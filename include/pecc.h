@@ -348,8 +348,8 @@ int pecc_gbo_kbatch_bfgs_descend(const pecc_instances *inst, float *xy, const in
 
 /* ------------------------------------------------------------------------
  * FP64 feasibility check of Eq. 1-2 through the energy of Def. 3.2 with
- * unit circles: every pair i<j of each instance is enumerated (no list),
- * in FP64 on the FP32 positions.  Per instance: energy64 = E,
+ * unit circles, in FP64 on the FP32 positions (no list: every pair that can
+ * overlap is found from the positions themselves).  Per instance: energy64 = E,
  * max_pair_overlap = max_{i<j} d_ij, max_cont_overlap = max_i d_i0 (both
  * >= 0), feasible = (E < tol).  Any output pointer except energy64 may be
  * NULL.  Radii come from R64 when given, else from R.

@@ -29,15 +29,16 @@ struct Grid {
     int nc;        // cells per axis
 };
 
+template <int NC = kNcMax>             // cells per axis at most
 __device__ __forceinline__ Grid make_grid(float R, float h_req)
 {
     Grid g;
     const float span = 2.0f * R;
     float h = h_req;
-    if (span / (float)kNcMax > h) h = span / (float)kNcMax;
+    if (span / (float)NC > h) h = span / (float)NC;
     float t = span / h;
-    int nc = (t >= 1.0f) ? (int)ceilf(fminf(t, (float)kNcMax)) : 1;
-    if (nc > kNcMax) nc = kNcMax;
+    int nc = (t >= 1.0f) ? (int)ceilf(fminf(t, (float)NC)) : 1;
+    if (nc > NC) nc = NC;
     if (nc < 1) nc = 1;
     g.lo = -R;
     g.inv_h = (h > 0.0f && h < 3.0e38f) ? 1.0f / h : 0.0f;

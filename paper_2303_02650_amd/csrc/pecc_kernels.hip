@@ -5,6 +5,7 @@
 // on chip.
 #include "pecc_device.hpp"
 #include "pecc_launch.hpp"
+#include "pecc_lbfgs.hpp"
 
 #include <type_traits>
 
@@ -745,13 +746,20 @@ __global__ __launch_bounds__(kHalfBlock) __attribute__((amdgpu_waves_per_eu(8, 8
 }
 
 // ---------------------------------------------------------------------------
-// FP64 verify: every pair of the instance once.  Circle i is paired with
-// the next floor((n-1)/2) circles cyclically (and, for even n, with i+n/2
-// when i < n/2), which visits each unordered pair exactly once and gives
-// every thread the same amount of work; the positions sit in LDS twice in
-// a row, so partner i + t needs no wrap.  512 threads per instance, partner
-// positions read four at a time so that LDS latency overlaps.  No
+// FP64 verify: the overlap energy of every pair and every circle, each pair
+// once.  Only pairs closer than 2 contribute, so the circles are sorted into
+// cells of side >= 2 and a circle at slot s meets the slots after it in its
+// own cell row (its cell and the next) and the three cells of the row above:
+// two runs of consecutive positions, about five candidates in all at the
+// densities of packings.  An FP32 distance (within 4e-7) passes the
+// candidates within 1e-5 of an overlap to FP64, in which every term is formed
+// and summed; the others' terms are exactly zero.  Slots are in cell order,
+// then circle order (sort_cells), so every sum has a fixed order.  No
 // contraction: products and sums round as written, like the oracle's.
+// Up to kVerifyBrute circles every pair is tested without a grid: circle i
+// with the next floor((n-1)/2) circles cyclically (and, for even n, with
+// i+n/2 when i < n/2); the positions sit in LDS twice in a row, so partner
+// i + t needs no wrap.
 // With R_tight set it also forms the smallest container of the unit
 // circles, rho_max = max_i fl(|c_i| + 1): at any radius R >= rho_max every
 // containment term (fl(|c_i| + 1) - R) is <= 0, so the layout is feasible
@@ -759,8 +767,15 @@ __global__ __launch_bounds__(kHalfBlock) __attribute__((amdgpu_waves_per_eu(8, 8
 // rho_max rounded up to FP32 when that holds and the value is below the
 // instance's radius, else the instance's FP32 radius; feas_tight[b] is
 // feasibility at R_tight[b].
+// 256 threads and 17 KB of LDS per instance: eight workgroups per CU, so one
+// instance's sort (a chain of LDS round trips and barriers) runs beside the
+// others' distances.  2048 x n = 1000: 26 us, against 277 us with every pair
+// tested in FP64 from LDS; 256 x n = 1000 53 -> 10 us.
 // ---------------------------------------------------------------------------
-constexpr int kVerifyBlock = 512;
+constexpr int kVerifyBlock = 256;
+constexpr int kVerifyCpt = kMaxN / kVerifyBlock;
+constexpr int kVerifyNc = 32;            // cells per axis at most (side 2.2 at n = 1024, R = 35)
+constexpr int kVerifyBrute = 64;         // 2048 instances of 96: 14.8 us tested pair by pair, of 200 sorted 12.9
 
 __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
     const int32_t *__restrict__ offset, const float *__restrict__ R,
@@ -770,13 +785,18 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
     int32_t *__restrict__ feas_tight)
 {
 #pragma clang fp contract(off)
-    __shared__ float2 pos[2 * kMaxN];
-    __shared__ double sum_tmp[kVerifyBlock / kWave];
+    __shared__ float2 psort[kMaxN + 4];
+    __shared__ int cell_start[kVerifyNc * kVerifyNc + 1];
+    __shared__ uint16_t cell_circ[kMaxN];
+    __shared__ uint16_t slot_tmp[kMaxN];
+    __shared__ int scan_tmp[kVerifyBlock / kWave];
+    __shared__ double part[kVerifyBlock / kWave][5];
 
+    const int tid = threadIdx.x;
     const int b = blockIdx.x;
     int off, n;
     if (!instance_range(offset, b, total_n, &off, &n)) {
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             if (energy64) energy64[b] = __builtin_nan("");
             if (max_pair) max_pair[b] = __builtin_nan("");
             if (max_cont) max_cont[b] = __builtin_nan("");
@@ -786,44 +806,87 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
         }
         return;
     }
-    {
-        const float2 *src = reinterpret_cast<const float2 *>(xy) + off;
-        for (int i = threadIdx.x; i < n; i += kVerifyBlock) {
-            const float2 v = src[i];
-            pos[i] = v;
-            pos[i + n] = v;
-        }
+    float2 p[kVerifyCpt];
+#pragma unroll
+    for (int u = 0; u < kVerifyCpt; ++u) {
+        const int i = tid + u * kVerifyBlock;
+        p[u] = i < n ? reinterpret_cast<const float2 *>(xy)[off + i] : make_float2(0.f, 0.f);
     }
-    __syncthreads();
     const double Rb = R64 ? R64[b] : (double)R[b];
     double sp = 0.0, sc = 0.0, mp = 0.0, mc = 0.0, rm = 0.0;
-    const int half = (n - 1) / 2;
-    const bool even = (n & 1) == 0;
-    for (int i = threadIdx.x; i < n; i += kVerifyBlock) {
-        const double xi = pos[i].x, yi = pos[i].y;
-        const int extra = (even && i < n / 2) ? 1 : 0;
-        const int cnt = half + extra;
-        // the overlap branch is rare (never taken once a layout is
-        // feasible): a real branch, not a flattened square root per pair
-        auto pair = [&](float2 pj) {
-            const double dx = xi - (double)pj.x;
-            const double dy = yi - (double)pj.y;
-            const double l2 = dx * dx + dy * dy;
-            if (__builtin_expect(l2 < 4.0, 0)) {
-                const double d = 2.0 - sqrt(l2);
-                sp = sp + d * d;
-                mp = fmax(mp, d);
-            }
-        };
-        int t = 1;
-        for (; t + 3 <= cnt; t += 4) {
-            float2 pj[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pj[u] = pos[i + t + u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pair(pj[u]);
+    // the FP64 term of a pair
+    auto pair = [&](float2 pi, float2 pj) {
+#pragma clang fp contract(off)
+        const double dx = (double)pi.x - (double)pj.x;
+        const double dy = (double)pi.y - (double)pj.y;
+        const double l2 = dx * dx + dy * dy;
+        if (l2 < 4.0) {
+            const double d = 2.0 - sqrt(l2);
+            sp = sp + d * d;
+            mp = fmax(mp, d);
         }
-        for (; t <= cnt; ++t) pair(pos[i + t]);
+    };
+    // FP32 tests: a pair that may overlap, a circle that may reach past R
+    const float near2 = 4.0f * (1.0f + 1e-5f);
+    const double inner = Rb - 1.0;
+    const float lim2 = inner > 0.0 ? (float)(inner * inner * (1.0 - 1e-5)) : -1.0f;
+
+    if (n <= kVerifyBrute) {
+        if (tid < n) {
+            psort[tid] = p[0];
+            psort[tid + n] = p[0];
+        }
+        __syncthreads();
+        const int cnt = (n - 1) / 2 + (((n & 1) == 0 && tid < n / 2) ? 1 : 0);
+        if (tid < n)
+            for (int t = 1; t <= cnt; ++t) {
+                const float2 pj = psort[tid + t];
+                const float dx = p[0].x - pj.x, dy = p[0].y - pj.y;
+                if (dx * dx + dy * dy < near2) pair(p[0], pj);
+            }
+    } else {
+        const Grid g = make_grid<kVerifyNc>(R[b], 2.0f * (1.0f + kCellSafety));
+        int own[kVerifyCpt];
+        sort_cells<kVerifyBlock, kVerifyCpt>(tid, p, n, g, cell_start, cell_circ, slot_tmp, psort,
+                                             scan_tmp, own);
+#pragma unroll
+        for (int u = 0; u < kVerifyCpt; ++u) {
+            const int s = tid + u * kVerifyBlock;
+            const bool on = s < n;
+            p[u] = psort[on ? s : 0];                 // from here on: the circle of slot s
+            const int cx = cell_coord(p[u].x, g), cy = cell_coord(p[u].y, g);
+            const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < g.nc - 1 ? cx + 1 : g.nc - 1;
+            const int up = cy < g.nc - 1 ? cy + 1 : cy;
+            const int a1 = cell_start[up * g.nc + x0], z1 = cell_start[up * g.nc + x1 + 1];
+            const int z0 = cell_start[cy * g.nc + x1 + 1];
+            const int run0 = on ? z0 - (s + 1) : 0, run1 = on && up > cy ? z1 - a1 : 0;
+            // both runs as one, four candidates in flight
+            for (int k0 = 0; k0 < run0 + run1; k0 += 4) {
+                float2 pj[4];
+                bool hit[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int k = k0 + q;
+                    pj[q] = psort[k < run0 ? s + 1 + k : k < run0 + run1 ? a1 + (k - run0) : 0];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float dx = p[u].x - pj[q].x, dy = p[u].y - pj[q].y;
+                    hit[q] = k0 + q < run0 + run1 && dx * dx + dy * dy < near2;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (hit[q]) pair(p[u], pj[q]);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kVerifyCpt; ++u) {
+        if (tid + u * kVerifyBlock >= n) continue;
+        const float2 q = p[u];
+        // (a non-finite coordinate fails the test)
+        if (R_tight == nullptr && q.x * q.x + q.y * q.y < lim2) continue;
+        const double xi = q.x, yi = q.y;
         const double rho = sqrt(xi * xi + yi * yi);
         rm = fmax(rm, rho + 1.0);
         const double d0 = (rho + 1.0) - Rb;
@@ -833,12 +896,21 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
         }
         if (!(isfinite(xi) && isfinite(yi))) sc = __builtin_nan("");
     }
-    const double Ep = block_sum<kVerifyBlock>(sp, sum_tmp);
-    const double Ec = block_sum<kVerifyBlock>(sc, sum_tmp);
-    const double Mp = block_max<kVerifyBlock>(mp, sum_tmp);
-    const double Mc = block_max<kVerifyBlock>(mc, sum_tmp);
-    const double Rm = R_tight ? block_max<kVerifyBlock>(rm, sum_tmp) : 0.0;
-    if (threadIdx.x == 0) {
+    const double v[5] = {wave_sum_dpp(sp), wave_sum_dpp(sc), wave_max_dpp(mp), wave_max_dpp(mc), wave_max_dpp(rm)};
+    if ((tid & (kWave - 1)) == 0)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) part[tid / kWave][q] = v[q];
+    __syncthreads();
+    if (tid == 0) {
+        double Ep = part[0][0], Ec = part[0][1], Mp = part[0][2], Mc = part[0][3], Rm = part[0][4];
+#pragma unroll
+        for (int w = 1; w < kVerifyBlock / kWave; ++w) {
+            Ep += part[w][0];
+            Ec += part[w][1];
+            Mp = fmax(Mp, part[w][2]);
+            Mc = fmax(Mc, part[w][3]);
+            Rm = fmax(Rm, part[w][4]);
+        }
         const double E = Ep + Ec;
         const bool bad = E != E;     // a non-finite coordinate
         if (energy64) energy64[b] = E;

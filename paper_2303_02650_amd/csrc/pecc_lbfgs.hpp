@@ -318,6 +318,19 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
+// Maximum of a non-negative double over the 64 lanes (NaN is passed over),
+// returned wave-uniform.
+__device__ __forceinline__ double wave_max_dpp(double v)
+{
+    v = fmax(v, dpp64<kDppXor1>(v));
+    v = fmax(v, dpp64<kDppXor2>(v));
+    v = fmax(v, dpp64<kDppHalfMirror>(v));
+    v = fmax(v, dpp64<kDppRowMirror>(v));
+    v = fmax(v, dpp64<kDppBcast15, 0xa>(v));
+    v = fmax(v, dpp64<kDppBcast31, 0xc>(v));
+    return lane_value64(v, 63);
+}
+
 // Slot held by lane L after wave_reduce_scatter: slot L.
 __device__ __forceinline__ int lane_slot(int L) { return L; }
 
