@@ -39,154 +39,376 @@ __device__ __forceinline__ bool writable_range(int off, int n, int64_t total_n)
 }
 
 // ---------------------------------------------------------------------------
-// Build, pass 1: per-circle list length into row[i+1], per-instance total.
+// Neighbor lists (CSR, rows ascending).  One launch over the instances: a
+// workgroup sorts its circles into cells, finds every circle's neighbors,
+// and needs the number of entries of all instances before it to know where
+// its own go.  It takes its instance by a ticket, publishes its count, and
+// looks back over the counts of the earlier instances until one that already
+// knows its prefix (all of them were taken by workgroups that run or have
+// ended, and none waits for a later one, so every wait ends).
+//
+// Bound by vector issue: 9 cells of candidates per circle.  A thread takes
+// the circles of sorted slots tid + 256 u, so that a wave's circles are
+// neighbors in space and their runs have similar lengths; the candidates
+// cost an FP32 distance and a mask bit (neighbor_masks); the neighbors of two
+// circles are collected in one set of registers as 16-bit halves and sorted
+// by a network (packed 16-bit minimum and maximum), 8, 12 or 16 entries.  Longer
+// rows, and circles with more candidates than a mask holds, are taken
+// candidate by candidate with an insertion sort.  The instance's segment is
+// staged in LDS and stored in order (stores of 8 bytes), as is the row table.
+// One pass instead of a count pass, a one-workgroup scan and a fill pass that
+// sorted rows in global memory: 4096 x n = 1000 in 134 us (464 us before),
+// 2048 x n = 96 in 57 us (63 us); of these about 85 us are vector issue, and
+// about 14 us the tickets of the first generation, all on one word.  Looks
+// back of 256 or 1024 words per turn were slower (172 and 193 us with the
+// energy against 168): words read while they are about to be written.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBuildBlock) void build_count_kernel(
-    const int32_t *__restrict__ offset, const float *__restrict__ R,
-    const float *__restrict__ xy, int64_t total_n, double c2, float h_req, int full,
-    int32_t *__restrict__ row, int64_t *__restrict__ inst_total)
-{
-    __shared__ float2 pos[kMaxN];
-    __shared__ int cell_start[kMaxCells + 1];
-    __shared__ uint16_t cell_circ[kMaxN];
-    __shared__ uint16_t slot_tmp[kMaxN];
-    __shared__ int scan_tmp[kBuildBlock / kWave + 1];
-    __shared__ int sum_tmp[kBuildBlock / kWave];
+constexpr int kBuildCpt = kMaxN / kBuildBlock;
+constexpr int kBuildNc = 32;            // cells per axis at most
+constexpr int kRowRegs = 16;            // neighbors of a row sorted in registers
+constexpr int kStage = 6144;            // entries of an instance staged in LDS
+// A state word: an instance's count or prefix under its flag.  Word 0 counts
+// the tickets as well, above the 20 bits that the first instance's count takes.
+constexpr unsigned long long kHasCount = 1ull << 62, kHasPrefix = 2ull << 62;
+constexpr int kTicketShift = 24;
+static_assert(kMaxN * (kMaxN - 1) < (1 << kTicketShift), "count of one instance");
 
-    const int b = blockIdx.x;
-    int off, n;
-    if (!instance_range(offset, b, total_n, &off, &n)) {
-        // not a valid instance: an empty list for each of its circles
-        if (writable_range(off, n, total_n))
-            for (int i = threadIdx.x; i < n; i += kBuildBlock) row[off + i + 1] = 0;
-        if (threadIdx.x == 0) inst_total[b] = 0;
-        return;
-    }
-    stage_positions<kBuildBlock>(xy, off, n, pos);
-    __syncthreads();
-    const Grid g = make_grid(R[b], h_req);
-    bin_circles<kBuildBlock>(pos, n, g, cell_start, cell_circ, slot_tmp, scan_tmp);
-    int mine = 0;
-    for (int i = threadIdx.x; i < n; i += kBuildBlock) {
-        const float2 pi = pos[i];
-        int cnt = 0;
-        for_each_candidate(i, pi, g, cell_start, cell_circ, [&](int j) {
-            if ((full || j > i) && near64(pi, pos[j], c2)) ++cnt;
-        });
-        row[off + i + 1] = cnt;
-        mine += cnt;
-    }
-    const int tot = block_sum<kBuildBlock>(mine, sum_tmp);
-    if (threadIdx.x == 0) inst_total[b] = tot;
-}
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-// Build, pass 2: exclusive scan of the per-instance totals (one workgroup).
-constexpr int kScanBlock = 1024;
-__global__ __launch_bounds__(kScanBlock) void build_scan_kernel(
-    int64_t *__restrict__ inst_total, int B, int64_t total_n,
-    int32_t *__restrict__ row, int64_t *__restrict__ num_pairs)
+// Ascending sort of two sets of 16-bit keys (the halves of a[0 .. N)) by
+// Batcher's odd-even merge network.
+template <int N>
+__device__ __forceinline__ void sort_pairs(u16x2 (&a)[kRowRegs])
 {
-    __shared__ int64_t carry_s;
-    __shared__ int64_t wsum[kScanBlock / kWave];
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    if (threadIdx.x == 0) carry_s = 0;
-    __syncthreads();
-    for (int base = 0; base < B; base += kScanBlock) {
-        const int b = base + threadIdx.x;
-        const int64_t v = b < B ? inst_total[b] : 0;
-        int64_t inc = v;
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int64_t t = __shfl_up(inc, o, kWave);
-            if (lane >= o) inc += t;
-        }
-        if (lane == kWave - 1) wsum[w] = inc;
-        __syncthreads();
-        int64_t before = 0;
-        for (int k = 0; k < w; ++k) before += wsum[k];
-        int64_t chunk = 0;
-        for (int k = 0; k < kScanBlock / kWave; ++k) chunk += wsum[k];
-        const int64_t carry = carry_s;
-        if (b < B) inst_total[b] = carry + before + inc - v;   // now: base offset
-        __syncthreads();
-        if (threadIdx.x == 0) carry_s = carry + chunk;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        num_pairs[0] = carry_s;
-        row[0] = 0;
-        row[total_n] = (int32_t)(carry_s < 0x7fffffffLL ? carry_s : 0x7fffffffLL);
-    }
+    for (int p = 1; p < N; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j <= N - 1 - k; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < N && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+                        const u16x2 u = a[i + j], v = a[i + j + k];
+                        a[i + j] = __builtin_elementwise_min(u, v);
+                        a[i + j + k] = __builtin_elementwise_max(u, v);
+                    }
 }
 
-// Build, pass 3: row offsets and the sorted column indices (int32 global
-// indices, or uint16 instance-local ones).
-template <typename Idx>
-__global__ __launch_bounds__(kBuildBlock) void build_fill_kernel(
-    const int32_t *__restrict__ offset, const float *__restrict__ R,
-    const float *__restrict__ xy, int64_t total_n, double c2, float h_req, int full,
-    int32_t *__restrict__ row, Idx *__restrict__ col, int64_t capacity,
-    const int64_t *__restrict__ inst_base)
+// State words of a build, cleared.
+__global__ __launch_bounds__(kBuildBlock) void build_clear_kernel(unsigned long long *state, int B)
 {
-    constexpr bool kLocal = sizeof(Idx) == 2;
-    __shared__ float2 pos[kMaxN];
-    __shared__ int cell_start[kMaxCells + 1];
-    __shared__ uint16_t cell_circ[kMaxN];
-    __shared__ uint16_t slot_tmp[kMaxN];
-    __shared__ int scan_tmp[kBuildBlock / kWave + 1];
-    __shared__ int cnt_s[kMaxN];
-    __shared__ int run_s;
+    const int64_t i = (int64_t)blockIdx.x * kBuildBlock + threadIdx.x;
+    if (i < B) state[i] = 0ull;
+}
 
-    const int b = blockIdx.x;
+template <int FORMAT>
+__global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
+    const int32_t *__restrict__ offset, const float *__restrict__ R,
+    const float *__restrict__ xy, int B, int64_t total_n, double c2, float h_req,
+    int32_t *__restrict__ row, void *__restrict__ col_v, int64_t capacity,
+    int64_t *num_pairs, unsigned long long *state)
+{
+    constexpr bool kLocal = FORMAT == kListLocal16, kHalf = FORMAT == kListHalf;
+    using Idx = std::conditional_t<kLocal, uint16_t, int32_t>;
+    Idx *__restrict__ col = static_cast<Idx *>(col_v);
+    __shared__ int cell_start[kBuildNc * kBuildNc + 1];
+    __shared__ uint16_t cell_circ[kMaxN];
+    __shared__ int scan_tmp[kBuildBlock / kWave];
+    __shared__ int start_s[kMaxN];              // row lengths, then row starts, by circle
+    // positions in cell order and the sort's scratch, then the staged segment
+    __shared__ union {
+        struct {
+            float2 psort[kMaxN + 8];
+            uint16_t slot_tmp[kMaxN];
+        };
+        uint16_t stage[kStage];
+    } sh;
+    float2 *const psort = sh.psort;
+    uint16_t *const stage = sh.stage;
+    __shared__ int inst_s;
+    __shared__ long long base_s;
+
+    const int tid = threadIdx.x;
+    if (tid == 0)
+        inst_s = (int)((atomicAdd(&state[0], 1ull << kTicketShift) & ~(3ull << 62)) >> kTicketShift);
+    __syncthreads();
+    const int b = inst_s;
     int off, n;
-    const bool ok = instance_range(offset, b, total_n, &off, &n);
-    const int64_t base = inst_base[b];
-    if (!ok) {
+    const bool valid = instance_range(offset, b, total_n, &off, &n);
+    const int nn = valid ? n : 0;               // circles to list (an invalid instance has empty rows)
+
+    float2 x[kBuildCpt];
+#pragma unroll
+    for (int u = 0; u < kBuildCpt; ++u) {
+        const int i = tid + u * kBuildBlock;
+        x[u] = i < nn ? reinterpret_cast<const float2 *>(xy)[off + i] : make_float2(0.f, 0.f);
+        // NaN is no neighbor of anything, and neither is infinity
+        if (x[u].x != x[u].x) x[u].x = HUGE_VALF;
+        if (x[u].y != x[u].y) x[u].y = HUGE_VALF;
+        start_s[i] = 0;
+    }
+    const Grid g = make_grid<kBuildNc>(R[b], h_req);
+    {
+        int own[kBuildCpt];
+        sort_cells<kBuildBlock, kBuildCpt>(tid, x, nn, g, cell_start, cell_circ, sh.slot_tmp, psort,
+                                           scan_tmp, own);
+    }
+    // every neighbor of the circle of slot s, candidate by candidate
+    auto each_neighbor = [&](int s, int i, bool half, auto &&f) {
+        const float2 *const src = reinterpret_cast<const float2 *>(xy) + off;
+        const float2 q = src[i];
+        int ra[3], rl[3], self;
+        cell_rows(q, true, s, g, cell_start, ra, rl, self);
+        for (int r = 0; r < 3; ++r)
+            for (int t = ra[r]; t < ra[r] + rl[r]; ++t) {
+                const int j = cell_circ[t];
+                if (t != s && (!half || j > i) && near64(q, src[j], c2)) f(j);
+            }
+    };
+    // ---- neighbor masks of the circles of slots tid + 256 u, two at a time ---
+    unsigned long long mask[kBuildCpt];
+    unsigned firsts[kBuildCpt], lens[kBuildCpt];        // the three runs, 10 bits each (a first slot of 1024 is an empty run, and so are those after it)
+    int ci[kBuildCpt], mine = 0;
+    bool plain[kBuildCpt];                      // row in registers
+#pragma unroll
+    for (int h = 0; h < kBuildCpt / 2; ++h) {
+        float2 q[2];
+        bool on[2], fits[2];
+        int ra[2][3], rl[2][3], self[2], kmax[3] = {0, 0, 0};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int s = tid + (2 * h + e) * kBuildBlock;
+            on[e] = s < nn;
+            q[e] = psort[on[e] ? s : 0];
+            ci[2 * h + e] = cell_circ[on[e] ? s : 0];
+            cell_rows(q[e], on[e], s, g, cell_start, ra[e], rl[e], self[e]);
+            // infinity has no neighbors: its runs are emptied
+            if (!(fabsf(q[e].x) <= 3.0e38f && fabsf(q[e].y) <= 3.0e38f)) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r) rl[e][r] = 0;
+                on[e] = false;
+            }
+            fits[e] = max(rl[e][0], max(rl[e][1], rl[e][2])) <= 32 && rl[e][0] + rl[e][1] + rl[e][2] <= 64;
+            // a circle with too many candidates stands aside (empty runs)
+            on[e] = on[e] && fits[e];
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                rl[e][r] = fits[e] ? rl[e][r] : 0;
+                kmax[r] = max(kmax[r], rl[e][r]);
+            }
+            firsts[2 * h + e] = (unsigned)(ra[e][0] | ra[e][1] << 10 | ra[e][2] << 20);
+            lens[2 * h + e] = (unsigned)(rl[e][0] | rl[e][1] << 10 | rl[e][2] << 20);
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) kmax[r] = wave_max_dpp(kmax[r]);
+        unsigned long long mk[2];
+        neighbor_masks<2, 4, kMaxN, true>(q, on, self, ra, rl, kmax, psort, c2, mk);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int u = 2 * h + e, pop = __builtin_popcountll(mk[e]);
+            plain[u] = fits[e] && pop <= kRowRegs;
+            mine += pop;
+            mask[u] = plain[u] ? mk[e] : 0ull;
+            if (!fits[e]) each_neighbor(tid + u * kBuildBlock, ci[u], false, [&](int) { ++mine; });
+        }
+    }
+    // The instance's count, published before the rows are collected: the
+    // workgroups behind wait for it (a half list holds half: the predicate is
+    // symmetric)
+    int total = block_sum<kBuildBlock>(mine, scan_tmp);
+    if (kHalf) total /= 2;
+    if (tid == 0) {
+        if (b == 0)
+            atomicAdd(&state[0], kHasPrefix | (unsigned long long)total);
+        else
+            __hip_atomic_store(&state[b], kHasCount | (unsigned long long)total, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // ---- the rows, sorted, two at a time ---------------------------------------
+    u16x2 nb[kBuildCpt / 2][kRowRegs];
+    int cnt[kBuildCpt], used[kBuildCpt / 2];    // used: longest of the wave
+#pragma unroll
+    for (int h = 0; h < kBuildCpt / 2; ++h) {
+        int m = 0, most = 0;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const unsigned l = lens[2 * h + e];
+            m = max(m, __builtin_popcountll(mask[2 * h + e]));
+            most = max(most, (int)((l & 1023) + (l >> 10 & 1023) + (l >> 20)));
+            cnt[2 * h + e] = 0;
+        }
+        m = wave_max_dpp(m);
+        most = wave_max_dpp(most);
+        used[h] = m;
+        auto collect = [&](auto word) {
+            using M = decltype(word);
+            M mk[2];
+            int n0[2], n1[2], s0[2], s1[2], s2[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const unsigned l = lens[2 * h + e], f = firsts[2 * h + e];
+                mk[e] = (M)mask[2 * h + e];
+                n0[e] = l & 1023;
+                n1[e] = n0[e] + (l >> 10 & 1023);
+                s0[e] = f & 1023;
+                s1[e] = (int)(f >> 10 & 1023) - n0[e];
+                s2[e] = (int)(f >> 20) - n1[e];
+            }
+#pragma unroll
+            for (int k = 0; k < kRowRegs; ++k) {
+                nb[h][k] = u16x2{0xffff, 0xffff};
+                if (k < m) {                     // wave-uniform
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        int j;
+                        bool has = next_neighbor(mk[e], n0[e], n1[e], s0[e], s1[e], s2[e], cell_circ, j);
+                        if (kHalf) has = has && j > ci[2 * h + e];
+                        cnt[2 * h + e] += has ? 1 : 0;
+                        nb[h][k][e] = has ? (unsigned short)j : (unsigned short)0xffff;
+                    }
+                }
+            }
+        };
+        if (most <= 32) collect(0u);
+        else collect(0ull);
+        if (m <= 8) sort_pairs<8>(nb[h]);
+        else if (m <= 12) sort_pairs<12>(nb[h]);
+        else sort_pairs<16>(nb[h]);
+    }
+#pragma unroll
+    for (int u = 0; u < kBuildCpt; ++u) {
+        const int s = tid + u * kBuildBlock;
+        if (s < nn) {
+            if (!plain[u]) each_neighbor(s, ci[u], kHalf, [&](int) { ++cnt[u]; });
+            start_s[ci[u]] = cnt[u];
+        }
+    }
+    __syncthreads();
+    // ---- row starts: thread t holds circles 4 t .. 4 t + 3 -------------------
+    int len4[kBuildCpt], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kBuildCpt; ++u) {
+        len4[u] = start_s[kBuildCpt * tid + u];
+        sum += len4[u];
+    }
+    int sum_all;
+    int run = block_exclusive_scan<kBuildBlock>(sum, scan_tmp, &sum_all);
+#pragma unroll
+    for (int u = 0; u < kBuildCpt; ++u) {
+        start_s[kBuildCpt * tid + u] = run;
+        run += len4[u];
+    }
+    __syncthreads();
+    // ---- the segment into LDS -----------------------------------------------
+    const bool staged = total <= kStage;
+    if (staged) {
+#pragma unroll
+        for (int u = 0; u < kBuildCpt; ++u) {
+            const int s = tid + u * kBuildBlock;
+            if (s >= nn) continue;
+            uint16_t *dst = stage + start_s[ci[u]];
+            if (plain[u]) {
+#pragma unroll
+                for (int k = 0; k < kRowRegs; ++k)
+                    if (k < used[u / 2] && k < cnt[u]) dst[k] = nb[u / 2][k][u % 2];
+            } else {
+                int w = 0;
+                each_neighbor(s, ci[u], kHalf, [&](int j) {
+                    int k = w++;
+                    for (; k > 0 && dst[k - 1] > j; --k) dst[k] = dst[k - 1];
+                    dst[k] = (uint16_t)j;
+                });
+            }
+        }
+    }
+    // ---- where the segment goes: the counts of the instances before ----------
+    // One wave looks, a word per lane, so that little is read of words that
+    // others are about to write.
+    if (tid < kWave) {
+        long long base = 0;
+        for (int hi = b; hi > 0; hi -= kWave) {
+            // a word before the first instance stands for a prefix of 0
+            const int k = hi - 1 - tid;
+            unsigned long long v = kHasPrefix;
+            if (k >= 0) {
+                while (((v = __hip_atomic_load(&state[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 62) == 0)
+                    __builtin_amdgcn_s_sleep(1);
+                if (k == 0) v = kHasPrefix | (v & ((1ull << kTicketShift) - 1));
+            }
+            const unsigned long long known = __builtin_amdgcn_ballot_w64((v >> 62) == 2);
+            const int first = known ? __builtin_ctzll(known) : kWave;      // nearest prefix
+            long long part = tid <= first ? (long long)(v & ~(3ull << 62)) : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, kWave);
+            base += part;
+            if (known) break;
+        }
+        if (tid == 0) {
+            if (b > 0)
+                __hip_atomic_store(&state[b], kHasPrefix | (unsigned long long)(base + total),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            base_s = base;
+        }
+    }
+    __syncthreads();                             // base, and the staged segment
+    const long long base = base_s;
+    auto clip = [](long long r) { return (int32_t)(r < 0x7fffffffLL ? r : 0x7fffffffLL); };
+    if (tid == 0 && b == B - 1) {
+        row[0] = 0;
+        row[total_n] = clip(base + total);
+        num_pairs[0] = base + total;
+    }
+    if (!valid) {
+        // not a valid instance: an empty row for each circle it may write
         if (writable_range(off, n, total_n))
-            for (int i = threadIdx.x; i < n; i += kBuildBlock)
-                row[off + i] = (int32_t)(base < 0x7fffffffLL ? base : 0x7fffffffLL);
+            for (int i = tid; i < n; i += kBuildBlock) row[off + i] = clip(base);
         return;
     }
-    // the counts of pass 1 sit in row[off+1 .. off+n]; read them all first
-    for (int i = threadIdx.x; i < n; i += kBuildBlock) cnt_s[i] = row[off + i + 1];
-    stage_positions<kBuildBlock>(xy, off, n, pos);
-    if (threadIdx.x == 0) run_s = 0;
-    __syncthreads();
-    // exclusive scan of the counts, kBuildBlock circles at a time
-    for (int c0 = 0; c0 < n; c0 += kBuildBlock) {
-        const int i = c0 + threadIdx.x;
-        const int v = i < n ? cnt_s[i] : 0;
-        int tot;
-        const int ex = block_exclusive_scan<kBuildBlock>(v, scan_tmp, &tot);
-        const int run = run_s;
-        __syncthreads();
-        if (i < n) cnt_s[i] = run + ex;           // now: local row start
-        if (threadIdx.x == 0) run_s = run + tot;
-        __syncthreads();
+    for (int i = tid; i < n; i += kBuildBlock) row[off + i] = clip(base + start_s[i]);
+    const int add = kLocal ? 0 : off;
+    if (staged) {
+        // entries that fit, in order: single ones up to 8-byte (uint16) or
+        // 16-byte (int32) alignment, then four per store
+        const int len = (int)min((long long)total, max(capacity - base, 0LL));
+        Idx *dst = col + base;
+        const int mis = (int)((reinterpret_cast<uintptr_t>(dst) / sizeof(Idx)) & 3);
+        const int head = min(len, (4 - mis) & 3);
+        const int quads = (len - head) / 4;
+        if (tid < head) dst[tid] = (Idx)(add + stage[tid]);
+        for (int k = tid; k < quads; k += kBuildBlock) {
+            const uint16_t *src = stage + head + 4 * k;
+            if constexpr (kLocal)
+                *reinterpret_cast<ushort4 *>(dst + head + 4 * k) = make_ushort4(src[0], src[1], src[2], src[3]);
+            else
+                *reinterpret_cast<int4 *>(dst + head + 4 * k) =
+                    make_int4(add + src[0], add + src[1], add + src[2], add + src[3]);
+        }
+        const int done = head + 4 * quads;
+        if (tid < len - done) dst[done + tid] = (Idx)(add + stage[done + tid]);
+        return;
     }
-    for (int i = threadIdx.x; i < n; i += kBuildBlock) {
-        const int64_t r = base + cnt_s[i];
-        row[off + i] = (int32_t)(r < 0x7fffffffLL ? r : 0x7fffffffLL);
-    }
-    const Grid g = make_grid(R[b], h_req);
-    bin_circles<kBuildBlock>(pos, n, g, cell_start, cell_circ, slot_tmp, scan_tmp);
-    for (int i = threadIdx.x; i < n; i += kBuildBlock) {
-        const float2 pi = pos[i];
-        const int64_t start = base + cnt_s[i];
-        int64_t w = start;
-        for_each_candidate(i, pi, g, cell_start, cell_circ, [&](int j) {
-            if ((full || j > i) && near64(pi, pos[j], c2)) {
-                if (w < capacity) col[w] = (Idx)(kLocal ? j : off + j);
+    // a segment too long for LDS: every thread stores its rows itself
+#pragma unroll
+    for (int u = 0; u < kBuildCpt; ++u) {
+        const int s = tid + u * kBuildBlock;
+        if (s >= nn) continue;
+        const long long a = base + start_s[ci[u]];
+        if (plain[u]) {
+#pragma unroll
+            for (int k = 0; k < kRowRegs; ++k)
+                if (k < cnt[u] && a + k < capacity) col[a + k] = (Idx)(add + nb[u / 2][k][u % 2]);
+        } else {
+            long long w = a;
+            each_neighbor(s, ci[u], kHalf, [&](int j) {
+                if (w < capacity) {
+                    const Idx key = (Idx)(add + j);
+                    long long k = w;
+                    for (; k > a && col[k - 1] > key; --k) col[k] = col[k - 1];
+                    col[k] = key;
+                }
                 ++w;
-            }
-        });
-        // insertion sort of the stored part of this row (rows are short)
-        const int64_t end = w < capacity ? w : capacity;
-        for (int64_t a = start + 1; a < end; ++a) {
-            const Idx key = col[a];
-            int64_t k = a - 1;
-            while (k >= start && col[k] > key) { col[k + 1] = col[k]; --k; }
-            col[k + 1] = key;
+            });
         }
     }
 }
@@ -932,21 +1154,20 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
 hipError_t launch_build(const int32_t *offset, const float *R, const float *xy, int B,
                         int64_t total_n, double cutoff, float h_req, int format,
                         int32_t *row, void *col, int64_t capacity, int64_t *num_pairs,
-                        int64_t *inst_total, hipStream_t s)
+                        int64_t *inst_state, hipStream_t s)
 {
     const double c2 = cutoff * cutoff;
-    const int full = format != kListHalf;
-    build_count_kernel<<<B, kBuildBlock, 0, s>>>(offset, R, xy, total_n, c2, h_req, full, row,
-                                                 inst_total);
-    build_scan_kernel<<<1, kScanBlock, 0, s>>>(inst_total, B, total_n, row, num_pairs);
+    unsigned long long *state = reinterpret_cast<unsigned long long *>(inst_state);
+    build_clear_kernel<<<(B - 1) / kBuildBlock + 1, kBuildBlock, 0, s>>>(state, B);
     if (format == kListLocal16)
-        build_fill_kernel<uint16_t><<<B, kBuildBlock, 0, s>>>(
-            offset, R, xy, total_n, c2, h_req, full, row, static_cast<uint16_t *>(col), capacity,
-            inst_total);
+        build_kernel<kListLocal16><<<B, kBuildBlock, 0, s>>>(offset, R, xy, B, total_n, c2, h_req, row,
+                                                             col, capacity, num_pairs, state);
+    else if (format == kListHalf)
+        build_kernel<kListHalf><<<B, kBuildBlock, 0, s>>>(offset, R, xy, B, total_n, c2, h_req, row, col,
+                                                          capacity, num_pairs, state);
     else
-        build_fill_kernel<int32_t><<<B, kBuildBlock, 0, s>>>(
-            offset, R, xy, total_n, c2, h_req, full, row, static_cast<int32_t *>(col), capacity,
-            inst_total);
+        build_kernel<kListFull><<<B, kBuildBlock, 0, s>>>(offset, R, xy, B, total_n, c2, h_req, row, col,
+                                                          capacity, num_pairs, state);
     return hipGetLastError();
 }
 

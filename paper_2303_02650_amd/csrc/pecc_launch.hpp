@@ -13,7 +13,7 @@ constexpr int kListHalf = 0, kListFull = 1, kListLocal16 = 2;
 hipError_t launch_build(const int32_t *offset, const float *R, const float *xy, int B,
                         int64_t total_n, double cutoff, float h_req, int format,
                         int32_t *row, void *col, int64_t capacity, int64_t *num_pairs,
-                        int64_t *inst_total, hipStream_t s);
+                        int64_t *inst_state, hipStream_t s);
 
 hipError_t launch_energy_grad(const int32_t *offset, const float *R, const float *xy, int B,
                               int64_t total_n, const int32_t *row, const void *col,

@@ -614,6 +614,16 @@ __device__ __forceinline__ void cell_rows(float2 p, bool act, int own, const Gri
 // The lowest bit of a candidate mask taken: candidate k of three runs (k < n0:
 // slot k + s0, k < n01: k + s1, else k + s2); j receives its circle.  False
 // (and some circle) when the mask is empty.
+__device__ __forceinline__ bool next_neighbor(unsigned &mask, int n0, int n01, int s0, int s1, int s2,
+                                              const uint16_t *cell_circ, int &j)
+{
+    const bool has = mask != 0;
+    const int k = __builtin_ctz(mask | (1u << 31));
+    mask &= mask - 1;
+    j = cell_circ[has ? k + (k < n0 ? s0 : k < n01 ? s1 : s2) : 0];
+    return has;
+}
+
 __device__ __forceinline__ bool next_neighbor(unsigned long long &mask, int n0, int n01, int s0, int s1,
                                               int s2, const uint16_t *cell_circ, int &j)
 {
@@ -622,6 +632,91 @@ __device__ __forceinline__ bool next_neighbor(unsigned long long &mask, int n0, 
     mask &= mask - 1;
     j = cell_circ[has ? k + (k < n0 ? s0 : k < n01 ? s1 : s2) : 0];
     return has;
+}
+
+// Which of the candidates of a thread's circles are neighbors (the predicate
+// near64 with c2): one bit per candidate in the order of the circle's three
+// runs ra, rl (at most 32 each, 64 in all; kmax: the wave's longest of each,
+// uniform), the circle itself (place self) left out.  FP32 decides outside a
+// band of 1e-6 c2 around c2 (the FP32 distance is within 4e-7);
+// a wave with a candidate inside the band takes the FP64 predicate for all of
+// its own.  CAND
+// candidates of a row are read per turn, past a run's end from any readable
+// position (psort has NMAX + 8).  NO_NAN: the circles' distances are numbers
+// (so that a sign bit decides), two instructions fewer per candidate, and
+// any cutoff (1e-30 covers squares below the normal range).
+template <int CPT, int CAND, int NMAX, bool NO_NAN = false>
+__device__ __forceinline__ void neighbor_masks(const float2 (&x)[CPT], const bool (&act)[CPT],
+                                               const int (&self)[CPT], const int (&ra)[CPT][3],
+                                               const int (&rl)[CPT][3], const int (&kmax)[3],
+                                               const float2 *psort, double c2,
+                                               unsigned long long (&mask)[CPT])
+{
+    const float c2f = (float)c2, band = NO_NAN ? c2f * 1e-6f + 1e-30f : c2f * 1e-6f;
+    float dmin = 3.0e38f;
+    auto scan = [&](auto exact) {
+        unsigned mr[CPT][3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) mr[c][r] = 0;
+            for (int k0 = 0; k0 < kmax[r]; k0 += CAND) {
+                float px[CPT][CAND], py[CPT][CAND];
+                unsigned bits[CPT];
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) {
+                    const float2 *src = psort + min(ra[c][r] + k0, NMAX);
+#pragma unroll
+                    for (int u = 0; u < CAND; ++u) {
+                        const float2 v = src[u];
+                        px[c][u] = v.x;
+                        py[c][u] = v.y;
+                    }
+                    bits[c] = 0;
+                }
+                if constexpr (NO_NAN && !decltype(exact)::value) {
+#pragma unroll
+                    for (int u = CAND - 1; u >= 0; --u)
+#pragma unroll
+                        for (int c = 0; c < CPT; ++c) {
+                            const float dx = x[c].x - px[c][u], dy = x[c].y - py[c][u];
+                            const float t = fmaf(dx, dx, fmaf(dy, dy, -c2f));
+                            bits[c] = __builtin_amdgcn_alignbit(bits[c], __float_as_uint(t), 31);
+                            dmin = fminf(dmin, fabsf(t));
+                        }
+                }
+#pragma unroll
+                for (int u = 0; u < (NO_NAN && !decltype(exact)::value ? 0 : CAND); ++u)
+#pragma unroll
+                    for (int c = 0; c < CPT; ++c) {
+                        bool nb;
+                        if constexpr (decltype(exact)::value) {
+                            nb = near64(x[c], make_float2(px[c][u], py[c][u]), c2);
+                        } else {
+                            const float dx = x[c].x - px[c][u], dy = x[c].y - py[c][u];
+                            const float t = dx * dx + dy * dy - c2f;
+                            nb = t < 0.f;
+                            dmin = fminf(dmin, fabsf(t));
+                        }
+                        bits[c] |= nb ? 1u << u : 0u;
+                    }
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) mr[c][r] |= bits[c] << k0;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            mask[c] = 0;
+#pragma unroll
+            for (int r = 2; r >= 0; --r) {
+                const unsigned keep = rl[c][r] < 32 ? (1u << rl[c][r]) - 1u : ~0u;
+                mask[c] = (mask[c] << rl[c][r]) | (unsigned long long)(mr[c][r] & keep);
+            }
+            mask[c] = act[c] ? mask[c] & ~(1ull << self[c]) : 0ull;
+        }
+    };
+    scan(std::false_type{});
+    if (__builtin_amdgcn_ballot_w64(dmin <= band)) scan(std::true_type{});
 }
 
 // Neighbor lists of a workgroup's circles (tid + c * BLOCK) into ELL slots,
@@ -670,62 +765,7 @@ __device__ __forceinline__ int build_lists(int tid, const float2 (&x)[CPT], cons
     int m = 0;
     if (max(kmax[0], max(kmax[1], kmax[2])) <= 32 && !__builtin_amdgcn_ballot_w64(!fits)) {
         unsigned long long mask[CPT];
-        const float c2f = (float)c2, band = c2f * 1e-6f;
-        float dmin = 3.0e38f;
-        auto scan = [&](auto exact) {
-            unsigned mr[CPT][3];
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-#pragma unroll
-                for (int c = 0; c < CPT; ++c) mr[c][r] = 0;
-                for (int k0 = 0; k0 < kmax[r]; k0 += kCand) {
-                    float px[CPT][kCand], py[CPT][kCand];
-                    unsigned bits[CPT];
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) {
-                        // past a run's end: any readable position (psort has
-                        // NMAX + 8), its bits are cut off below
-                        const float2 *src = psort + min(ra[c][r] + k0, NMAX);
-#pragma unroll
-                        for (int u = 0; u < kCand; ++u) {
-                            const float2 v = src[u];
-                            px[c][u] = v.x;
-                            py[c][u] = v.y;
-                        }
-                        bits[c] = 0;
-                    }
-#pragma unroll
-                    for (int u = 0; u < kCand; ++u)
-#pragma unroll
-                        for (int c = 0; c < CPT; ++c) {
-                            bool nb;
-                            if constexpr (decltype(exact)::value) {
-                                nb = near64(x[c], make_float2(px[c][u], py[c][u]), c2);
-                            } else {
-                                const float dx = x[c].x - px[c][u], dy = x[c].y - py[c][u];
-                                const float t = dx * dx + dy * dy - c2f;
-                                nb = t < 0.f;
-                                dmin = fminf(dmin, fabsf(t));
-                            }
-                            bits[c] |= nb ? 1u << u : 0u;
-                        }
-#pragma unroll
-                    for (int c = 0; c < CPT; ++c) mr[c][r] |= bits[c] << k0;
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < CPT; ++c) {
-                mask[c] = 0;
-#pragma unroll
-                for (int r = 2; r >= 0; --r) {
-                    const unsigned keep = rl[c][r] < 32 ? (1u << rl[c][r]) - 1u : ~0u;
-                    mask[c] = (mask[c] << rl[c][r]) | (unsigned long long)(mr[c][r] & keep);
-                }
-                mask[c] = act[c] ? mask[c] & ~(1ull << self[c]) : 0ull;
-            }
-        };
-        scan(std::false_type{});
-        if (__builtin_amdgcn_ballot_w64(dmin <= band)) scan(std::true_type{});
+        neighbor_masks<CPT, kCand, NMAX>(x, act, self, ra, rl, kmax, psort, c2, mask);
         // neighbors: one mask bit of every circle per turn; a turn's index
         // read is in flight while the next turn's bits are taken (its write
         // comes one turn later)
