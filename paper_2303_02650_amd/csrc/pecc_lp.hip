@@ -5,7 +5,8 @@
 //
 // Kernels
 //   features_kernel   8 features per candidate, cell grid of side >= 4 in LDS,
-//                     FP64 distances on the FP32 coordinates
+//                     FP32 distances, FP64 where they cannot decide and
+//                     for the overlaps
 //   mlp_forward_kernel    8 -> 64 -> 64 -> 1 erf-GELU network on BF16 MFMA
 //   mlp_grad_kernel       forward + backward of the mean BCE-with-logits loss,
 //                         per-workgroup partial gradients (MFMA for every
@@ -37,6 +38,7 @@
 
 #include "pecc_device.hpp"
 #include "pecc_launch.hpp"
+#include "pecc_lbfgs.hpp"
 
 namespace pecc {
 namespace {
@@ -51,46 +53,147 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // ---------------------------------------------------------------------------
 // Features
 // ---------------------------------------------------------------------------
-constexpr int kFeatBlock = 256;
+// Bound by vector issue: two points per candidate (the circle and its
+// destination), each against the 3 x 3 cells of side 4 around it, 38 circles
+// at packing density.  Those cost an FP32 distance and a sign bit per
+// threshold, the bits collected per cell row and counted at the end; a circle
+// that may overlap, or lies within a band of a threshold that the FP32
+// distance cannot decide (distances of 2 and 4 are common in packings), is
+// taken in FP64, the overlaps in the order of the cells.  512 threads share
+// one sort of the circles; both points of a candidate run side by side.
+// 128 x 4096 candidates at n = 1000: 48 us (127 us with every distance in
+// FP64, a square root evaluated by the whole wave at nearly every circle).
+constexpr int kFeatBlock = 512;
+constexpr int kFeatCpt = kMaxN / kFeatBlock;
 constexpr int kFeatChunk = 1024;     // candidates per workgroup
 constexpr float kDensRadius = 4.0f;  // widest radius a feature looks at
 
 struct FeatShared {
-    float2 pos[kMaxN];
+    float2 psort[kMaxN + 8];         // positions in cell order
     int cell_start[kMaxCells + 1];
     uint16_t cell_circ[kMaxN];
     uint16_t slot_tmp[kMaxN];
-    int scan_tmp[kFeatBlock / 64 + 1];
+    uint16_t slot_of[kMaxN];         // place of a circle in the cell order
+    int scan_tmp[kFeatBlock / 64];
 };
 
-// Overlap energy, neighbor count, boundary gap and density around point p
-// over the circles j != skip (the circle that would move is lifted out).
-__device__ void feature_quad(const FeatShared &S, const Grid &g, double R, int skip, float2 p,
-                             float *f)
+// Overlap energy, neighbor count, boundary gap and density around the points
+// p[0], p[1] over the circles except the one at place `own` (the circle that
+// would move is lifted out).
+__device__ __forceinline__ void feature_quads(const FeatShared &S, const Grid &g, double R, bool act,
+                                              int own, const float2 (&p)[2], float *f)
 {
 #pragma clang fp contract(off)   // distances rounded operation by operation, like the oracle
-    const double px = (double)p.x, py = (double)p.y;
-    double e = 0.0;
-    int near = 0, dens = 0;
-    for_each_candidate(skip, p, g, S.cell_start, S.cell_circ, [&](int j) {
+    // thresholds on the squared distance; lo/hi: outside the FP32 distance's
+    // error (4e-7 of it) on either side
+    constexpr float kBand = 1e-6f;
+    constexpr float kOver = 4.0f * (1.0f + kBand);
+    constexpr float kNearLo = 5.29f * (1.0f - kBand), kNearHi = 5.29f * (1.0f + kBand);
+    constexpr float kDensLo = 16.0f * (1.0f - kBand), kDensHi = 16.0f * (1.0f + kBand);
+    int ra[2][3], rl[2][3];
+    bool plain[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        int place;
+        // a point that is not finite is near nothing
+        const bool on = act && fabsf(p[q].x) <= 3.0e38f && fabsf(p[q].y) <= 3.0e38f;
+        cell_rows(p[q], on, 0, g, S.cell_start, ra[q], rl[q], place);
+        plain[q] = max(rl[q][0], max(rl[q][1], rl[q][2])) <= 32 && rl[q][0] + rl[q][1] + rl[q][2] <= 64;
+    }
+    int near[2] = {0, 0}, dens[2] = {0, 0};
+    double e[2] = {0.0, 0.0};
+    unsigned exact[2][3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int longest = wave_max_dpp(max(plain[0] ? rl[0][r] : 0, plain[1] ? rl[1][r] : 0));
+        unsigned over[2] = {0, 0}, nlo[2] = {0, 0}, nhi[2] = {0, 0}, dlo[2] = {0, 0}, dhi[2] = {0, 0};
+        // downwards, so that the bit shifted in last is the first candidate
+        for (int k0 = (longest + 3) / 4 * 4 - 4; k0 >= 0; k0 -= 4) {
+            float2 c[2][4];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const float2 *src = S.psort + min(ra[q][r] + k0, kMaxN);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) c[q][u] = src[u];
+            }
+#pragma unroll
+            for (int u = 3; u >= 0; --u)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float dx = p[q].x - c[q][u].x, dy = p[q].y - c[q][u].y;
+                    const float l2 = fmaf(dx, dx, dy * dy);
+                    auto push = [&](unsigned &w, float limit) {
+                        w = __builtin_amdgcn_alignbit(w, __float_as_uint(l2 - limit), 31);
+                    };
+                    push(over[q], kOver);
+                    push(nlo[q], kNearLo);
+                    push(nhi[q], kNearHi);
+                    push(dlo[q], kDensLo);
+                    push(dhi[q], kDensHi);
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            unsigned keep = rl[q][r] < 32 ? (1u << rl[q][r]) - 1u : ~0u;
+            const unsigned place = (unsigned)(own - ra[q][r]);
+            if (place < 32u) keep &= ~(1u << place);
+            if (!plain[q]) keep = 0;
+            const unsigned ex = (over[q] | (nhi[q] & ~nlo[q]) | (dhi[q] & ~dlo[q])) & keep;
+            exact[q][r] = ex;
+            near[q] += __builtin_popcount(nlo[q] & keep & ~ex);
+            dens[q] += __builtin_popcount(dlo[q] & keep & ~ex);
+        }
+    }
+    auto visit = [&](int q, float2 c) {
 #pragma clang fp contract(off)
-        const double dx = px - (double)S.pos[j].x;
-        const double dy = py - (double)S.pos[j].y;
+        const double dx = (double)p[q].x - (double)c.x;
+        const double dy = (double)p[q].y - (double)c.y;
         const double l2 = dx * dx + dy * dy;
         if (l2 < 4.0) {
             const double d = 2.0 - sqrt(l2);
-            e = e + d * d;
+            e[q] = e[q] + d * d;
         }
-        near += l2 < 5.29;
-        dens += l2 < 16.0;
-    });
-    const double rho = sqrt(px * px + py * py);
-    const double d0 = (rho + 1.0) - R;
-    if (d0 > 0.0) e = e + d0 * d0;
-    f[0] = (float)(log10(e + 1e-20) / 20.0 + 1.0);
-    f[1] = (float)near;
-    f[2] = (float)((R - 1.0 - rho) / R);
-    f[3] = (float)((double)dens / (16.0 * 3.14159265358979323846));
+        near[q] += l2 < 5.29;
+        dens[q] += l2 < 16.0;
+    };
+    unsigned long long mask[2];
+    int cut[2], s1[2], s2[2], longest = 0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        cut[q] = rl[q][0] + rl[q][1];
+        s1[q] = ra[q][1] - rl[q][0];
+        s2[q] = ra[q][2] - cut[q];
+        mask[q] = (unsigned long long)exact[q][2];
+        mask[q] = (mask[q] << (rl[q][1] & 63)) | exact[q][1];
+        mask[q] = (mask[q] << (rl[q][0] & 63)) | exact[q][0];
+        longest = max(longest, __builtin_popcountll(mask[q]));
+    }
+    longest = wave_max_dpp(longest);
+    for (int k = 0; k < longest; ++k) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool has = mask[q] != 0;
+            const int t = __builtin_ctzll(mask[q] | (1ull << 63));
+            mask[q] &= mask[q] - 1;
+            const float2 c = S.psort[has ? t + (t < rl[q][0] ? ra[q][0] : t < cut[q] ? s1[q] : s2[q]) : 0];
+            if (has) visit(q, c);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (!plain[q])               // a crowded neighborhood: candidate by candidate
+            for (int r = 0; r < 3; ++r)
+                for (int t = ra[q][r]; t < ra[q][r] + rl[q][r]; ++t)
+                    if (t != own) visit(q, S.psort[t]);
+        const double px = (double)p[q].x, py = (double)p[q].y;
+        const double rho = sqrt(px * px + py * py);
+        const double d0 = (rho + 1.0) - R;
+        if (d0 > 0.0) e[q] = e[q] + d0 * d0;
+        f[4 * q] = (float)(log10(e[q] + 1e-20) / 20.0 + 1.0);
+        f[4 * q + 1] = (float)near[q];
+        f[4 * q + 2] = (float)((R - 1.0 - rho) / R);
+        f[4 * q + 3] = (float)((double)dens[q] / (16.0 * 3.14159265358979323846));
+    }
 }
 
 __global__ __launch_bounds__(kFeatBlock) void features_kernel(
@@ -100,44 +203,51 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(
     float *__restrict__ feat)
 {
     __shared__ FeatShared S;
-    const int b = blockIdx.y;
+    const int b = blockIdx.y, tid = threadIdx.x;
     const int o = offset[b];
     int n = offset[b + 1] - o;
     const bool bad = n < 0 || n > kMaxN;
     if (bad) n = 0;
     const double R = R64 ? R64[b] : (double)Rf[b];
     const float2 *p2 = reinterpret_cast<const float2 *>(xy) + o;
-    for (int i = threadIdx.x; i < n; i += kFeatBlock) S.pos[i] = p2[i];
-    __syncthreads();
     const Grid g = make_grid(Rf[b], kDensRadius * (1.0f + kCellSafety));
-    bin_circles<kFeatBlock>(S.pos, n, g, S.cell_start, S.cell_circ, S.slot_tmp, S.scan_tmp);
-    // ascending order inside each cell: every sum runs in a fixed order
-    for (int c = threadIdx.x; c < g.nc * g.nc; c += kFeatBlock) {
-        const int a = S.cell_start[c], e = S.cell_start[c + 1];
-        for (int k = a + 1; k < e; ++k) {
-            const uint16_t v = S.cell_circ[k];
-            int m = k - 1;
-            while (m >= a && S.cell_circ[m] > v) {
-                S.cell_circ[m + 1] = S.cell_circ[m];
-                --m;
-            }
-            S.cell_circ[m + 1] = v;
+    {
+        float2 x[kFeatCpt];
+        int own[kFeatCpt];
+#pragma unroll
+        for (int u = 0; u < kFeatCpt; ++u) {
+            const int i = tid + u * kFeatBlock;
+            x[u] = i < n ? p2[i] : make_float2(0.f, 0.f);
+            // a circle at NaN is near nothing, like one at infinity (whose
+            // sign bits are known)
+            if (x[u].x != x[u].x) x[u].x = HUGE_VALF;
+            if (x[u].y != x[u].y) x[u].y = HUGE_VALF;
         }
+        sort_cells<kFeatBlock, kFeatCpt>(tid, x, n, g, S.cell_start, S.cell_circ, S.slot_tmp, S.psort,
+                                         S.scan_tmp, own);
+#pragma unroll
+        for (int u = 0; u < kFeatCpt; ++u)
+            if (tid + u * kFeatBlock < n) S.slot_of[tid + u * kFeatBlock] = (uint16_t)own[u];
+        __syncthreads();
     }
-    __syncthreads();
     const int c0 = blockIdx.x * kFeatChunk;
     const int c1 = min(C, c0 + kFeatChunk);
-    for (int k = c0 + (int)threadIdx.x; k < c1; k += kFeatBlock) {
+    for (int k0 = c0; k0 < c1; k0 += kFeatBlock) {
+        // threads past the end take the last candidate (whole waves: the
+        // longest runs are found across the lanes) and store nothing
+        const int k = min(k0 + tid, c1 - 1);
         const int64_t gi = (int64_t)b * C + k;
         const int i = cand_circle[gi];
+        const bool act = !bad && i >= 0 && i < n;
         float f[8];
-        if (bad || i < 0 || i >= n) {
+        const float2 p[2] = {act ? p2[i] : make_float2(0.f, 0.f),
+                             reinterpret_cast<const float2 *>(cand_dest)[gi]};
+        feature_quads(S, g, R, act, act ? S.slot_of[i] : 0, p, f);
+        if (!act) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) f[q] = __builtin_nanf("");
-        } else {
-            feature_quad(S, g, R, i, S.pos[i], f);
-            feature_quad(S, g, R, i, reinterpret_cast<const float2 *>(cand_dest)[gi], f + 4);
         }
+        if (k0 + tid >= c1) continue;
         float4 *dst = reinterpret_cast<float4 *>(feat + gi * 8);
         dst[0] = make_float4(f[0], f[1], f[2], f[3]);
         dst[1] = make_float4(f[4], f[5], f[6], f[7]);
