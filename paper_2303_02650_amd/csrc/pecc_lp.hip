@@ -49,6 +49,7 @@ constexpr int oW1 = 0, oB1 = 512, oW2 = 576, oB2 = 4672, oW3 = 4736, oB3 = 4800;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Features
@@ -261,7 +262,8 @@ struct NetWeights {
     alignas(16) __bf16 w1[kHid * kFeat];     // [n][k]
     alignas(16) __bf16 w2[kHid * kHid];      // [n][k]
     alignas(16) __bf16 w2t[kHid * kHid];     // [k][n]  (backward)
-    float b1[kHid], b2[kHid], w3[kHid];   // w3 holds the BF16 values
+    alignas(16) float b1[kHid];
+    float b2[kHid], w3[kHid];             // w3 holds the BF16 values
     float b3;
 };
 
@@ -288,40 +290,58 @@ __device__ void load_weights(const float *__restrict__ P, NetWeights &W, bool tr
     }
 }
 
-// erf(x) by the rational approximation 7.1.26 of Abramowitz and Stegun
-// (Handbook of Mathematical Functions): erf(x) = 1 - (a1 t + ... + a5 t^5)
-// exp(-x^2) with t = 1 / (1 + p x) for x >= 0, odd in x; at most 1.5e-7 from
-// erf in exact arithmetic, about 6e-7 in FP32 with the hardware reciprocal
-// and exponential.  gauss receives the exp(-x^2) it forms.  One reciprocal,
-// one exponential and seven FMAs, against the library erff's longer
-// piecewise evaluation: the network's 128 activations per row are most of
-// its vector work.
-__device__ __forceinline__ float erf_as(float x, float &gauss)
+// Phi(-|t|), the normal distribution's tail, from the rational approximation
+// 7.1.26 of Abramowitz and Stegun (Handbook of Mathematical Functions) of
+// erf(x), x = |t| / sqrt 2: (a1 u + ... + a5 u^5) exp(-x^2) / 2 with u =
+// 1 / (1 + p x); at most 0.75e-7 off in exact arithmetic, about 3e-7 in FP32
+// with the hardware reciprocal and exponential.  The factors 1/2 and 1/sqrt 2
+// are in the constants.  gauss receives exp(-t^2 / 2).
+__device__ __forceinline__ float normal_tail(float t, float &gauss)
 {
-    const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
-    float q = fmaf(t, 1.061405429f, -1.453152027f);
-    q = fmaf(t, q, 1.421413741f);
-    q = fmaf(t, q, -0.284496736f);
-    q = fmaf(t, q, 0.254829592f);
-    gauss = __expf(-ax * ax);
-    return copysignf(fmaf(-t * q, gauss, 1.0f), x);
+    const float u = __builtin_amdgcn_rcpf(fmaf(0.23164188f, fabsf(t), 1.0f));
+    float q = fmaf(u, 0.5307027145f, -0.7265760135f);
+    q = fmaf(u, q, 0.7107068705f);
+    q = fmaf(u, q, -0.142248368f);
+    q = fmaf(u, q, 0.127414796f);
+    gauss = __builtin_amdgcn_exp2f(t * (t * -0.72134752044f));
+    return u * q * gauss;
 }
 
-// GELU(t) = t Phi(t) = 0.5 t (1 + erf(t / sqrt 2)) and its derivative
-// Phi(t) + t phi(t), phi(t) = exp(-t^2 / 2) / sqrt(2 pi) (the same
-// exponential as the erf's).
+// GELU(t) = t Phi(t) = max(t, 0) - |t| Phi(-|t|) and its derivative Phi(t) +
+// t phi(t), phi(t) = exp(-t^2 / 2) / sqrt(2 pi) (the same exponential as the
+// tail's).
 __device__ __forceinline__ float gelu(float t)
 {
     float gs;
-    return 0.5f * t * (1.0f + erf_as(t * 0.70710678118654752f, gs));
+    const float tail = normal_tail(t, gs);
+    const float c = __builtin_amdgcn_fmed3f(t, -3.0e38f, 3.0e38f);   // infinity times 0
+    return fmaf(-fabsf(c), tail, __builtin_elementwise_maximum(t, 0.0f));
 }
 
 __device__ __forceinline__ float gelu_prime(float t)
 {
     float gs;
-    const float e = erf_as(t * 0.70710678118654752f, gs);
-    return 0.5f * (1.0f + e) + t * 0.39894228040143268f * gs;
+    const float tail = normal_tail(t, gs);
+    return fmaf(t * 0.39894228040143268f, gs, t < 0.0f ? tail : 1.0f - tail);
+}
+
+// GELU where its derivative is not wanted: log2 Phi(-|t|) is close to a
+// parabola, so one exponential of a polynomial gives the tail.  Degree 6,
+// the coefficients fitted (minimax over 0 <= |t| <= 8) for |t| Phi(-|t|):
+// 5.1e-8 off in exact arithmetic, 8.7e-8 in FP32, against 2.6e-7 for 0.5 t (1
+// + erf(t / sqrt 2)) by the rational approximation.  The network's 128
+// activations per row are most of its vector work: 10 instructions each with
+// one transcendental, 19 with two in that form.  The maximum keeps NaN.
+__device__ __forceinline__ float gelu_fast(float t)
+{
+    const float c = fabsf(__builtin_amdgcn_fmed3f(t, -8.0f, 8.0f));
+    float q = fmaf(c, 3.30928088e-05f, -7.69219594e-04f);
+    q = fmaf(c, q, 8.08071624e-03f);
+    q = fmaf(c, q, -5.34121022e-02f);
+    q = fmaf(c, q, -4.58770961e-01f);
+    q = fmaf(c, q, -1.15120173e+00f);
+    q = fmaf(c, q, -9.99993086e-01f);
+    return fmaf(-c, __builtin_amdgcn_exp2f(q), __builtin_elementwise_maximum(t, 0.0f));
 }
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c)
@@ -352,21 +372,32 @@ __device__ __forceinline__ bf16x8 frag_perm(const __bf16 *M, int t, int c, int g
     return cat(*reinterpret_cast<const bf16x4 *>(row), *reinterpret_cast<const bf16x4 *>(row + 16));
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// The BF16 roundings of a pair of values and of their remainders: hi + lo
+// carries them to about 2^-16 relative.
+__device__ __forceinline__ void split2(float x, float y, unsigned &hi, unsigned &lo)
+{
+    hi = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{x, y}, bf16x2));
+    const float xl = x - __uint_as_float(hi << 16), yl = y - __uint_as_float(hi & 0xffff0000u);
+    lo = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{xl, yl}, bf16x2));
+}
+
 // B fragments of chunk c from a result held as v[t][i] (neuron 16t + 4g + i):
-// hi gets the BF16 rounding, lo the BF16 rounding of the remainder, so that
-// hi + lo carries v to about 2^-16 relative.
+// hi gets the BF16 rounding, lo the BF16 rounding of the remainder.
 __device__ __forceinline__ void frag_chunk(const float (&v)[4][4], int c, bf16x8 &hi, bf16x8 &lo)
 {
+    u32x4 h, l;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float x = v[2 * c + h][i];
-            const __bf16 xh = (__bf16)x;
-            hi[4 * h + i] = xh;
-            lo[4 * h + i] = (__bf16)(x - (float)xh);
-        }
+    for (int k = 0; k < 4; ++k) {
+        unsigned a, b;
+        split2(v[2 * c + k / 2][2 * (k % 2)], v[2 * c + k / 2][2 * (k % 2) + 1], a, b);
+        h[k] = a;
+        l[k] = b;
     }
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // Single BF16 rounding (the backward contractions).
@@ -386,23 +417,26 @@ __device__ __forceinline__ bf16x8 frag_chunk1(const float (&v)[4][4], int c)
 __device__ __forceinline__ bf16x8 frag_x(const float *__restrict__ X, int64_t row, int64_t rows,
                                          int g)
 {
-    bf16x8 b = {};
+    u32x4 b = {0, 0, 0, 0};
     if (g < 2 && row < rows) {
         const float4 *p = reinterpret_cast<const float4 *>(X + row * kFeat);
         const float4 u = p[0], v = p[1];
         const float f[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const __bf16 h = (__bf16)f[i];
-            b[i] = g == 0 ? h : (__bf16)(f[i] - (float)h);
+        for (int i = 0; i < 4; ++i) {
+            unsigned hi, lo;
+            split2(f[2 * i], f[2 * i + 1], hi, lo);
+            b[i] = g == 0 ? hi : lo;
         }
     }
-    return b;
+    return __builtin_bit_cast(bf16x8, b);
 }
 
 // Forward pass of 16 rows; a1/a2 get the pre-activations (neuron 16t+4g+i of
 // this lane's row), h1b the BF16 high parts of h1 as B fragments, h2 the
 // second activations; the return value is the logit of row r in every lane.
+// TRAIN: the activation whose terms the derivative shares.
+template <bool TRAIN>
 __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g, int r,
                                            float (&a1)[4][4], float (&a2)[4][4], bf16x8 (&h1b)[2],
                                            float (&h2)[4][4])
@@ -410,11 +444,12 @@ __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g
     float h1[4][4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        const f32x4 d = mfma(frag_w1(W, t, g, r), xb, f32x4{0.f, 0.f, 0.f, 0.f});
+        const f32x4 bias = *reinterpret_cast<const f32x4 *>(&W.b1[16 * t + 4 * g]);
+        const f32x4 d = mfma(frag_w1(W, t, g, r), xb, bias);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            a1[t][i] = d[i] + W.b1[16 * t + 4 * g + i];
-            h1[t][i] = gelu(a1[t][i]);
+            a1[t][i] = d[i];
+            h1[t][i] = TRAIN ? gelu(a1[t][i]) : gelu_fast(a1[t][i]);
         }
     }
     bf16x8 h1l[2];
@@ -424,15 +459,15 @@ __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const bf16x8 w0 = frag_perm(W.w2, t, 0, g, r), w1 = frag_perm(W.w2, t, 1, g, r);
-        f32x4 d = mfma(w0, h1b[0], f32x4{0.f, 0.f, 0.f, 0.f});
+        f32x4 d = mfma(w0, h1b[0], *reinterpret_cast<const f32x4 *>(&W.b2[16 * t + 4 * g]));
         d = mfma(w1, h1b[1], d);
         d = mfma(w0, h1l[0], d);
         d = mfma(w1, h1l[1], d);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int nn = 16 * t + 4 * g + i;
-            a2[t][i] = d[i] + W.b2[nn];
-            h2[t][i] = gelu(a2[t][i]);
+            a2[t][i] = d[i];
+            h2[t][i] = TRAIN ? gelu(a2[t][i]) : gelu_fast(a2[t][i]);
             zp += W.w3[nn] * h2[t][i];
         }
     }
@@ -444,7 +479,17 @@ __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g
 
 constexpr int kMlpBlock = 256;
 
-__global__ __launch_bounds__(kMlpBlock) void mlp_forward_kernel(const float *__restrict__ P,
+// Bound by vector issue: per 16 rows 32 activations and the split of 24 values
+// per lane against 20 matrix products.  The weight fragments and biases stay
+// in registers over a wave's tiles (read from LDS per tile the kernel takes
+// 70 us), the products start from the biases, and the bound of two waves per
+// SIMD lets them land in vector registers (from accumulation registers every
+// value is moved once more).  137 registers: three workgroups per CU.
+// 524288 rows: 40 us, 63 us with the longer activation, added biases and a
+// grid of four workgroups per CU, of which three were resident.
+constexpr int kMlpPerCu = 3;
+
+__global__ __launch_bounds__(kMlpBlock, 2) void mlp_forward_kernel(const float *__restrict__ P,
                                                                 const float *__restrict__ X,
                                                                 int64_t rows,
                                                                 float *__restrict__ Z)
@@ -460,7 +505,7 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_forward_kernel(const float *__r
         const int64_t row = tile * 16 + r;
         float a1[4][4], a2[4][4], h2[4][4];
         bf16x8 h1b[2];
-        const float z = forward16(W, frag_x(X, row, rows, g), g, r, a1, a2, h1b, h2);
+        const float z = forward16<false>(W, frag_x(X, row, rows, g), g, r, a1, a2, h1b, h2);
         if (g == 0 && row < rows) Z[row] = z;
     }
 }
@@ -536,7 +581,7 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
             const bf16x8 xb = frag_x(X, row, rows, g);
             float a1[4][4], a2[4][4], h2[4][4];
             bf16x8 h1b[2];
-            const float z = forward16(W, xb, g, r, a1, a2, h1b, h2);
+            const float z = forward16<true>(W, xb, g, r, a1, a2, h1b, h2);
             const float y = valid ? Y[row] : 0.0f;
             const float dz = valid ? 1.0f / (1.0f + __expf(-z)) - y : 0.0f;
             if (g == 0 && valid) {
@@ -811,9 +856,10 @@ hipError_t launch_mlp_forward(const float *params, const float *X, int64_t rows,
                               hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
-    // at least two 16-row tiles per wave, at most 4 workgroups per CU
+    // at least two 16-row tiles per wave, and no more workgroups than are
+    // resident: each loads the weights
     const int64_t need = (rows + 4 * 32 - 1) / (4 * 32);
-    const int grid = (int)(need > 1024 ? 1024 : need);
+    const int grid = (int)(need > kMlpPerCu * 256 ? kMlpPerCu * 256 : need);
     hipLaunchKernelGGL(mlp_forward_kernel, dim3(grid), dim3(kMlpBlock), 0, s, params, X, rows, Z);
     return hipGetLastError();
 }
