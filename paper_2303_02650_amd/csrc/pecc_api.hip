@@ -568,10 +568,9 @@ int pecc_mlp_train_step(float *params, float *m, float *v, int32_t *step,
     pecc::AdamArgs a;
     rc = adam_checks(fn, params, m, v, grad, step, hp, &a);
     if (rc) return rc;
-    rc = check_hip(pecc::launch_mlp_grad(params, features, labels, rows, loss, grad, ws, stream),
-                   fn);
-    if (rc) return rc;
-    return check_hip(pecc::launch_adam(params, m, v, grad, step, a, stream), fn);
+    return check_hip(pecc::launch_train_step(params, m, v, step, a, features, labels, rows, loss,
+                                             grad, ws, stream),
+                     fn);
 }
 
 int pecc_propose(const pecc_instances *inst, const float *xy, int32_t cands_per_inst,

@@ -100,6 +100,9 @@ struct AdamArgs {
 };
 hipError_t launch_adam(float *params, float *m, float *v, const float *grad, int32_t *step,
                        const AdamArgs &a, hipStream_t s);
+hipError_t launch_train_step(float *params, float *m, float *v, int32_t *step, const AdamArgs &a,
+                             const float *X, const float *Y, int64_t rows, float *loss, float *grad,
+                             void *ws, hipStream_t s);
 hipError_t launch_propose(const int32_t *offset, const float *xy, int B, int C,
                           const int32_t *cand_circle, const float *cand_dest, const float *scores,
                           int k, int32_t *selected, float *xy_out, hipStream_t s);

@@ -11,8 +11,8 @@
 //   mlp_grad_kernel       forward + backward of the mean BCE-with-logits loss,
 //                         per-workgroup partial gradients (MFMA for every
 //                         contraction), then grad_reduce_kernel sums them in a
-//                         fixed order
-//   adam_kernel           Adam on FP32 master weights
+//                         fixed order and, in a training step, updates
+//   adam_kernel           Adam on FP32 master weights by itself
 //   propose_kernel        top-k distinct circles by score (or the first k
 //                         distinct candidates without usable scores) and the
 //                         relocated layout
@@ -258,10 +258,14 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(
 // ---------------------------------------------------------------------------
 // Network: weights in LDS as BF16 (round to nearest even of the FP32 master)
 // ---------------------------------------------------------------------------
+// Rows of 68 values: the fragments' 8-byte reads down 16 rows, and the
+// transposed row of W2 written across 64 rows, would meet in one bank at 64.
+constexpr int kRow2 = kHid + 4;
+
 struct NetWeights {
     alignas(16) __bf16 w1[kHid * kFeat];     // [n][k]
-    alignas(16) __bf16 w2[kHid * kHid];      // [n][k]
-    alignas(16) __bf16 w2t[kHid * kHid];     // [k][n]  (backward)
+    alignas(16) __bf16 w2[kHid * kRow2];     // [n][k]
+    alignas(16) __bf16 w2t[kHid * kRow2];    // [k][n]  (backward)
     alignas(16) float b1[kHid];
     float b2[kHid], w3[kHid];             // w3 holds the BF16 values
     float b3;
@@ -270,21 +274,30 @@ struct NetWeights {
 template <int BLOCK>
 __device__ void load_weights(const float *__restrict__ P, NetWeights &W, bool transpose)
 {
-    for (int k = threadIdx.x; k < kParams; k += BLOCK) {
-        const float v = P[k];
+    constexpr int kPer = (kParams + BLOCK - 1) / BLOCK;
+    float in[kPer];                  // all in flight together
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int k = threadIdx.x + q * BLOCK;
+        in[q] = P[k < kParams ? k : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int k = threadIdx.x + q * BLOCK;
+        const float v = in[q];
         if (k < oB1) {
             W.w1[k] = (__bf16)v;
         } else if (k < oW2) {
             W.b1[k - oB1] = v;
         } else if (k < oB2) {
-            const int q = k - oW2;
-            W.w2[q] = (__bf16)v;
-            if (transpose) W.w2t[(q % kHid) * kHid + q / kHid] = (__bf16)v;
+            const int n = (k - oW2) / kHid, c = (k - oW2) % kHid;
+            W.w2[n * kRow2 + c] = (__bf16)v;
+            if (transpose) W.w2t[c * kRow2 + n] = (__bf16)v;
         } else if (k < oW3) {
             W.b2[k - oB2] = v;
         } else if (k < oB3) {
             W.w3[k - oW3] = (float)(__bf16)v;
-        } else {
+        } else if (k < kParams) {
             W.b3 = v;
         }
     }
@@ -368,7 +381,7 @@ __device__ __forceinline__ bf16x8 frag_w1(const NetWeights &W, int t, int g, int
 // columns 32c + 16 + 4g + i' - 4.
 __device__ __forceinline__ bf16x8 frag_perm(const __bf16 *M, int t, int c, int g, int r)
 {
-    const __bf16 *row = M + (16 * t + r) * kHid + 32 * c + 4 * g;
+    const __bf16 *row = M + (16 * t + r) * kRow2 + 32 * c + 4 * g;
     return cat(*reinterpret_cast<const bf16x4 *>(row), *reinterpret_cast<const bf16x4 *>(row + 16));
 }
 
@@ -485,7 +498,7 @@ constexpr int kMlpBlock = 256;
 // 70 us), the products start from the biases, and the bound of two waves per
 // SIMD lets them land in vector registers (from accumulation registers every
 // value is moved once more).  137 registers: three workgroups per CU.
-// 524288 rows: 40 us, 63 us with the longer activation, added biases and a
+// 524288 rows: 37 us, 63 us with the longer activation, added biases and a
 // grid of four workgroups per CU, of which three were resident.
 constexpr int kMlpPerCu = 3;
 
@@ -513,18 +526,20 @@ __global__ __launch_bounds__(kMlpBlock, 2) void mlp_forward_kernel(const float *
 // ---------------------------------------------------------------------------
 // Backward
 // ---------------------------------------------------------------------------
+constexpr int kStageRow = 40;         // 32 rows and a pad against bank conflicts
+
 struct WaveStage {                    // one per wave: 32 rows of the pair tile
-    alignas(16) __bf16 da2[kHid][32];
-    alignas(16) __bf16 h1[kHid][32];
-    alignas(16) __bf16 da1[kHid][32];
-    alignas(16) __bf16 x[16][32];     // features 8..15 stay zero
+    alignas(16) __bf16 da2[kHid][kStageRow];
+    alignas(16) __bf16 h1[kHid][kStageRow];
+    alignas(16) __bf16 da1[kHid][kStageRow];
+    alignas(16) __bf16 x[16][kStageRow];     // features 8..15 stay zero
 };
 
 struct GradShared {
     NetWeights W;
     union {
         WaveStage stage[kMlpBlock / 64];
-        float sum[kParams + 1];       // workgroup reduction after the row loop
+        float sum[kMlpBlock / 64][kParams + 1];   // the waves' sums after the row loop
     } u;
 };
 
@@ -537,20 +552,27 @@ __device__ __forceinline__ void wave_sync()
 
 __device__ __forceinline__ float sum16(float v)   // over the 16 lanes of a group
 {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 8);
+    v += dpp<kDppXor1>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppHalfMirror>(v);
+    v += dpp<kDppRowMirror>(v);
     return v;
 }
 
+// Bound by latency at a minibatch (8192 rows: one tile of 32 rows per wave):
+// the weights' loads are in flight together, their transposed copy and the
+// staged tiles are laid out without bank conflicts, and the waves' sums meet
+// in LDS in one step instead of a read-modify-write chain of 130 values per
+// lane and wave.  8192 rows: 16 us (32 us before); with the update in the
+// reduction (5 us) a training step takes 19 us, 51 us before.
 // Per workgroup: partial d(sum of row losses)/d params (not yet divided by
 // rows) and the partial loss sum, written to part[blockIdx.x][0..kParams].
 __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__restrict__ P,
                                                              const float *__restrict__ X,
                                                              const float *__restrict__ Y,
                                                              int64_t rows,
-                                                             float *__restrict__ part)
+                                                             float *__restrict__ part,
+                                                             int32_t *__restrict__ step)
 {
     __shared__ GradShared S;
     load_weights<kMlpBlock>(P, S.W, true);
@@ -558,7 +580,7 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
     const int wv = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
     WaveStage &st = S.u.stage[wv];
-    for (int k = lane; k < 16 * 32; k += 64) (&st.x[0][0])[k] = (__bf16)0.0f;
+    for (int k = lane; k < 16 * kStageRow; k += 64) (&st.x[0][0])[k] = (__bf16)0.0f;
     __syncthreads();
 
     f32x4 gW2[4][4], gW1[4];
@@ -642,9 +664,10 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
         wave_sync();
     }
 
-    // ---- workgroup reduction in a fixed order: wave 0 stores, waves 1..3 add
-    __syncthreads();                  // the stages are dead; reuse as sum[]
-    float *sum = S.u.sum;
+    // ---- workgroup reduction in a fixed order: every wave stores its sums,
+    // the threads add them in the order of the waves
+    __syncthreads();                  // the stages are dead; reuse as sum[][]
+    float *sum = S.u.sum[wv];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -655,75 +678,95 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
         }
     gB3 = sum16(gB3);
     lsum = sum16(lsum);
-    for (int w = 0; w < kMlpBlock / 64; ++w) {
-        if (wv == w) {
-            const bool first = w == 0;
 #pragma unroll
-            for (int tn = 0; tn < 4; ++tn)
+    for (int tn = 0; tn < 4; ++tn)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int nn = 16 * tn + 4 * g + i;
+        for (int i = 0; i < 4; ++i) {
+            const int nn = 16 * tn + 4 * g + i;
 #pragma unroll
-                    for (int tk = 0; tk < 4; ++tk) {
-                        float *q = &sum[oW2 + nn * kHid + 16 * tk + r];
-                        *q = first ? gW2[tn][tk][i] : *q + gW2[tn][tk][i];
-                    }
-                    if (r < kFeat) {
-                        float *q = &sum[oW1 + nn * kFeat + r];
-                        *q = first ? gW1[tn][i] : *q + gW1[tn][i];
-                    }
-                    if (r == 0) {
-                        float *q3 = &sum[oW3 + nn], *q2 = &sum[oB2 + nn], *q1 = &sum[oB1 + nn];
-                        *q3 = first ? gW3[tn][i] : *q3 + gW3[tn][i];
-                        *q2 = first ? gB2[tn][i] : *q2 + gB2[tn][i];
-                        *q1 = first ? gB1[tn][i] : *q1 + gB1[tn][i];
-                    }
-                }
-            if (lane == 0) {
-                sum[oB3] = first ? gB3 : sum[oB3] + gB3;
-                sum[kParams] = first ? lsum : sum[kParams] + lsum;
+            for (int tk = 0; tk < 4; ++tk) sum[oW2 + nn * kHid + 16 * tk + r] = gW2[tn][tk][i];
+            if (r < kFeat) sum[oW1 + nn * kFeat + r] = gW1[tn][i];
+            if (r == 0) {
+                sum[oW3 + nn] = gW3[tn][i];
+                sum[oB2 + nn] = gB2[tn][i];
+                sum[oB1 + nn] = gB1[tn][i];
             }
         }
-        __syncthreads();
+    if (lane == 0) {
+        sum[oB3] = gB3;
+        sum[kParams] = lsum;
     }
+    __syncthreads();
     float *dst = part + (int64_t)blockIdx.x * (kParams + 1);
-    for (int k = threadIdx.x; k <= kParams; k += kMlpBlock) dst[k] = sum[k];
+    for (int k = threadIdx.x; k <= kParams; k += kMlpBlock) {
+        float v = S.u.sum[0][k];
+#pragma unroll
+        for (int w = 1; w < kMlpBlock / 64; ++w) v += S.u.sum[w][k];
+        dst[k] = v;
+    }
+    // the optimizer's step count, for the update that follows
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) *step += 1;
+}
+
+// ---------------------------------------------------------------------------
+// Adam
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void adam_update(float *__restrict__ p, float *__restrict__ m,
+                                            float *__restrict__ v, float gk, int t, const AdamArgs &a,
+                                            int k)
+{
+    const float c1 = (float)(1.0 - pow((double)a.b1, (double)t));
+    const float c2 = (float)(1.0 - pow((double)a.b2, (double)t));
+    const float mk = a.b1 * m[k] + (1.0f - a.b1) * gk;
+    const float vk = a.b2 * v[k] + (1.0f - a.b2) * gk * gk;
+    m[k] = mk;
+    v[k] = vk;
+    p[k] -= a.lr * (mk / c1) / (sqrtf(vk / c2) + a.eps);
 }
 
 // grad[k] = (sum over workgroups, in workgroup order) / rows; loss likewise.
-__global__ void grad_reduce_kernel(const float *__restrict__ part, int nparts, int64_t rows,
-                                   float *__restrict__ grad, float *__restrict__ loss)
+// ADAM: and the update of parameter k, with the count in *step.  A thread's
+// sum is a serial chain of additions; its loads are not: 16 in flight (one at
+// a time the sum of 64 parts takes 16 us).  Workgroups of one wave, to spread
+// over the CUs.
+constexpr int kReduceBlock = 64;
+
+template <bool ADAM>
+__global__ __launch_bounds__(kReduceBlock) void grad_reduce_kernel(
+    const float *__restrict__ part, int nparts, int64_t rows, float *__restrict__ grad,
+    float *__restrict__ loss, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
+    const int32_t *__restrict__ step, AdamArgs a)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    const int k = blockIdx.x * kReduceBlock + threadIdx.x;
     if (k > kParams) return;
+    constexpr int kFly = 16;
     float s = 0.0f;
-    for (int w = 0; w < nparts; ++w) s += part[(int64_t)w * (kParams + 1) + k];
-    const float v = rows > 0 ? s / (float)rows : 0.0f;
+    for (int w = 0; w < nparts; w += kFly) {
+        float x[kFly];
+#pragma unroll
+        for (int q = 0; q < kFly; ++q) x[q] = part[(int64_t)min(w + q, nparts - 1) * (kParams + 1) + k];
+#pragma unroll
+        for (int q = 0; q < kFly; ++q)
+            if (w + q < nparts) s += x[q];
+    }
+    const float mean = rows > 0 ? s / (float)rows : 0.0f;
     if (k < kParams) {
-        grad[k] = v;
+        grad[k] = mean;
+        if constexpr (ADAM) adam_update(p, m, v, mean, *step, a, k);
     } else if (loss) {
-        *loss = v;
+        *loss = mean;
     }
 }
 
-// ---------------------------------------------------------------------------
-// Adam (step counter on the device: t = *step + 1 is used, then stored)
-// ---------------------------------------------------------------------------
+// An update by itself: step counter on the device, t = *step + 1 is used,
+// then stored.
 __global__ void adam_kernel(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
                             const float *__restrict__ g, const int32_t *__restrict__ step,
                             AdamArgs a, int count)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= count) return;
-    const int t = *step + 1;
-    const float c1 = (float)(1.0 - pow((double)a.b1, (double)t));
-    const float c2 = (float)(1.0 - pow((double)a.b2, (double)t));
-    const float gk = g[k];
-    const float mk = a.b1 * m[k] + (1.0f - a.b1) * gk;
-    const float vk = a.b2 * v[k] + (1.0f - a.b2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    p[k] -= a.lr * (mk / c1) / (sqrtf(vk / c2) + a.eps);
+    adam_update(p, m, v, g[k], *step + 1, a, k);
 }
 
 __global__ void step_bump_kernel(int32_t *step) { *step += 1; }
@@ -874,12 +917,25 @@ hipError_t launch_mlp_grad(const float *params, const float *X, const float *Y, 
 {
     const int grid = mlp_grid(rows, 4 * 32);
     float *part = static_cast<float *>(ws);
-    hipLaunchKernelGGL(mlp_grad_kernel, dim3(grid), dim3(kMlpBlock), 0, s, params, X, Y, rows,
-                       part);
+    mlp_grad_kernel<<<grid, kMlpBlock, 0, s>>>(params, X, Y, rows, part, nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((kParams + 1 + 255) / 256), dim3(256), 0, s, part,
-                       grid, rows, grad, loss);
+    grad_reduce_kernel<false><<<(kParams + kReduceBlock) / kReduceBlock, kReduceBlock, 0, s>>>(
+        part, grid, rows, grad, loss, nullptr, nullptr, nullptr, nullptr, AdamArgs{});
+    return hipGetLastError();
+}
+
+hipError_t launch_train_step(float *params, float *m, float *v, int32_t *step, const AdamArgs &a,
+                             const float *X, const float *Y, int64_t rows, float *loss, float *grad,
+                             void *ws, hipStream_t s)
+{
+    const int grid = mlp_grid(rows, 4 * 32);
+    float *part = static_cast<float *>(ws);
+    mlp_grad_kernel<<<grid, kMlpBlock, 0, s>>>(params, X, Y, rows, part, step);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    grad_reduce_kernel<true><<<(kParams + kReduceBlock) / kReduceBlock, kReduceBlock, 0, s>>>(
+        part, grid, rows, grad, loss, params, m, v, step, a);
     return hipGetLastError();
 }
 
