@@ -42,7 +42,6 @@ enum : int { kModeWhole = 0, kModeAdj = 1, kModeSeq = 2, kModeDense = 3 };
 // neighbor list up to the longest list of its wave: a pair with it has no
 // overlap, so its terms add exact zeros and the list loop needs no test.
 constexpr int far_off(int nmax) { return nmax * (int)sizeof(float2); }
-constexpr float kFarCoord = 3.0e18f;      // (3e18)^2 * 2 is finite in FP32
 
 // Whole-instance descent: row length of the Gram ring in LDS.  Row r (the
 // basis vector in storage slot r: s 0..9, y 10..19, g 20) holds the s

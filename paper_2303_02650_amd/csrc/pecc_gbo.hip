@@ -30,6 +30,17 @@
 //     visits in the caller's workspace (L2-resident per instance).
 // Results are bitwise reproducible: membership, list order and every sum
 // are functions of the positions only.
+//
+// Bound by latency: one wave per SIMD on as many CUs as there are instances,
+// whose visits are serial chains of LDS reads, global loads (history) and
+// dependent arithmetic.  So loads that do not depend on each other are issued
+// together (history, Gram matrix, eight list neighbors of a circle, four
+// circles of a thread outside the visits), what a wave keeps in LDS is one
+// array indexed by offsets (an access through a chosen pointer becomes a flat
+// one, which waits for every counter), and the lists are built from mask bits.
+// 64 instances of n = 1000 in 4 x 4 blocks, 300 outer iterations: 17.8 ms,
+// 24.5 ms with one load or neighbor at a time.  Loading the next visit's
+// history ahead gained under 1 % more (not kept).
 #include "pecc_device.hpp"
 #include "pecc_host.hpp"
 #include "pecc_launch.hpp"
@@ -43,43 +54,157 @@ constexpr int kGCPB = 2;                    // circles per lane inside a batch
 constexpr int kGEll = 24;                   // neighbor slots per circle
 constexpr int kMaxGboBatch = kWave * kGCPB; // circles per batch at most
 constexpr int kMaxGboBatches = 64;          // blocks x blocks, blocks <= 8
+constexpr int kGU = kMaxN / kGT;            // circles per thread outside the visits
+constexpr int kInBatch = kMaxN * (int)sizeof(float2);      // list entries: the trial position
+constexpr int kNowhere = 2 * kInBatch;                     // and the place beyond everything
+
+constexpr int kTot = 2 * kNB * kNB;         // slot totals in a wave's array
 
 struct GboShared {
-    float2 pos[kMaxN];                      // positions at the start of the colour
-    float2 tpos[kMaxN];                     // trial positions of visited batches
+    // positions at the start of the colour, trial positions of the visited
+    // batches, a place beyond everything; a list entry is a byte offset here
+    float2 xy[2 * kMaxN + 1];
     float2 npos[kMaxN];                     // positions after the colour
     float2 xref[kMaxN];                     // positions at the last rebuild
     int cell_start[kMaxCells + 1];
     uint16_t cell_circ[kMaxN];
     uint16_t slot_tmp[kMaxN];
-    uint16_t list[kGEll][kMaxN];
+    float2 psort[kMaxN + 8];                // positions in cell order
+    uint16_t code[kMaxN];                   // and there, circle + batch << 10
+    uint16_t list[kGEll][kMaxN];            // kInBatch set: a circle of the same batch
     uint8_t list_n[kMaxN];
     uint8_t batch_of[kMaxN];
     uint16_t members[kMaxN];                // circles grouped by batch, ascending
     int bstart[kMaxGboBatches + 1];
     uint8_t colour_batches[4][kMaxGboBatches];
     int ncolour[4];
-    float Bw[kGW][2][kNB * kNB];            // per-wave Gram matrix, double-buffered
-    float totw[kGW][kWave];                 // per-wave slot totals
+    // per wave: Gram matrix, double-buffered, and the slot totals (one array,
+    // so that an entry's source is an offset and every access stays an LDS one)
+    float wave[kGW][kTot + kWave];
     uint16_t bsrc[2][kNB * kNB];
     float redf[2][kGW];
     double redd[2][kGW];
     int scan_tmp[kGW + 1];
+    int bk[kMaxGboBatches], bhead[kMaxGboBatches];   // pairs and ring position of every batch
     int evw[kGW];                           // per-wave evaluation counts at the end
     int flag, over, bad, work;
 };
 
-struct GboBatchState {   // in the workspace, per batch
-    int k, head;
-};
-
 // Workspace of one instance: history S and Y (rings of kMM pairs of up to
-// kMaxGboBatch circles), Gram matrices and ring state of every batch.
+// kMaxGboBatch circles) and Gram matrices of every batch.
 __host__ __device__ inline size_t gbo_instance_bytes(int nbat)
 {
     const size_t b = (size_t)nbat * (2 * (size_t)kMM * kMaxGboBatch * sizeof(float2) +
-                                     (size_t)kNB * kNB * sizeof(float) + sizeof(GboBatchState));
+                                     (size_t)kNB * kNB * sizeof(float));
     return (b + 255) & ~(size_t)255;
+}
+
+// Neighbor lists at the current positions: the circles sorted into cells, and
+// of every circle the neighbors (predicate near64 with c2) in the order of the
+// cells.  Mask bits over the sorted positions (neighbor_masks), the four circles
+// of a thread side by side; a wave with a circle that has more candidates than
+// a mask holds goes through them one by one.  Returns whether some list is too long.
+__device__ __forceinline__ bool gbo_build(GboShared &sh, int tid, int n, const Grid &grid, double c2)
+{
+    {
+        float2 x[kGU];
+        int own[kGU];
+#pragma unroll
+        for (int u = 0; u < kGU; ++u) x[u] = sh.xy[tid + u * kGT];
+        sort_cells<kGT, kGU>(tid, x, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp, sh.psort,
+                             sh.scan_tmp, own);
+#pragma unroll
+        for (int u = 0; u < kGU; ++u)
+            if (tid + u * kGT < n)
+                sh.code[own[u]] = (uint16_t)(tid + u * kGT + (sh.batch_of[tid + u * kGT] << 10));
+    }
+    if (tid == 0) sh.over = 0;
+    __syncthreads();
+    bool over = false;
+    float2 q[kGU];
+    bool on[kGU], fits = true;
+    int ci[kGU], bi[kGU], ra[kGU][3], rl[kGU][3], self[kGU], kmax[3] = {0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < kGU; ++e) {
+        const int s = tid + e * kGT;
+        on[e] = s < n;
+        q[e] = sh.psort[on[e] ? s : 0];
+        const int code = sh.code[on[e] ? s : 0];
+        ci[e] = code & 1023;
+        bi[e] = code >> 10;
+    }
+#pragma unroll
+    for (int e = 0; e < kGU; ++e) {
+        cell_rows(q[e], on[e], tid + e * kGT, grid, sh.cell_start, ra[e], rl[e], self[e]);
+        fits = fits && max(rl[e][0], max(rl[e][1], rl[e][2])) <= 32 && rl[e][0] + rl[e][1] + rl[e][2] <= 64;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) kmax[r] = max(kmax[r], rl[e][r]);
+    }
+    // list entry of the circle of a code
+    auto entry = [&](int code, int batch) {
+        return (uint16_t)((code & 1023) * (int)sizeof(float2) + (code >> 10 == batch ? kInBatch : 0));
+    };
+    if (__builtin_amdgcn_ballot_w64(!fits)) {
+#pragma unroll
+        for (int e = 0; e < kGU; ++e) {
+            if (!on[e]) continue;
+            int m = 0;
+            for (int r = 0; r < 3; ++r)
+                for (int t = ra[e][r]; t < ra[e][r] + rl[e][r]; ++t) {
+                    if (t == tid + e * kGT || !near64(q[e], sh.psort[t], c2)) continue;
+                    if (m < kGEll) sh.list[m][ci[e]] = entry(sh.code[t], bi[e]);
+                    ++m;
+                }
+            over = over || m > kGEll;
+            sh.list_n[ci[e]] = (uint8_t)min(m, kGEll);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) kmax[r] = wave_max_dpp(kmax[r]);
+        unsigned long long mask[kGU];
+        neighbor_masks<kGU, 4, kMaxN>(q, on, self, ra, rl, kmax, sh.psort, c2, mask);
+        int cut[kGU], s1[kGU], s2[kGU], code[kGU], m = 0;
+        bool has[kGU];
+#pragma unroll
+        for (int e = 0; e < kGU; ++e) {
+            cut[e] = rl[e][0] + rl[e][1];
+            s1[e] = ra[e][1] - rl[e][0];
+            s2[e] = ra[e][2] - cut[e];
+            const int cnt = __builtin_popcountll(mask[e]);
+            over = over || cnt > kGEll;
+            if (on[e]) sh.list_n[ci[e]] = (uint8_t)min(cnt, kGEll);
+            m = max(m, cnt);
+        }
+        m = min(wave_max_dpp(m), kGEll);
+        // the next neighbors' codes are read before the current ones are stored
+#pragma unroll
+        for (int e = 0; e < kGU; ++e)
+            has[e] = next_neighbor(mask[e], rl[e][0], cut[e], ra[e][0], s1[e], s2[e], sh.code, code[e]);
+        for (int k = 0; k < m; ++k) {
+            int cur[kGU];
+            bool put[kGU];
+#pragma unroll
+            for (int e = 0; e < kGU; ++e) { cur[e] = code[e]; put[e] = has[e]; }
+#pragma unroll
+            for (int e = 0; e < kGU; ++e)
+                has[e] = next_neighbor(mask[e], rl[e][0], cut[e], ra[e][0], s1[e], s2[e], sh.code, code[e]);
+#pragma unroll
+            for (int e = 0; e < kGU; ++e)
+                if (put[e]) sh.list[k][ci[e]] = entry(cur[e], bi[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < kGU; ++e)
+        if (on[e]) sh.xref[ci[e]] = q[e];
+    if (over) sh.over = 1;
+    if (tid == 0) sh.flag = 0;
+    __syncthreads();
+    return sh.over != 0;
+}
+
+__device__ __forceinline__ float2 at_offset(const GboShared &sh, int byte_offset)
+{
+    return *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(sh.xy) + byte_offset);
 }
 
 template <bool F64>
@@ -96,7 +221,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
     const int nbat = blocks * blocks;
     for (int q = tid; q < 2 * kNB * kNB; q += kGT)
         sh.bsrc[q / (kNB * kNB)][q % (kNB * kNB)] = gram_source(q % (kNB * kNB), q >= kNB * kNB);
-    const float c2lo = (float)(A.c2 * (1.0 - 1e-5)), c2hi = (float)(A.c2 * (1.0 + 1e-5));
+    if (tid == 0) sh.xy[2 * kMaxN] = make_float2(kFarCoord, kFarCoord);
 
     for (;;) {
         __syncthreads();
@@ -129,13 +254,12 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
         float2 *histS = reinterpret_cast<float2 *>(wsi);
         float2 *histY = histS + (size_t)nbat * kMM * kMaxGboBatch;
         float *gram = reinterpret_cast<float *>(histY + (size_t)nbat * kMM * kMaxGboBatch);
-        GboBatchState *bst = reinterpret_cast<GboBatchState *>(gram + (size_t)nbat * kNB * kNB);
 
         // ---- load, partition (FP64, from the input positions) ------------------
         if (tid == 0) { sh.bad = 0; sh.flag = 1; }
         for (int i = tid; i < n; i += kGT) {
             const float2 p = reinterpret_cast<const float2 *>(xy)[off + i];
-            sh.pos[i] = p;
+            sh.xy[i] = p;
             sh.npos[i] = p;
             const double S = 2.0 * (double)R / blocks;
             const double tx = floor(((double)p.x + (double)R) / S), ty = floor(((double)p.y + (double)R) / S);
@@ -144,7 +268,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
             sh.batch_of[i] = (uint8_t)(by * blocks + bx);
         }
         for (int e = tid; e < nbat * kNB * kNB; e += kGT) gram[e] = 0.f;
-        for (int p = tid; p < nbat; p += kGT) { bst[p].k = 0; bst[p].head = 0; }
+        for (int p = tid; p < nbat; p += kGT) { sh.bk[p] = 0; sh.bhead[p] = 0; }
         __syncthreads();
         // members, ascending inside a batch: one thread per batch
         for (int p = tid; p < nbat; p += kGT) {
@@ -184,215 +308,188 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
         bool overflow = false;
         double ehist = 0.0, E64t = -1.0;
         float Ew = 0.f, gsum = 0.f, gs_all = 0.f;   // gsum: this wave's visits
-        const int W = A.ftol_window;
+        const int window = A.ftol_window;
 
-        for (;;) {
-            // ---- neighbor lists at sh.pos when flagged ---------------------------
+        constexpr int kGramTurns = (kNB * kNB + kWave - 1) / kWave;
+        // entry of a turn; the last turn's spare lanes repeat the last entry
+        auto gram_entry = [&](int t) { return min(lane + t * kWave, kNB * kNB - 1); };
+        // A turn is a colour; the energies and stop tests come before colour 0.
+        for (int colour = 0;; colour = (colour + 1) & 3) {
+            // ---- neighbor lists at the current positions when flagged -------------
             if (sh.flag) {
-                bin_circles<kGT>(sh.pos, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp,
-                                 sh.scan_tmp);
-                for (int cc = tid; cc < grid.nc * grid.nc; cc += kGT) {
-                    const int a = sh.cell_start[cc], z = sh.cell_start[cc + 1];
-                    for (int q = a + 1; q < z; ++q) {
-                        const uint16_t key = sh.cell_circ[q];
-                        int t = q - 1;
-                        while (t >= a && sh.cell_circ[t] > key) { sh.cell_circ[t + 1] = sh.cell_circ[t]; --t; }
-                        sh.cell_circ[t + 1] = key;
-                    }
-                }
-                if (tid == 0) sh.over = 0;
-                __syncthreads();
-                for (int i0 = 0; i0 < n; i0 += kGT) {
-                    const int i = i0 + tid;
-                    const bool act = i < n;
-                    const float2 q = sh.pos[act ? i : 0];
-                    const int bi = sh.batch_of[act ? i : 0];
-                    // candidates: the circles of the 3 x 3 cells around q's, in cell
-                    // order; three cell rows (start, length), read together, one run
-                    int ra[3], rl[3];
-                    {
-                        const int cx = cell_coord(q.x, grid), cy = cell_coord(q.y, grid);
-                        const int y0 = cy > 0 ? cy - 1 : 0, y1 = cy < grid.nc - 1 ? cy + 1 : grid.nc - 1;
-                        const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < grid.nc - 1 ? cx + 1 : grid.nc - 1;
-#pragma unroll
-                        for (int r = 0; r < 3; ++r) {
-                            const bool row = act && y0 + r <= y1;
-                            const int yy = y0 + r <= y1 ? y0 + r : y0;
-                            const int a = sh.cell_start[yy * grid.nc + x0];
-                            const int z = sh.cell_start[yy * grid.nc + x1 + 1];
-                            ra[r] = row ? a : 0;
-                            rl[r] = row ? z - a : 0;
-                        }
-                    }
-                    const int K = rl[0] + rl[1] + rl[2];
-                    // the wave walks its longest run, four candidates per step with their
-                    // reads in flight; FP32 test outside the +-1e-5 band around the
-                    // cutoff, FP64 inside, behind one uniform branch
-                    const int kmax = wave_max_dpp(K);
-                    int m = 0;
-                    for (int k0 = 0; k0 < kmax; k0 += 4) {
-                        int jv[4];
-                        bool ok[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int k = k0 + u;
-                            ok[u] = k < K;
-                            const int t = k < rl[0]         ? ra[0] + k
-                                        : k < rl[0] + rl[1] ? ra[1] + (k - rl[0])
-                                                            : ra[2] + (k - rl[0] - rl[1]);
-                            const int jj = sh.cell_circ[ok[u] ? t : 0];
-                            jv[u] = ok[u] ? jj : 0;
-                        }
-                        float2 pv[4];
-                        int bj[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            pv[u] = sh.pos[jv[u]];
-                            bj[u] = sh.batch_of[jv[u]];
-                        }
-                        bool nb[4], band[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const float dx = q.x - pv[u].x, dy = q.y - pv[u].y;
-                            const float l2 = dx * dx + dy * dy;
-                            const bool cand = ok[u] && jv[u] != i;
-                            nb[u] = cand && l2 < c2lo;
-                            band[u] = cand && l2 >= c2lo && l2 <= c2hi;
-                        }
-                        if (__builtin_amdgcn_ballot_w64(band[0] || band[1] || band[2] || band[3])) {
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                if (band[u]) nb[u] = near64(q, pv[u], A.c2);
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            if (nb[u] && m < kGEll) sh.list[m][i] = (uint16_t)(jv[u] | (bj[u] == bi ? 0x8000 : 0));
-                            m += nb[u] ? 1 : 0;
-                        }
-                    }
-                    if (act) {
-                        if (m > kGEll) sh.over = 1;
-                        sh.list_n[i] = (uint8_t)(m < kGEll ? m : kGEll);
-                        sh.xref[i] = q;
-                    }
-                }
+                overflow = gbo_build(sh, tid, n, grid, A.c2);
                 ++rebuilds;
-                if (tid == 0) sh.flag = 0;
-                __syncthreads();
-                overflow = sh.over != 0;
             }
 
             // ---- whole-instance energies and the stop tests ------------------------
-            {
-                float e = 0.f, e1 = 0.f;
+            if (colour == 0) {
+                float e = 0.f;
                 double et = 0.0;
-                for (int i = tid; i < n; i += kGT) {
-                    const float2 q = sh.pos[i];
-                    float ec = 0.f, e1c = 0.f, gx = 0.f, gy = 0.f;
-                    double eoc = 0.0, etc = 0.0;
-                    auto visit_pair = [&](int j) {
-                        if (j <= i) return;
-                        const float2 pj = sh.pos[j];
-                        pair_term32(q, pj, true, two_r, four_r2, ec, e1c, gx, gy);
-                        pair_term64(q, pj, two_r64, four_r2_64, eoc, etc);
-                    };
-                    if (!overflow) {
-                        const int mc = sh.list_n[i];
-                        for (int t = 0; t < mc; ++t) visit_pair(sh.list[t][i] & 0x7fff);
-                    } else {
-                        for_each_candidate(i, q, grid, sh.cell_start, sh.cell_circ, visit_pair);
+                float2 qv[kGU];
+                float ec[kGU];
+                double etc[kGU];
+                int mc[kGU], mmax = 0;
+#pragma unroll
+                for (int u = 0; u < kGU; ++u) {
+                    const int i = tid + u * kGT;
+                    qv[u] = sh.xy[i];
+                    mc[u] = i < n ? sh.list_n[i] : 0;
+                    mmax = max(mmax, mc[u]);
+                    ec[u] = 0.f;
+                    etc[u] = 0.0;
+                }
+                // every pair once, at its lower circle; a thread's four circles
+                // side by side, two neighbors each in flight (a neighbor that
+                // does not count stands beyond everything and adds zeros)
+                auto visit_pair = [&](float2 q, float2 pj, float &ecu, double &etu) {
+                    float e1 = 0.f, gx = 0.f, gy = 0.f;
+                    double eo = 0.0;
+                    pair_term32(q, pj, true, two_r, four_r2, ecu, e1, gx, gy);
+                    const float l2 = dot2(q.x - pj.x, q.x - pj.x, q.y - pj.y, q.y - pj.y);
+                    const float il = l2 > 0.f ? __builtin_amdgcn_rsqf(l2) : 0.f;
+                    pair_term64s(q, pj, l2 * il, il, two_r64, four_r2_64, eo, etu);
+                };
+                if (!overflow) {
+                    mmax = wave_max_dpp(mmax);
+                    for (int t0 = 0; t0 < mmax; t0 += 2) {
+                        int o[2][kGU];
+                        float2 pj[2][kGU];
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int u = 0; u < kGU; ++u) o[t][u] = sh.list[t0 + t][tid + u * kGT];
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int u = 0; u < kGU; ++u) {
+                                const int j = o[t][u] & ~kInBatch;
+                                const bool use = t0 + t < mc[u] && j > (tid + u * kGT) * (int)sizeof(float2);
+                                pj[t][u] = at_offset(sh, use ? j : kNowhere);
+                            }
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int u = 0; u < kGU; ++u) visit_pair(qv[u], pj[t][u], ec[u], etc[u]);
                     }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kGU; ++u) {
+                        const int i = tid + u * kGT;
+                        if (i < n)
+                            for_each_candidate(i, qv[u], grid, sh.cell_start, sh.cell_circ, [&](int j) {
+                                if (j > i) visit_pair(qv[u], sh.xy[j], ec[u], etc[u]);
+                            });
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kGU; ++u) {
+                    if (tid + u * kGT >= n) continue;
+                    const float2 q = qv[u];
                     const float r2 = q.x * q.x + q.y * q.y;
                     const float ir = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
                     const float d0 = fmaxf(r2 * ir + rad - R, 0.f);
-                    ec += d0 * d0;
-                    const float d01 = fmaxf(d0 - (rad - 1.f), 0.f);
-                    e1c += d01 * d01;
-                    const double r64 = sqrt((double)q.x * q.x + (double)q.y * q.y);
+                    ec[u] += d0 * d0;
+                    const double r64 = sqrt(dot2((double)q.y, (double)q.y, (double)q.x, (double)q.x));
                     const double ct = r64 + 1.0 - R64;
-                    if (ct > 0.0) etc += ct * ct;
-                    if (!(isfinite(q.x) && isfinite(q.y))) { ec = e1c = __builtin_nanf(""); etc = __builtin_nan(""); }
-                    e += ec;
-                    e1 += e1c;
-                    et += etc;
+                    if (ct > 0.0) etc[u] += ct * ct;
+                    if (!(isfinite(q.x) && isfinite(q.y))) { ec[u] = __builtin_nanf(""); etc[u] = __builtin_nan(""); }
+                    e += ec[u];
+                    et += etc[u];
                 }
                 e = wave_sum(e);
-                e1 = wave_sum(e1);
                 et = wave_sum(et);
                 const int par = outer & 1;
                 if (lane == 0) {
                     sh.redf[par][wv] = e;
                     sh.redd[par][wv] = et;
-                    sh.totw[wv][0] = e1;   // free at this point
-                    sh.totw[wv][1] = gsum;
+                    sh.wave[wv][kTot + 1] = gsum;   // free at this point
                 }
                 __syncthreads();
                 Ew = 0.f;
-                float E1w = 0.f, gs = 0.f;
+                float gs = 0.f;
                 double ett = 0.0;
 #pragma unroll
                 for (int w = 0; w < kGW; ++w) {
                     Ew += sh.redf[par][w];
                     ett += sh.redd[par][w];
-                    E1w += sh.totw[w][0];
-                    gs += sh.totw[w][1];
+                    gs += sh.wave[w][kTot + 1];
                 }
-                __syncthreads();   // totw is the waves' scratch again below
+                __syncthreads();   // the totals are the waves' scratch again below
                 gs_all = gs;
                 E64t = ett;
                 const double Eacc = (double)Ew;
                 if (!isfinite(Ew)) { status = 6; break; }
                 if (E64t < A.e_feasible) { status = 1; break; }
                 if (outer > 0 && gs <= A.g_tol) { status = 2; break; }
-                if (A.ftol > 0.f && outer >= W) {
-                    const int src = (outer - W) % (W + 1);
+                if (A.ftol > 0.f && outer >= window) {
+                    const int src = (outer - window) % (window + 1);
                     const long long bits = __builtin_bit_cast(long long, ehist);
                     const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), src);
                     const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), src);
                     const double eold = __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
                     if (eold - Eacc <= (double)A.ftol * eold) { status = 3; break; }
                 }
-                if (lane == outer % (W + 1)) ehist = Eacc;
+                if (lane == outer % (window + 1)) ehist = Eacc;
                 if (outer >= A.max_iter) { status = 5; break; }
-                (void)E1w;
+                ++outer;
+                gsum = 0.f;
             }
 
-            // ---- one outer iteration: the four colours ---------------------------
-            gsum = 0.f;
-            for (int colour = 0; colour < 4; ++colour) {
+            // ---- the colour's batches ---------------------------------------------
+            {
                 for (int r = wv; r < sh.ncolour[colour]; r += kGW) {
                     const int p = sh.colour_batches[colour][r];
                     const int m0 = sh.bstart[p], np = sh.bstart[p + 1] - m0;
                     // ---- visit batch p: registers <- its circles and history --
-                    GboBatchState st = bst[p];
-                    int k = st.k;
+                    int k = __builtin_amdgcn_readfirstlane(sh.bk[p]);
+                    int head = __builtin_amdgcn_readfirstlane(sh.bhead[p]);
                     bool act[kGCPB];
                     int ci[kGCPB];
                     float2 x[kGCPB], g[kGCPB], pd[kGCPB];
-                    float2 S[kGCPB][kMM], Y[kGCPB][kMM];
-                    float2 *hS = histS + (size_t)p * kMM * kMaxGboBatch;
-                    float2 *hY = histY + (size_t)p * kMM * kMaxGboBatch;
+                    // history and Gram matrix, every load in flight (a slot that
+                    // holds no pair is read and dropped; the second circles'
+                    // only where the batch has them)
+                    float2 S[kGCPB][kMM] = {}, Y[kGCPB][kMM] = {};
+                    float gv[kGramTurns];
+                    {
+                        const float2 *hS = histS + (size_t)p * kMM * kMaxGboBatch;
+                        const float2 *hY = histY + (size_t)p * kMM * kMaxGboBatch;
+                        const float *gp = gram + (size_t)p * kNB * kNB;
+#pragma unroll
+                        for (int t = 0; t < kGramTurns; ++t) gv[t] = gp[gram_entry(t)];
+#pragma unroll
+                        for (int c = 0; c < kGCPB; ++c) {
+                            if (c * kWave >= np) break;
+#pragma unroll
+                            for (int j = 0; j < kMM; ++j) {
+                                // logical j (newest at kMM-1) is ring slot head - (kMM-1-j)
+                                const int sl = head - (kMM - 1 - j) + (head < kMM - 1 - j ? kMM : 0);
+                                S[c][j] = hS[(size_t)sl * kMaxGboBatch + lane + c * kWave];
+                                Y[c][j] = hY[(size_t)sl * kMaxGboBatch + lane + c * kWave];
+                            }
+                        }
+                    }
 #pragma unroll
                     for (int c = 0; c < kGCPB; ++c) {
                         const int q = lane + c * kWave;
                         act[c] = q < np;
                         ci[c] = act[c] ? sh.members[m0 + q] : 0;
-                        x[c] = act[c] ? sh.pos[ci[c]] : make_float2(0.f, 0.f);
+                        x[c] = act[c] ? sh.xy[ci[c]] : make_float2(0.f, 0.f);
                         g[c] = make_float2(0.f, 0.f);
                         pd[c] = make_float2(0.f, 0.f);
+                    }
+#pragma unroll
+                    for (int c = 0; c < kGCPB; ++c)
 #pragma unroll
                         for (int j = 0; j < kMM; ++j) {
-                            // logical j (newest at kMM-1) is ring slot head - (kMM-1-j)
-                            const int sl = (st.head - (kMM - 1 - j) + 2 * kMM) % kMM;
                             const bool valid = act[c] && j >= kMM - k;
-                            S[c][j] = valid ? hS[(size_t)sl * kMaxGboBatch + q] : make_float2(0.f, 0.f);
-                            Y[c][j] = valid ? hY[(size_t)sl * kMaxGboBatch + q] : make_float2(0.f, 0.f);
+                            S[c][j] = valid ? S[c][j] : make_float2(0.f, 0.f);
+                            Y[c][j] = valid ? Y[c][j] : make_float2(0.f, 0.f);
                         }
-                    }
-                    float *Bwc[2] = {sh.Bw[wv][0], sh.Bw[wv][1]};
-                    int cur = 0;
-                    const float *gp_src = gram + (size_t)p * kNB * kNB;
-                    for (int e = lane; e < kNB * kNB; e += kWave) Bwc[0][e] = gp_src[e];
+                    float *const W = sh.wave[wv];
+                    int cur = 0;            // offset of the current Gram matrix
+#pragma unroll
+                    for (int t = 0; t < kGramTurns; ++t) W[gram_entry(t)] = gv[t];
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -406,23 +503,21 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                                         bool far) -> float {
 #pragma unroll
                         for (int c = 0; c < kGCPB; ++c)
-                            if (act[c]) sh.tpos[ci[c]] = xt[c];
+                            if (act[c]) sh.xy[kMaxN + ci[c]] = xt[c];
                         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                         __builtin_amdgcn_wave_barrier();
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        float e = 0.f, e1 = 0.f;
+                        float e = 0.f, e1_unused = 0.f;
                         double ed = 0.0;
                         int pe = 0;
 #pragma unroll
                         for (int c = 0; c < kGCPB; ++c) {
                             float gx = 0.f, gy = 0.f;
                             double gxd = 0.0, gyd = 0.0;
-                            if (act[c]) {
+                            {
                                 const int i = ci[c];
                                 const float2 q = xt[c];
-                                auto term_in = [&](int j, bool inb) {
-                                    const float2 pj = inb ? sh.tpos[j] : sh.pos[j];
-                                    const bool ce = inb ? j < i : true;    // Eq. 7
+                                auto term_at = [&](float2 pj, bool ce) {
                                     pe += ce;
                                     if (F64) {
                                         const double dx = (double)q.x - (double)pj.x;
@@ -439,30 +534,51 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                                             }
                                         }
                                     } else {
-                                        pair_term32(q, pj, ce, two_r, four_r2, e, e1, gx, gy);
+                                        pair_term32(q, pj, ce, two_r, four_r2, e, e1_unused, gx, gy);
                                     }
                                 };
-                                auto term = [&](int j) { term_in(j, sh.batch_of[j] == p); };
-                                if (far) {
-                                    // a circle of the batch left the skin: the other
-                                    // circles from the cell grid, the batch's own from
-                                    // its member list
+                                auto term = [&](int j) {
+                                    const bool inb = sh.batch_of[j] == p;
+                                    term_at(sh.xy[j + (inb ? kMaxN : 0)], inb ? j < i : true);   // Eq. 7
+                                };
+                                if (c * kWave < np && !far && !overflow) {
+                                    // the wave's longest list, eight neighbors in
+                                    // flight; past a list's end a place that adds
+                                    // zeros
+                                    const int mc = act[c] ? sh.list_n[i] : 0;
+                                    const int mmax = wave_max_dpp(mc);
+                                    constexpr int kTurn = 8;
+                                    for (int t0 = 0; t0 < mmax; t0 += kTurn) {
+                                        int o[kTurn];
+                                        float2 pj[kTurn];
+#pragma unroll
+                                        for (int t = 0; t < kTurn; ++t) o[t] = sh.list[t0 + t][i];
+#pragma unroll
+                                        for (int t = 0; t < kTurn; ++t) {
+                                            o[t] = t0 + t < mc ? o[t] : kNowhere;
+                                            pj[t] = at_offset(sh, o[t]);
+                                        }
+#pragma unroll
+                                        for (int t = 0; t < kTurn; ++t)      // Eq. 7: a pair of the batch once
+                                            term_at(pj[t], o[t] < kInBatch + i * (int)sizeof(float2));
+                                    }
+                                }
+                                if (act[c] && (far || overflow)) {
+                                    // lists that do not fit: all circles from the cell
+                                    // grid.  A circle of the batch that left the skin:
+                                    // the other circles from the cell grid, the batch's
+                                    // own from its member list
                                     for_each_candidate(i, q, grid, sh.cell_start, sh.cell_circ, [&](int j) {
-                                        if (sh.batch_of[j] != p) term(j);
+                                        if (!far || sh.batch_of[j] != p) term(j);
                                     });
-                                    for (int t = 0; t < np; ++t) {
+                                    for (int t = 0; t < (far ? np : 0); ++t) {
                                         const int j = sh.members[m0 + t];
                                         if (j != i) term(j);
                                     }
-                                } else if (!overflow) {
-                                    const int mc = sh.list_n[i];
-                                    for (int t = 0; t < mc; ++t) {
-                                        const int en = sh.list[t][i];
-                                        term_in(en & 0x7fff, (en & 0x8000) != 0);
-                                    }
-                                } else {
-                                    for_each_candidate(i, q, grid, sh.cell_start, sh.cell_circ, term);
                                 }
+                            }
+                            if (act[c]) {
+                                const float2 q = xt[c];
                                 if (F64) {
                                     const double r64 = sqrt((double)q.x * q.x + (double)q.y * q.y);
                                     const double d0 = r64 + (double)rad - R64;
@@ -493,102 +609,115 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                             yc[c] = make_float2(gx - g[c].x, gy - g[c].y);
                         }
                         if (F64) e = (float)ed;
-                        e64 = wave_sum(ed);
+                        e64 = F64 ? wave_sum(ed) : 0.0;
                         ++evals;
                         cell_mine += (far || overflow) ? 1 : 0;
                         pair_mine += pe;
-                        return wave_reduce_scatter<true>(gt, sc, yc, S, Y, e, e1);
+                        return wave_reduce_scatter<false>(gt, sc, yc, S, Y, e, 0.f);
                     };
 
-                    // ---- gradient at the start of the visit (Alg. 1) -----
-                    float2 gt[kGCPB], yc[kGCPB], sc0[kGCPB];
-#pragma unroll
-                    for (int c = 0; c < kGCPB; ++c) sc0[c] = make_float2(0.f, 0.f);
-                    double e64 = 0.0;
-                    // (every circle starts a colour within skin / 2 of its list
-                    // position, so the visit's first point is in range of the lists)
-                    float tot = evaluate(x, sc0, gt, yc, e64, false);
-                    // slot totals are lane-indexed by lane_slot(); stage them
-                    sh.totw[wv][lane_slot(lane)] = tot;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                     auto gram_update = [&](bool push) {
-                        for (int e = lane; e < kNB * kNB; e += kWave) {
-                            const int src = sh.bsrc[push ? 1 : 0][e];
-                            Bwc[cur ^ 1][e] = (src & 0x8000) ? sh.totw[wv][src & 0x7fff] : Bwc[cur][src];
+                        int src[kGramTurns];
+                        float v[kGramTurns];
+#pragma unroll
+                        for (int t = 0; t < kGramTurns; ++t) src[t] = sh.bsrc[push ? 1 : 0][gram_entry(t)];
+#pragma unroll
+                        for (int t = 0; t < kGramTurns; ++t) {
+                            v[t] = W[(src[t] & 0x8000) ? kTot + (src[t] & 0x7fff) : cur + src[t]];
                         }
-                        cur ^= 1;
+#pragma unroll
+                        for (int t = 0; t < kGramTurns; ++t) W[kNB * kNB - cur + gram_entry(t)] = v[t];
+                        cur = kNB * kNB - cur;
                         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                         __builtin_amdgcn_wave_barrier();
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                     };
-                    gram_update(false);
-                    Ep = sh.totw[wv][sE];
-                    Ep64 = e64;
-#pragma unroll
-                    for (int c = 0; c < kGCPB; ++c) g[c] = gt[c];
-                    const float gg = Bwc[cur][kG * kNB + kG];
-                    const float gn = sqrtf(fmaxf(gg, 0.f));
-                    gsum += gn;
-
-                    // ---- direction: two-loop on the batch's Gram matrix -----------
-                    float Bc[kNB];
-#pragma unroll
-                    for (int a2 = 0; a2 < kNB; ++a2) Bc[a2] = lane < kNB ? Bwc[cur][a2 * kNB + lane] : 0.f;
-                    // two-loop on the Gram matrix: lane l keeps (B q)_l, the Gram
-                    // product of the current q with basis vector l (q = g at the
-                    // start), so each step is one readlane and one FMA
-                    const int jp = lane < kMM ? lane : lane - kMM;
-                    const bool live = lane < 2 * kMM && jp >= kMM - k;
-                    float rho_v = 0.f;              // 1 / s_j'y_j at lanes j and kMM + j
-                    if (live) rho_v = 1.f / Bwc[cur][(lane < kMM ? kMM + lane : lane - kMM) * kNB + lane];
-                    float acc = Bc[kG];
-                    float alph_v = 0.f;             // a_j at lanes j and kMM + j
-#pragma unroll
-                    for (int j = kMM - 1; j >= 0; --j) {
-                        const float a = lane_value(rho_v * acc, j);           // rho_j s_j'q
-                        if (jp == j) alph_v = a;
-                        acc -= a * Bc[kMM + j];
-                    }
-                    float gam = 1.f;
-                    if (k > 0) gam = lane_value(Bc[kMM - 1], 2 * kMM - 1) / lane_value(Bc[2 * kMM - 1], 2 * kMM - 1);
-                    acc *= gam;
-                    float cs_v = 0.f;               // coefficient of s_j at lane j
-#pragma unroll
-                    for (int j = 0; j < kMM; ++j) {
-                        const float c = lane_value(alph_v - rho_v * acc, kMM + j);   // a_j - rho_j y_j'r
-                        if (lane == j) cs_v = c;
-                        acc += c * Bc[j];
-                    }
-                    float gp = -lane_value(acc, kG);                               // g'p = -g'r
-                    {
-                        float cs[kMM], cy[kMM];
-#pragma unroll
-                        for (int j = 0; j < kMM; ++j) { cs[j] = lane_value(cs_v, j); cy[j] = -gam * lane_value(alph_v, j); }
-#pragma unroll
-                        for (int c = 0; c < kGCPB; ++c) {
-                            float px = -gam * g[c].x, py = -gam * g[c].y;
-#pragma unroll
-                            for (int j = 0; j < kMM; ++j) {
-                                px -= cs[j] * S[c][j].x + cy[j] * Y[c][j].x;
-                                py -= cs[j] * S[c][j].y + cy[j] * Y[c][j].y;
-                            }
-                            pd[c] = make_float2(px, py);
-                        }
-                    }
-                    if (k > 0 && !(gp < 0.f)) {
-                        k = 0;
-#pragma unroll
-                        for (int c = 0; c < kGCPB; ++c) pd[c] = make_float2(-g[c].x, -g[c].y);
-                        gp = -gg;
-                    }
-                    float alpha = k > 0 ? 1.f : 1.f / fmaxf(1.f, gn);
-
-                    // ---- backtracking line search on E(x_p) ----------------------
+                    // ---- the gradient at the start of the visit (Alg. 1), then the
+                    // backtracking line search on E(x_p), over one copy of the
+                    // evaluation ----------------------------------------------------
                     bool accepted = false, push = false;
-                    float2 xt[kGCPB], sc[kGCPB];
-                    for (int h = 0; h <= A.max_halvings; ++h) {
+                    float2 xt[kGCPB], sc[kGCPB], gt[kGCPB], yc[kGCPB];
+                    double e64 = 0.0;
+                    float gp = 0.f, alpha = 0.f;
+#pragma unroll
+                    for (int c = 0; c < kGCPB; ++c) { xt[c] = x[c]; sc[c] = make_float2(0.f, 0.f); }
+                    // (every circle starts a colour within skin / 2 of its list
+                    // position, so the visit's first point is in range of the lists)
+                    bool far = false;
+                    for (int h = -1;;) {
+                        const float tot = evaluate(xt, sc, gt, yc, e64, far);
+                        // slot totals are lane-indexed by lane_slot(); stage them
+                        W[kTot + lane_slot(lane)] = tot;
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                        if (h >= 0) {
+                            const float Et = W[kTot + sE];
+                            const bool ok = F64 ? e64 <= Ep64 + (double)A.c1 * (double)alpha * (double)gp
+                                                : Et <= Ep + A.c1 * alpha * gp;
+                            if (ok) {
+                                accepted = true;
+                                push = W[kTot + sScYc] > A.eps_curv * W[kTot + sYcYc];
+                            }
+                        }
+                        if (h < 0 || accepted) gram_update(push);
+                        if (accepted) break;
+                        if (h < 0) {
+                            Ep = W[kTot + sE];
+                            Ep64 = e64;
+#pragma unroll
+                            for (int c = 0; c < kGCPB; ++c) g[c] = gt[c];
+                            const float gg = W[cur + kG * kNB + kG];
+                            const float gn = sqrtf(fmaxf(gg, 0.f));
+                            gsum += gn;
+
+                            // ---- direction: two-loop on the batch's Gram matrix -----------
+                            float Bc[kNB];
+#pragma unroll
+                            for (int a2 = 0; a2 < kNB; ++a2) Bc[a2] = W[cur + a2 * kNB + min(lane, kNB - 1)];
+#pragma unroll
+                            for (int a2 = 0; a2 < kNB; ++a2) Bc[a2] = lane < kNB ? Bc[a2] : 0.f;
+                            // two-loop on the Gram matrix: lane l keeps (B q)_l, the Gram
+                            // product of the current q with basis vector l (q = g at the
+                            // start), so each step is one readlane and one FMA
+                            const int jp = lane < kMM ? lane : lane - kMM;
+                            const bool live = lane < 2 * kMM && jp >= kMM - k;
+                            float rho_v = 0.f;              // 1 / s_j'y_j at lanes j and kMM + j
+                            if (live) rho_v = 1.f / W[cur + (lane < kMM ? kMM + lane : lane - kMM) * kNB + lane];
+                            float acc = Bc[kG];
+                            float cf = 0.f;                 // a_j at lane kMM + j, coefficient of s_j at lane j
+                            two_loop_down(Bc + kMM, rho_v, acc, cf);               // a_j = rho_j s_j'q
+                            float gam = 1.f;
+                            if (k > 0) gam = lane_value(Bc[kMM - 1], 2 * kMM - 1) / lane_value(Bc[2 * kMM - 1], 2 * kMM - 1);
+                            acc *= gam;
+                            two_loop_up(Bc, rho_v, acc, cf);                       // a_j - rho_j y_j'r
+                            gp = -lane_value(acc, kG);                               // g'p = -g'r
+                            {
+                                float cs[kMM], cy[kMM];
+#pragma unroll
+                                for (int j = 0; j < kMM; ++j) { cs[j] = lane_value(cf, j); cy[j] = -gam * lane_value(cf, kMM + j); }
+#pragma unroll
+                                for (int c = 0; c < kGCPB; ++c) {
+                                    float px = -gam * g[c].x, py = -gam * g[c].y;
+#pragma unroll
+                                    for (int j = 0; j < kMM; ++j) {
+                                        px -= cs[j] * S[c][j].x + cy[j] * Y[c][j].x;
+                                        py -= cs[j] * S[c][j].y + cy[j] * Y[c][j].y;
+                                    }
+                                    pd[c] = make_float2(px, py);
+                                }
+                            }
+                            if (k > 0 && !(gp < 0.f)) {
+                                k = 0;
+#pragma unroll
+                                for (int c = 0; c < kGCPB; ++c) pd[c] = make_float2(-g[c].x, -g[c].y);
+                                gp = -gg;
+                            }
+                            alpha = k > 0 ? 1.f : 1.f / fmaxf(1.f, gn);
+                        } else {
+                            alpha *= 0.5f;
+                        }
+                        if (++h > A.max_halvings) break;
                         bool out = false;
 #pragma unroll
                         for (int c = 0; c < kGCPB; ++c) {
@@ -600,35 +729,20 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                                 out |= dx * dx + dy * dy > A.skin2;
                             }
                         }
-                        const bool far = __builtin_amdgcn_ballot_w64(out) != 0;
-                        tot = evaluate(xt, sc, gt, yc, e64, far);
-                        sh.totw[wv][lane_slot(lane)] = tot;
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                        const float Et = sh.totw[wv][sE];
-                        const bool ok = F64 ? e64 <= Ep64 + (double)A.c1 * (double)alpha * (double)gp
-                                            : Et <= Ep + A.c1 * alpha * gp;
-                        if (ok) {
-                            accepted = true;
-                            push = sh.totw[wv][sScYc] > A.eps_curv * sh.totw[wv][sYcYc];
-                            break;
-                        }
-                        alpha *= 0.5f;
+                        far = __builtin_amdgcn_ballot_w64(out) != 0;
                     }
                     if (accepted) {
-                        gram_update(push);
                         if (push) {
-                            const int sl = (st.head + 1) % kMM;
+                            const int sl = (head + 1) % kMM;
 #pragma unroll
                             for (int c = 0; c < kGCPB; ++c) {
                                 const int q = lane + c * kWave;
                                 if (act[c]) {
-                                    hS[(size_t)sl * kMaxGboBatch + q] = sc[c];
-                                    hY[(size_t)sl * kMaxGboBatch + q] = yc[c];
+                                    histS[((size_t)p * kMM + sl) * kMaxGboBatch + q] = sc[c];
+                                    histY[((size_t)p * kMM + sl) * kMaxGboBatch + q] = yc[c];
                                 }
                             }
-                            st.head = sl;
+                            head = sl;
                             k = k + 1 > A.m ? A.m : k + 1;
                         }
 #pragma unroll
@@ -637,121 +751,35 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                     }
                     // ---- persist the batch's Gram matrix and ring ----------------
                     float *gdst = gram + (size_t)p * kNB * kNB;
-                    for (int e = lane; e < kNB * kNB; e += kWave) gdst[e] = Bwc[cur][e];
-                    if (lane == 0) { st.k = k; bst[p] = st; }
+#pragma unroll
+                    for (int t = 0; t < kGramTurns; ++t) gdst[gram_entry(t)] = W[cur + gram_entry(t)];
+                    if (lane == 0) { sh.bk[p] = k; sh.bhead[p] = head; }
                 }
                 // ---- end of the colour: commit, maybe rebuild --------------------
                 __syncthreads();
                 int moved = 0;
-                for (int i = tid; i < n; i += kGT) {
-                    const float2 q = sh.npos[i];
-                    sh.pos[i] = q;
-                    const double dx = (double)q.x - (double)sh.xref[i].x, dy = (double)q.y - (double)sh.xref[i].y;
-                    moved |= dx * dx + dy * dy > 0.25 * A.skin2;
+                {
+                    float2 q[kGU], rf[kGU];
+#pragma unroll
+                    for (int u = 0; u < kGU; ++u) {
+                        q[u] = sh.npos[tid + u * kGT];
+                        rf[u] = sh.xref[tid + u * kGT];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kGU; ++u) {
+                        if (tid + u * kGT >= n) continue;
+                        sh.xy[tid + u * kGT] = q[u];
+                        const double dx = (double)q[u].x - (double)rf[u].x, dy = (double)q[u].y - (double)rf[u].y;
+                        moved |= dx * dx + dy * dy > 0.25 * A.skin2;
+                    }
                 }
                 if (moved) sh.flag = 1;
                 __syncthreads();
-                if (sh.flag && colour < 3) {
-                    // rebuild between colours (the outer loop rebuilds after colour 3)
-                    bin_circles<kGT>(sh.pos, n, grid, sh.cell_start, sh.cell_circ, sh.slot_tmp,
-                                     sh.scan_tmp);
-                    for (int cc = tid; cc < grid.nc * grid.nc; cc += kGT) {
-                        const int a = sh.cell_start[cc], z = sh.cell_start[cc + 1];
-                        for (int q = a + 1; q < z; ++q) {
-                            const uint16_t key = sh.cell_circ[q];
-                            int t = q - 1;
-                            while (t >= a && sh.cell_circ[t] > key) { sh.cell_circ[t + 1] = sh.cell_circ[t]; --t; }
-                            sh.cell_circ[t + 1] = key;
-                        }
-                    }
-                    if (tid == 0) sh.over = 0;
-                    __syncthreads();
-                    for (int i0 = 0; i0 < n; i0 += kGT) {
-                        const int i = i0 + tid;
-                        const bool act = i < n;
-                        const float2 q = sh.pos[act ? i : 0];
-                        const int bi = sh.batch_of[act ? i : 0];
-                        // candidates: the circles of the 3 x 3 cells around q's, in cell
-                        // order; three cell rows (start, length), read together, one run
-                        int ra[3], rl[3];
-                        {
-                            const int cx = cell_coord(q.x, grid), cy = cell_coord(q.y, grid);
-                            const int y0 = cy > 0 ? cy - 1 : 0, y1 = cy < grid.nc - 1 ? cy + 1 : grid.nc - 1;
-                            const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < grid.nc - 1 ? cx + 1 : grid.nc - 1;
-#pragma unroll
-                            for (int r = 0; r < 3; ++r) {
-                                const bool row = act && y0 + r <= y1;
-                                const int yy = y0 + r <= y1 ? y0 + r : y0;
-                                const int a = sh.cell_start[yy * grid.nc + x0];
-                                const int z = sh.cell_start[yy * grid.nc + x1 + 1];
-                                ra[r] = row ? a : 0;
-                                rl[r] = row ? z - a : 0;
-                            }
-                        }
-                        const int K = rl[0] + rl[1] + rl[2];
-                        // the wave walks its longest run, four candidates per step with their
-                        // reads in flight; FP32 test outside the +-1e-5 band around the
-                        // cutoff, FP64 inside, behind one uniform branch
-                        const int kmax = wave_max_dpp(K);
-                        int m = 0;
-                        for (int k0 = 0; k0 < kmax; k0 += 4) {
-                            int jv[4];
-                            bool ok[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                const int k = k0 + u;
-                                ok[u] = k < K;
-                                const int t = k < rl[0]         ? ra[0] + k
-                                            : k < rl[0] + rl[1] ? ra[1] + (k - rl[0])
-                                                                : ra[2] + (k - rl[0] - rl[1]);
-                                const int jj = sh.cell_circ[ok[u] ? t : 0];
-                                jv[u] = ok[u] ? jj : 0;
-                            }
-                            float2 pv[4];
-                            int bj[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                pv[u] = sh.pos[jv[u]];
-                                bj[u] = sh.batch_of[jv[u]];
-                            }
-                            bool nb[4], band[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                const float dx = q.x - pv[u].x, dy = q.y - pv[u].y;
-                                const float l2 = dx * dx + dy * dy;
-                                const bool cand = ok[u] && jv[u] != i;
-                                nb[u] = cand && l2 < c2lo;
-                                band[u] = cand && l2 >= c2lo && l2 <= c2hi;
-                            }
-                            if (__builtin_amdgcn_ballot_w64(band[0] || band[1] || band[2] || band[3])) {
-#pragma unroll
-                                for (int u = 0; u < 4; ++u)
-                                    if (band[u]) nb[u] = near64(q, pv[u], A.c2);
-                            }
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {
-                                if (nb[u] && m < kGEll) sh.list[m][i] = (uint16_t)(jv[u] | (bj[u] == bi ? 0x8000 : 0));
-                                m += nb[u] ? 1 : 0;
-                            }
-                        }
-                        if (act) {
-                            if (m > kGEll) sh.over = 1;
-                            sh.list_n[i] = (uint8_t)(m < kGEll ? m : kGEll);
-                            sh.xref[i] = q;
-                        }
-                    }
-                    ++rebuilds;
-                    if (tid == 0) sh.flag = 0;
-                    __syncthreads();
-                    overflow = sh.over != 0;
-                }
             }
-            // waves' visit-gradient norms, summed in the energy block above
-            ++outer;
         }
 
         // ---- write back ----------------------------------------------------------
-        for (int i = tid; i < n; i += kGT) reinterpret_cast<float2 *>(xy)[off + i] = sh.pos[i];
+        for (int i = tid; i < n; i += kGT) reinterpret_cast<float2 *>(xy)[off + i] = sh.xy[i];
         {
             unsigned long long pm = (unsigned long long)pair_mine;
 #pragma unroll

@@ -9,6 +9,9 @@
 
 namespace pecc {
 
+// A place beyond everything: a pair term with it is zero.
+constexpr float kFarCoord = 3.0e18f;      // (3e18)^2 * 2 is finite in FP32
+
 constexpr int kMM = 10;                   // history slots (max m)
 constexpr int kNB = 2 * kMM + 1;          // basis size: s_0..s_9, y_0..y_9, g
 constexpr int kG = 2 * kMM;               // basis index of g
