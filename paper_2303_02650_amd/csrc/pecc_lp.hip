@@ -563,10 +563,11 @@ __device__ __forceinline__ float sum16(float v)   // over the 16 lanes of a grou
 // the weights' loads are in flight together, their transposed copy and the
 // staged tiles are laid out without bank conflicts, and the waves' sums meet
 // in LDS in one step instead of a read-modify-write chain of 130 values per
-// lane and wave.  8192 rows: 16 us (32 us before); with the update in the
-// reduction (5 us) a training step takes 19 us, 51 us before.
+// lane and wave.  8192 rows: 12.7 us (32 us before); with the update in the
+// reduction (4 us) a training step takes 15 us, 51 us before.
 // Per workgroup: partial d(sum of row losses)/d params (not yet divided by
 // rows) and the partial loss sum, written to part[blockIdx.x][0..kParams].
+template <int TILES>
 __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__restrict__ P,
                                                              const float *__restrict__ X,
                                                              const float *__restrict__ Y,
@@ -580,7 +581,13 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
     const int wv = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
     WaveStage &st = S.u.stage[wv];
-    for (int k = lane; k < 16 * kStageRow; k += 64) (&st.x[0][0])[k] = (__bf16)0.0f;
+    if constexpr (TILES == 1) {
+        // the second 16 rows of the contractions stay zero
+        for (int k = lane; k < (int)(sizeof(WaveStage) / 16); k += 64)
+            reinterpret_cast<u32x4 *>(&st)[k] = u32x4{0, 0, 0, 0};
+    } else {
+        for (int k = lane; k < 16 * kStageRow; k += 64) (&st.x[0][0])[k] = (__bf16)0.0f;
+    }
     __syncthreads();
 
     f32x4 gW2[4][4], gW1[4];
@@ -594,11 +601,11 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
     float gB3 = 0.0f, lsum = 0.0f;
 
     const int64_t waves = (int64_t)gridDim.x * (kMlpBlock / 64);
-    const int64_t pairs = (rows + 31) / 32;
+    const int64_t pairs = (rows + 16 * TILES - 1) / (16 * TILES);
     for (int64_t pt = (int64_t)blockIdx.x * (kMlpBlock / 64) + wv; pt < pairs; pt += waves) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int64_t row = pt * 32 + 16 * s + r;
+        for (int s = 0; s < TILES; ++s) {
+            const int64_t row = (pt * TILES + s) * 16 + r;
             const bool valid = row < rows;
             const bf16x8 xb = frag_x(X, row, rows, g);
             float a1[4][4], a2[4][4], h2[4][4];
@@ -711,25 +718,33 @@ __global__ __launch_bounds__(kMlpBlock) void mlp_grad_kernel(const float *__rest
 // ---------------------------------------------------------------------------
 // Adam
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void adam_update(float *__restrict__ p, float *__restrict__ m,
-                                            float *__restrict__ v, float gk, int t, const AdamArgs &a,
-                                            int k)
+// 1 - beta^t of both moments
+__device__ __forceinline__ float2 adam_bias(const AdamArgs &a, int t)
 {
-    const float c1 = (float)(1.0 - pow((double)a.b1, (double)t));
-    const float c2 = (float)(1.0 - pow((double)a.b2, (double)t));
-    const float mk = a.b1 * m[k] + (1.0f - a.b1) * gk;
-    const float vk = a.b2 * v[k] + (1.0f - a.b2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    p[k] -= a.lr * (mk / c1) / (sqrtf(vk / c2) + a.eps);
+    return make_float2((float)(1.0 - pow((double)a.b1, (double)t)),
+                       (float)(1.0 - pow((double)a.b2, (double)t)));
 }
 
-// grad[k] = (sum over workgroups, in workgroup order) / rows; loss likewise.
-// ADAM: and the update of parameter k, with the count in *step.  A thread's
-// sum is a serial chain of additions; its loads are not: 16 in flight (one at
-// a time the sum of 64 parts takes 16 us).  Workgroups of one wave, to spread
-// over the CUs.
-constexpr int kReduceBlock = 64;
+// pk, m0, v0: the parameter and its moments before the step
+__device__ __forceinline__ void adam_update(float *__restrict__ p, float *__restrict__ m,
+                                            float *__restrict__ v, float pk, float m0, float v0,
+                                            float gk, float2 bias, const AdamArgs &a, int k)
+{
+    const float mk = a.b1 * m0 + (1.0f - a.b1) * gk;
+    const float vk = a.b2 * v0 + (1.0f - a.b2) * gk * gk;
+    m[k] = mk;
+    v[k] = vk;
+    p[k] = pk - a.lr * (mk / bias.x) / (sqrtf(vk / bias.y) + a.eps);
+}
+
+// grad[k] = (sum over workgroups) / rows; loss likewise.  ADAM: and the update
+// of parameter k, with the count in *step.  Four waves take a quarter of the
+// parts of 64 entries each, in order, 16 loads in flight, and the quarters are
+// added in order (one thread per entry and one load at a time: 16 us for 64
+// parts; 4 us for 128 in this form); a fifth computes the moments' factors
+// meanwhile.
+constexpr int kReduceSplit = 4;
+constexpr int kReduceBlock = (kReduceSplit + 1) * kWave;
 
 template <bool ADAM>
 __global__ __launch_bounds__(kReduceBlock) void grad_reduce_kernel(
@@ -737,22 +752,37 @@ __global__ __launch_bounds__(kReduceBlock) void grad_reduce_kernel(
     float *__restrict__ loss, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
     const int32_t *__restrict__ step, AdamArgs a)
 {
-    const int k = blockIdx.x * kReduceBlock + threadIdx.x;
-    if (k > kParams) return;
-    constexpr int kFly = 16;
-    float s = 0.0f;
-    for (int w = 0; w < nparts; w += kFly) {
-        float x[kFly];
+    __shared__ float quarter[kReduceSplit][kWave];
+    __shared__ float2 bias;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int k = blockIdx.x * kWave + lane, kc = min(k, kParams);
+    float pk = 0.f, m0 = 0.f, v0 = 0.f;
+    if (w < kReduceSplit) {
+        if (ADAM && w == 0 && k < kParams) { pk = p[k]; m0 = m[k]; v0 = v[k]; }
+        const int w0 = nparts * w / kReduceSplit, w1 = nparts * (w + 1) / kReduceSplit;
+        constexpr int kFly = 16;
+        float s = 0.0f;
+        for (int q0 = w0; q0 < w1; q0 += kFly) {
+            float x[kFly];
 #pragma unroll
-        for (int q = 0; q < kFly; ++q) x[q] = part[(int64_t)min(w + q, nparts - 1) * (kParams + 1) + k];
+            for (int q = 0; q < kFly; ++q) x[q] = part[(int64_t)min(q0 + q, w1 - 1) * (kParams + 1) + kc];
 #pragma unroll
-        for (int q = 0; q < kFly; ++q)
-            if (w + q < nparts) s += x[q];
+            for (int q = 0; q < kFly; ++q)
+                if (q0 + q < w1) s += x[q];
+        }
+        quarter[w][lane] = s;
+    } else if (ADAM && lane == 0) {
+        bias = adam_bias(a, *step);
     }
+    __syncthreads();
+    if (w > 0 || k > kParams) return;
+    float s = quarter[0][lane];
+#pragma unroll
+    for (int q = 1; q < kReduceSplit; ++q) s += quarter[q][lane];
     const float mean = rows > 0 ? s / (float)rows : 0.0f;
     if (k < kParams) {
         grad[k] = mean;
-        if constexpr (ADAM) adam_update(p, m, v, mean, *step, a, k);
+        if constexpr (ADAM) adam_update(p, m, v, pk, m0, v0, mean, bias, a, k);
     } else if (loss) {
         *loss = mean;
     }
@@ -766,7 +796,7 @@ __global__ void adam_kernel(float *__restrict__ p, float *__restrict__ m, float 
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= count) return;
-    adam_update(p, m, v, g[k], *step + 1, a, k);
+    adam_update(p, m, v, p[k], m[k], v[k], g[k], adam_bias(a, *step + 1), a, k);
 }
 
 __global__ void step_bump_kernel(int32_t *step) { *step += 1; }
@@ -873,10 +903,27 @@ __global__ __launch_bounds__(kAcceptBlock) void accept_kernel(
     }
 }
 
-int mlp_grid(int64_t rows, int per_wg_rows)
+// 16-row tiles of a wave's turn in the gradient: one while that leaves no more
+// workgroups than CUs (a minibatch is a single turn, and half the turn's
+// chain), two beyond, where the contractions over rows then fill their 32
+// places.  8192 rows: 12.7 us with one, 16 us with two.
+int mlp_tiles(int64_t rows) { return rows <= 256 * 4 * 16 ? 1 : 2; }
+
+int mlp_grid(int64_t rows)
 {
+    const int per_wg_rows = (kMlpBlock / 64) * 16 * mlp_tiles(rows);
     const int64_t need = (rows + per_wg_rows - 1) / per_wg_rows;
     return (int)(need < 1 ? 1 : (need > 256 ? 256 : need));
+}
+
+void run_mlp_grad(const float *params, const float *X, const float *Y, int64_t rows, float *part,
+                  int32_t *step, hipStream_t s)
+{
+    const int grid = mlp_grid(rows);
+    if (mlp_tiles(rows) == 1)
+        mlp_grad_kernel<1><<<grid, kMlpBlock, 0, s>>>(params, X, Y, rows, part, step);
+    else
+        mlp_grad_kernel<2><<<grid, kMlpBlock, 0, s>>>(params, X, Y, rows, part, step);
 }
 
 }  // namespace
@@ -909,18 +956,21 @@ hipError_t launch_mlp_forward(const float *params, const float *X, int64_t rows,
 
 size_t mlp_grad_workspace_bytes(int64_t rows)
 {
-    return (size_t)mlp_grid(rows, 4 * 32) * (kParams + 1) * sizeof(float);
+    // enough for every smaller row count too: the most workgroups once they
+    // take two tiles
+    const int parts = mlp_tiles(rows) == 1 ? mlp_grid(rows) : 256;
+    return (size_t)parts * (kParams + 1) * sizeof(float);
 }
 
 hipError_t launch_mlp_grad(const float *params, const float *X, const float *Y, int64_t rows,
                            float *loss, float *grad, void *ws, hipStream_t s)
 {
-    const int grid = mlp_grid(rows, 4 * 32);
+    const int grid = mlp_grid(rows);
     float *part = static_cast<float *>(ws);
-    mlp_grad_kernel<<<grid, kMlpBlock, 0, s>>>(params, X, Y, rows, part, nullptr);
+    run_mlp_grad(params, X, Y, rows, part, nullptr, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    grad_reduce_kernel<false><<<(kParams + kReduceBlock) / kReduceBlock, kReduceBlock, 0, s>>>(
+    grad_reduce_kernel<false><<<kParams / kWave + 1, kReduceBlock, 0, s>>>(
         part, grid, rows, grad, loss, nullptr, nullptr, nullptr, nullptr, AdamArgs{});
     return hipGetLastError();
 }
@@ -929,12 +979,12 @@ hipError_t launch_train_step(float *params, float *m, float *v, int32_t *step, c
                              const float *X, const float *Y, int64_t rows, float *loss, float *grad,
                              void *ws, hipStream_t s)
 {
-    const int grid = mlp_grid(rows, 4 * 32);
+    const int grid = mlp_grid(rows);
     float *part = static_cast<float *>(ws);
-    mlp_grad_kernel<<<grid, kMlpBlock, 0, s>>>(params, X, Y, rows, part, step);
+    run_mlp_grad(params, X, Y, rows, part, step, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    grad_reduce_kernel<true><<<(kParams + kReduceBlock) / kReduceBlock, kReduceBlock, 0, s>>>(
+    grad_reduce_kernel<true><<<kParams / kWave + 1, kReduceBlock, 0, s>>>(
         part, grid, rows, grad, loss, params, m, v, step, a);
     return hipGetLastError();
 }

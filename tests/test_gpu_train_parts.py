@@ -42,3 +42,16 @@ def test_gradient_and_step(rows):
         assert la == lb.item() and torch.equal(A.grad, gb)
         assert A.step.item() == t + 1 == B.step.item()
         assert torch.equal(A.params, B.params) and torch.equal(A.m, B.m) and torch.equal(A.v, B.v)
+
+
+def test_workspace_holds_every_smaller_row_count():
+    import paper_2303_02650_amd as P
+
+    sizes = [P.pecc_mlp_grad_workspace_size(r) for r in (0, 1, 64, 65, 16384, 16385, 32768, 10**7)]
+    assert sizes == sorted(sizes)
+    p, x, y = data(16384)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    T = P.MlpTrainer(dev(p), lr=1e-3, max_rows=16400)
+    loss = T.train_step(dev(x), dev(y)).item()
+    L, _ = oracle.mlp_grad(p.astype(np.float64), x.astype(np.float64), y.astype(np.float64))
+    assert loss == pytest.approx(L, rel=1e-3)
