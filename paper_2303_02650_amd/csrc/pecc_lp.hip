@@ -151,7 +151,11 @@ __device__ __forceinline__ void feature_quads(const FeatShared &S, const Grid &g
         const double dy = (double)p[q].y - (double)c.y;
         const double l2 = dx * dx + dy * dy;
         if (l2 < 4.0) {
-            const double d = 2.0 - sqrt(l2);
+            // FP64 root by Newton steps from the FP32 one (2 - l is 2 for any
+            // l2 below the FP32 range's lower end)
+            const float l2f = (float)l2;
+            const float il = l2f > 1e-30f ? __builtin_amdgcn_rsqf(l2f) : 0.f;
+            const double d = 2.0 - sqrt64_from32(l2, l2f * il, il);
             e[q] = e[q] + d * d;
         }
         near[q] += l2 < 5.29;
