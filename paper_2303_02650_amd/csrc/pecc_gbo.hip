@@ -2,13 +2,13 @@
 // Eq. 8-11 and the batch energy of Eq. 7) for batches of instances, one
 // persistent launch.
 //
-// Mapping (one workgroup of 256 threads = 4 waves per instance):
+// Mapping (one workgroup of 512 threads = 8 waves per instance):
 //   * the circles are partitioned once, at the start, into the blocks of a
 //     blocks x blocks grid over [-R, R]^2 (computed in FP64 on the input
 //     positions); block (bx, by) has colour (bx mod 2) + 2 (by mod 2), so
 //     blocks of one colour never touch;
 //   * an outer iteration visits the colours 0..3 in turn; inside a colour
-//     the 4 waves take its batches, one batch per wave at a time, and run one
+//     the 8 waves take its batches, one batch per wave at a time, and run one
 //     quasi-Newton iteration each, entirely inside the wave: the batch's
 //     circles sit on the lanes (up to 128, two per lane), its curvature
 //     history is loaded into registers, its Gram matrix into a wave-private
@@ -31,15 +31,19 @@
 // Results are bitwise reproducible: membership, list order and every sum
 // are functions of the positions only.
 //
-// Bound by latency: one wave per SIMD on as many CUs as there are instances,
-// whose visits are serial chains of LDS reads, global loads (history) and
-// dependent arithmetic.  So loads that do not depend on each other are issued
-// together (history, Gram matrix, eight list neighbors of a circle, four
-// circles of a thread outside the visits), what a wave keeps in LDS is one
-// array indexed by offsets (an access through a chosen pointer becomes a flat
-// one, which waits for every counter), and the lists are built from mask bits.
-// 64 instances of n = 1000 in 4 x 4 blocks, 300 outer iterations: 17.8 ms,
-// 24.5 ms with one load or neighbor at a time.  Loading the next visit's
+// Bound by latency: a wave or two per SIMD on as many CUs as there are
+// instances, whose visits are serial chains of LDS reads, global loads
+// (history) and dependent arithmetic.  So loads that do not depend on each
+// other are issued together (history, Gram matrix, eight list neighbors of a
+// circle, a thread's circles outside the visits), what a wave keeps in LDS is
+// one array indexed by offsets (an access through a chosen pointer becomes a
+// flat one, which waits for every counter), and the lists are built from mask
+// bits.  Eight waves take up to eight batches of a colour at once, and share
+// the lists, energies and moves; the instance's sums keep the order of four
+// waves of four circles per thread.  64 instances of n = 1000 in 4 x 4 blocks,
+// 300 outer iterations: 17.2 ms; with four waves 17.8 ms, and 24.5 ms with one
+// load or neighbor at a time.  64 instances of n = 900 in 6 x 6 blocks, 100
+// outer iterations: 7.2 ms, 10.5 ms with four waves.  Loading the next visit's
 // history ahead gained under 1 % more (not kept).
 #include "pecc_device.hpp"
 #include "pecc_host.hpp"
@@ -48,13 +52,14 @@
 
 namespace pecc {
 
-constexpr int kGT = 256;                    // threads per workgroup
+constexpr int kGT = 512;                    // threads per workgroup
 constexpr int kGW = kGT / kWave;            // waves
 constexpr int kGCPB = 2;                    // circles per lane inside a batch
 constexpr int kGEll = 24;                   // neighbor slots per circle
 constexpr int kMaxGboBatch = kWave * kGCPB; // circles per batch at most
 constexpr int kMaxGboBatches = 64;          // blocks x blocks, blocks <= 8
 constexpr int kGU = kMaxN / kGT;            // circles per thread outside the visits
+constexpr int kGSum = 4;                    // waves whose order the instance's sums keep
 constexpr int kInBatch = kMaxN * (int)sizeof(float2);      // list entries: the trial position
 constexpr int kNowhere = 2 * kInBatch;                     // and the place beyond everything
 
@@ -80,9 +85,10 @@ struct GboShared {
     int ncolour[4];
     // per wave: Gram matrix, double-buffered, and the slot totals (one array,
     // so that an entry's source is an offset and every access stays an LDS one)
-    float wave[kGW][kTot + kWave];
+    alignas(8) float wave[kGW][kTot + kWave];
+    float gn[4][kMaxGboBatches];            // gradient norms of the visits, by colour
     uint16_t bsrc[2][kNB * kNB];
-    float redf[2][kGW];
+    float redf[2][kGW], redg[2][kGSum];
     double redd[2][kGW];
     int scan_tmp[kGW + 1];
     int bk[kMaxGboBatches], bhead[kMaxGboBatches];   // pairs and ring position of every batch
@@ -269,6 +275,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
         }
         for (int e = tid; e < nbat * kNB * kNB; e += kGT) gram[e] = 0.f;
         for (int p = tid; p < nbat; p += kGT) { sh.bk[p] = 0; sh.bhead[p] = 0; }
+        for (int q = tid; q < 4 * kMaxGboBatches; q += kGT) sh.gn[q / kMaxGboBatches][q % kMaxGboBatches] = 0.f;
         __syncthreads();
         // members, ascending inside a batch: one thread per batch
         for (int p = tid; p < nbat; p += kGT) {
@@ -307,7 +314,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
         int64_t pair_mine = 0;
         bool overflow = false;
         double ehist = 0.0, E64t = -1.0;
-        float Ew = 0.f, gsum = 0.f, gs_all = 0.f;   // gsum: this wave's visits
+        float Ew = 0.f, gs_all = 0.f;
         const int window = A.ftol_window;
 
         constexpr int kGramTurns = (kNB * kNB + kWave - 1) / kWave;
@@ -323,8 +330,9 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
 
             // ---- whole-instance energies and the stop tests ------------------------
             if (colour == 0) {
-                float e = 0.f;
-                double et = 0.0;
+                float *const e_of = &sh.wave[0][0];
+                double *const et_of = reinterpret_cast<double *>(e_of + kMaxN);
+                static_assert(sizeof(sh.wave) >= kMaxN * (sizeof(float) + sizeof(double)), "energies fit the scratch");
                 float2 qv[kGU];
                 float ec[kGU];
                 double etc[kGU];
@@ -383,7 +391,6 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                 }
 #pragma unroll
                 for (int u = 0; u < kGU; ++u) {
-                    if (tid + u * kGT >= n) continue;
                     const float2 q = qv[u];
                     const float r2 = q.x * q.x + q.y * q.y;
                     const float ir = r2 > 0.f ? __builtin_amdgcn_rsqf(r2) : 0.f;
@@ -393,28 +400,43 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                     const double ct = r64 + 1.0 - R64;
                     if (ct > 0.0) etc[u] += ct * ct;
                     if (!(isfinite(q.x) && isfinite(q.y))) { ec[u] = __builtin_nanf(""); etc[u] = __builtin_nan(""); }
-                    e += ec[u];
-                    et += etc[u];
+                    // (the waves' scratch is free here)
+                    const bool on = tid + u * kGT < n;
+                    e_of[tid + u * kGT] = on ? ec[u] : 0.f;
+                    et_of[tid + u * kGT] = on ? etc[u] : 0.0;
                 }
-                e = wave_sum(e);
-                et = wave_sum(et);
+                __syncthreads();
                 const int par = outer & 1;
-                if (lane == 0) {
-                    sh.redf[par][wv] = e;
-                    sh.redd[par][wv] = et;
-                    sh.wave[wv][kTot + 1] = gsum;   // free at this point
+                if (wv < kGSum) {
+                    // the sums of 256 threads of four circles each, and of the
+                    // visits of four waves, whatever the workgroup's size
+                    float e = 0.f, gs = 0.f;
+                    double et = 0.0;
+#pragma unroll
+                    for (int q = 0; q < kMaxN / (kGSum * kWave); ++q) {
+                        e += e_of[tid + q * kGSum * kWave];
+                        et += et_of[tid + q * kGSum * kWave];
+                    }
+                    for (int c = 0; c < 4; ++c)
+                        for (int r = wv; r < sh.ncolour[c]; r += kGSum) gs += sh.gn[c][r];
+                    e = wave_sum(e);
+                    et = wave_sum(et);
+                    if (lane == 0) {
+                        sh.redf[par][wv] = e;
+                        sh.redd[par][wv] = et;
+                        sh.redg[par][wv] = gs;
+                    }
                 }
                 __syncthreads();
                 Ew = 0.f;
                 float gs = 0.f;
                 double ett = 0.0;
 #pragma unroll
-                for (int w = 0; w < kGW; ++w) {
+                for (int w = 0; w < kGSum; ++w) {
                     Ew += sh.redf[par][w];
                     ett += sh.redd[par][w];
-                    gs += sh.wave[w][kTot + 1];
+                    gs += sh.redg[par][w];
                 }
-                __syncthreads();   // the totals are the waves' scratch again below
                 gs_all = gs;
                 E64t = ett;
                 const double Eacc = (double)Ew;
@@ -432,7 +454,6 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                 if (lane == outer % (window + 1)) ehist = Eacc;
                 if (outer >= A.max_iter) { status = 5; break; }
                 ++outer;
-                gsum = 0.f;
             }
 
             // ---- the colour's batches ---------------------------------------------
@@ -669,7 +690,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                             for (int c = 0; c < kGCPB; ++c) g[c] = gt[c];
                             const float gg = W[cur + kG * kNB + kG];
                             const float gn = sqrtf(fmaxf(gg, 0.f));
-                            gsum += gn;
+                            if (lane == 0) sh.gn[colour][r] = gn;
 
                             // ---- direction: two-loop on the batch's Gram matrix -----------
                             float Bc[kNB];
