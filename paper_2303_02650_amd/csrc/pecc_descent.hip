@@ -362,12 +362,18 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
     // every wave decides only in the dense mode
     static_assert(SOLO || DENSE, "the limited-memory modes decide on one wave");
     constexpr int ELL = SEQ ? kEllSeq : kEll;
-    // list slots per turn of the sweep: two where a lone wave per SIMD has
-    // only one circle per thread (their chains overlap), and in batch visits,
-    // which test two reads in a chain per slot (128 x n = 1000, five batches,
-    // 200 outer iterations: 15.23 ms with one slot, 14.98 with two, 15.09 with
-    // three, 15.7 with four, which spills)
-    constexpr int kTrips = (CPT == 1 && BLOCK <= 256) || SEQ ? 2 : 1;
+    // list slots per turn of the sweep, their reads in flight together; lists
+    // are padded to whole turns, and a wave's longest is five to eight.  Three
+    // fit best where registers allow: two circles per thread, 256 x n = 1000,
+    // 27.6 ms with one slot, 27.2 with two, 26.8 with three, 28.9 with four;
+    // a lone wave per SIMD, 64 x n = 60, 2.91 ms with two, 2.83 with three.
+    // 256 threads: 5.40 ms at 64 x n = 200 with two, 5.41 with three.  512
+    // threads with one circle have no registers for more than one (16.21 ms at
+    // 64 x n = 400, 16.34 with two).  Batch visits: 128 x n = 1000, five
+    // batches, 200 outer iterations, 15.23 ms with one, 14.98 with two, 15.09
+    // with three, 15.7 with four.
+    constexpr int kTrips = SEQ ? 2 : CPT == 2 || BLOCK <= 128 ? 3 : BLOCK == 256 ? 2 : 1;
+    static_assert(ELL % kTrips == 0, "whole turns");
     __shared__ DescentShared<ELL, kNM, kDW, DENSE> sh;
     __shared__ std::conditional_t<DENSE, DenseShared, std::conditional_t<SEQ, SeqShared, NoShared>> sq;
     const int tid = threadIdx.x;
