@@ -34,17 +34,19 @@
 // Bound by latency: a wave or two per SIMD on as many CUs as there are
 // instances, whose visits are serial chains of LDS reads, global loads
 // (history) and dependent arithmetic.  So loads that do not depend on each
-// other are issued together (history, Gram matrix, eight list neighbors of a
+// other are issued together (history, Gram matrix, six list neighbors of a
 // circle, a thread's circles outside the visits), what a wave keeps in LDS is
 // one array indexed by offsets (an access through a chosen pointer becomes a
 // flat one, which waits for every counter), and the lists are built from mask
 // bits.  Eight waves take up to eight batches of a colour at once, and share
 // the lists, energies and moves; the instance's sums keep the order of four
 // waves of four circles per thread.  64 instances of n = 1000 in 4 x 4 blocks,
-// 300 outer iterations: 17.2 ms; with four waves 17.8 ms, and 24.5 ms with one
-// load or neighbor at a time.  64 instances of n = 900 in 6 x 6 blocks, 100
-// outer iterations: 7.2 ms, 10.5 ms with four waves.  Loading the next visit's
-// history ahead gained under 1 % more (not kept).
+// 300 outer iterations: 16.7 ms (16.9 with three neighbors per turn, 17.6 with
+// four, 17.3 with eight, 18.3 with twelve: a list has five to twelve, and
+// places past its end cost their terms); with four waves 17.8 ms, and 24.5 ms
+// with one load or neighbor at a time.  64 instances of n = 900 in 6 x 6
+// blocks, 100 outer iterations: 7.05 ms, 10.5 ms with four waves.  Loading the
+// next visit's history ahead gained under 1 % more (not kept).
 #include "pecc_device.hpp"
 #include "pecc_host.hpp"
 #include "pecc_launch.hpp"
@@ -563,12 +565,13 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                                     term_at(sh.xy[j + (inb ? kMaxN : 0)], inb ? j < i : true);   // Eq. 7
                                 };
                                 if (c * kWave < np && !far && !overflow) {
-                                    // the wave's longest list, eight neighbors in
+                                    // the wave's longest list, six neighbors in
                                     // flight; past a list's end a place that adds
                                     // zeros
                                     const int mc = act[c] ? sh.list_n[i] : 0;
                                     const int mmax = wave_max_dpp(mc);
-                                    constexpr int kTurn = 8;
+                                    constexpr int kTurn = 6;
+                                    static_assert(kGEll % kTurn == 0, "whole turns");
                                     for (int t0 = 0; t0 < mmax; t0 += kTurn) {
                                         int o[kTurn];
                                         float2 pj[kTurn];
