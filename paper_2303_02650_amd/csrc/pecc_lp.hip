@@ -307,39 +307,40 @@ __device__ void load_weights(const float *__restrict__ P, NetWeights &W, bool tr
     }
 }
 
-// Phi(-|t|), the normal distribution's tail, from the rational approximation
-// 7.1.26 of Abramowitz and Stegun (Handbook of Mathematical Functions) of
-// erf(x), x = |t| / sqrt 2: (a1 u + ... + a5 u^5) exp(-x^2) / 2 with u =
-// 1 / (1 + p x); at most 0.75e-7 off in exact arithmetic, about 3e-7 in FP32
-// with the hardware reciprocal and exponential.  The factors 1/2 and 1/sqrt 2
-// are in the constants.  gauss receives exp(-t^2 / 2).
-__device__ __forceinline__ float normal_tail(float t, float &gauss)
+// erf(x) by the rational approximation 7.1.26 of Abramowitz and Stegun
+// (Handbook of Mathematical Functions): erf(x) = 1 - (a1 t + ... + a5 t^5)
+// exp(-x^2) with t = 1 / (1 + p x) for x >= 0, odd in x; at most 1.5e-7 from
+// erf in exact arithmetic, about 6e-7 in FP32 with the hardware reciprocal
+// and exponential.  gauss receives the exp(-x^2) it forms.  One reciprocal,
+// one exponential and seven FMAs, against the library erff's longer
+// piecewise evaluation.  Used where the derivative, which shares the
+// exponential, is wanted too (training).
+__device__ __forceinline__ float erf_as(float x, float &gauss)
 {
-    const float u = __builtin_amdgcn_rcpf(fmaf(0.23164188f, fabsf(t), 1.0f));
-    float q = fmaf(u, 0.5307027145f, -0.7265760135f);
-    q = fmaf(u, q, 0.7107068705f);
-    q = fmaf(u, q, -0.142248368f);
-    q = fmaf(u, q, 0.127414796f);
-    gauss = __builtin_amdgcn_exp2f(t * (t * -0.72134752044f));
-    return u * q * gauss;
+    const float ax = fabsf(x);
+    const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, ax, 1.0f));
+    float q = fmaf(t, 1.061405429f, -1.453152027f);
+    q = fmaf(t, q, 1.421413741f);
+    q = fmaf(t, q, -0.284496736f);
+    q = fmaf(t, q, 0.254829592f);
+    gauss = __expf(-ax * ax);
+    return copysignf(fmaf(-t * q, gauss, 1.0f), x);
 }
 
-// GELU(t) = t Phi(t) = max(t, 0) - |t| Phi(-|t|) and its derivative Phi(t) +
-// t phi(t), phi(t) = exp(-t^2 / 2) / sqrt(2 pi) (the same exponential as the
-// tail's).
+// GELU(t) = t Phi(t) = 0.5 t (1 + erf(t / sqrt 2)) and its derivative
+// Phi(t) + t phi(t), phi(t) = exp(-t^2 / 2) / sqrt(2 pi) (the same
+// exponential as the erf's).
 __device__ __forceinline__ float gelu(float t)
 {
     float gs;
-    const float tail = normal_tail(t, gs);
-    const float c = __builtin_amdgcn_fmed3f(t, -3.0e38f, 3.0e38f);   // infinity times 0
-    return fmaf(-fabsf(c), tail, __builtin_elementwise_maximum(t, 0.0f));
+    return 0.5f * t * (1.0f + erf_as(t * 0.70710678118654752f, gs));
 }
 
 __device__ __forceinline__ float gelu_prime(float t)
 {
     float gs;
-    const float tail = normal_tail(t, gs);
-    return fmaf(t * 0.39894228040143268f, gs, t < 0.0f ? tail : 1.0f - tail);
+    const float e = erf_as(t * 0.70710678118654752f, gs);
+    return 0.5f * (1.0f + e) + t * 0.39894228040143268f * gs;
 }
 
 // GELU where its derivative is not wanted: log2 Phi(-|t|) is close to a
@@ -452,7 +453,9 @@ __device__ __forceinline__ bf16x8 frag_x(const float *__restrict__ X, int64_t ro
 // Forward pass of 16 rows; a1/a2 get the pre-activations (neuron 16t+4g+i of
 // this lane's row), h1b the BF16 high parts of h1 as B fragments, h2 the
 // second activations; the return value is the logit of row r in every lane.
-// TRAIN: the activation whose terms the derivative shares.
+// TRAIN: the activation whose terms the derivative shares, and biases added to
+// the products (the forward pass starts the products from them; a gradient's
+// BF16 roundings would turn over with the last bit of an activation).
 template <bool TRAIN>
 __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g, int r,
                                            float (&a1)[4][4], float (&a2)[4][4], bf16x8 (&h1b)[2],
@@ -462,10 +465,10 @@ __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const f32x4 bias = *reinterpret_cast<const f32x4 *>(&W.b1[16 * t + 4 * g]);
-        const f32x4 d = mfma(frag_w1(W, t, g, r), xb, bias);
+        const f32x4 d = mfma(frag_w1(W, t, g, r), xb, TRAIN ? f32x4{0.f, 0.f, 0.f, 0.f} : bias);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            a1[t][i] = d[i];
+            a1[t][i] = TRAIN ? d[i] + bias[i] : d[i];
             h1[t][i] = TRAIN ? gelu(a1[t][i]) : gelu_fast(a1[t][i]);
         }
     }
@@ -476,14 +479,15 @@ __device__ __forceinline__ float forward16(const NetWeights &W, bf16x8 xb, int g
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const bf16x8 w0 = frag_perm(W.w2, t, 0, g, r), w1 = frag_perm(W.w2, t, 1, g, r);
-        f32x4 d = mfma(w0, h1b[0], *reinterpret_cast<const f32x4 *>(&W.b2[16 * t + 4 * g]));
+        const f32x4 bias = *reinterpret_cast<const f32x4 *>(&W.b2[16 * t + 4 * g]);
+        f32x4 d = mfma(w0, h1b[0], TRAIN ? f32x4{0.f, 0.f, 0.f, 0.f} : bias);
         d = mfma(w1, h1b[1], d);
         d = mfma(w0, h1l[0], d);
         d = mfma(w1, h1l[1], d);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int nn = 16 * t + 4 * g + i;
-            a2[t][i] = d[i];
+            a2[t][i] = TRAIN ? d[i] + bias[i] : d[i];
             h2[t][i] = TRAIN ? gelu(a2[t][i]) : gelu_fast(a2[t][i]);
             zp += W.w3[nn] * h2[t][i];
         }
