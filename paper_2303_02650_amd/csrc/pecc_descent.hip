@@ -277,7 +277,7 @@ struct NoShared {
 enum : int { kReqInit = 0, kReqFp64 = 1, kReqTrial = 2, kReqTotal = 3 };
 // outcome of an evaluation in the whole-instance descent
 enum : int { kDecAccept = 1, kDecPush = 2, kDecStop = 4, kDecNext = 8, kDecSteepest = 16, kDecAnm = 32,
-             kDecFp64 = 64 };
+             kDecFp64 = 64, kDecEnd = 128 };   // kDecEnd: NONFINITE, no further round
 constexpr int kDecReq = 8, kDecBatch = 16;   // bit positions of the request and the batch
 
 // Gram ring with pair 0 at storage pair hd: where lane l (basis vector l in
@@ -959,6 +959,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         float Rz = R, gR = 0.f, pR = 0.f, lam = ADJ ? A.lambda0 : 0.f;
         float hR_v = 0.f;
         int iters_all = 0;
+        bool ended = false;               // (uniform, unlike status) no further round
         for (int round = 0;; ++round) {
         if constexpr (ADJ) {
             if (round >= A.rounds) break;
@@ -1559,7 +1560,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                             float cf, gam;
                             const float gpv = two_loop(Bc, live ? rho_l : 0.f, cf, gam);
                             if (status != 0) {
-                                fl |= kDecStop;
+                                fl |= kDecStop | (status == 6 ? kDecEnd : 0);
                             } else {
                                 gp = gpv;
                                 if constexpr (ADJ) {
@@ -1625,6 +1626,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 }
                 if constexpr (SEQ)
                     if (fl & kDecAnm) anm_compare();                    // every wave
+                if constexpr (ADJ) ended = (fl & kDecEnd) != 0;
                 if (fl & kDecStop) break;
                 if (fl & kDecNext) continue;
                 // ---- direction p = -(gamma g + sum_j cs_j s_j + cy_j y_j),
@@ -1802,7 +1804,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         }
         iters_all += it;
         if constexpr (!ADJ) break;
-        if (status == 6) break;                  // NONFINITE ends the adjustment
+        if (ended) break;                        // NONFINITE ends the adjustment
         lam *= 0.5f;
         }   // rounds
 
