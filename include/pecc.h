@@ -100,7 +100,7 @@ const char *pecc_version(void);
  * col.
  * cell_size <= 0 selects cutoff; otherwise it must be >= cutoff.
  * Errors: PECC_ERR_INVALID for an unknown format or a misaligned col.
- * Workspace: pecc_build_neighbors_workspace_size().
+ * Workspace: pecc_build_neighbors_workspace_size() bytes, at any alignment.
  * ------------------------------------------------------------------------ */
 #define PECC_LIST_HALF    0
 #define PECC_LIST_FULL    1

@@ -95,11 +95,14 @@ __device__ __forceinline__ void sort_pairs(u16x2 (&a)[kRowRegs])
                     }
 }
 
-// State words of a build, cleared.
+// State words of a build, cleared.  The last instance's word is nobody's to
+// read and is left out (see launch_build), except where it is the only one.
+__device__ __host__ __forceinline__ int state_words(int B) { return B > 1 ? B - 1 : 1; }
+
 __global__ __launch_bounds__(kBuildBlock) void build_clear_kernel(unsigned long long *state, int B)
 {
     const int64_t i = (int64_t)blockIdx.x * kBuildBlock + threadIdx.x;
-    if (i < B) state[i] = 0ull;
+    if (i < state_words(B)) state[i] = 0ull;
 }
 
 template <int FORMAT>
@@ -221,7 +224,7 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
     if (tid == 0) {
         if (b == 0)
             atomicAdd(&state[0], kHasPrefix | (unsigned long long)total);
-        else
+        else if (b < state_words(B))
             __hip_atomic_store(&state[b], kHasCount | (unsigned long long)total, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -345,7 +348,7 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
             if (known) break;
         }
         if (tid == 0) {
-            if (b > 0)
+            if (b > 0 && b < state_words(B))
                 __hip_atomic_store(&state[b], kHasPrefix | (unsigned long long)(base + total),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             base_s = base;
@@ -1157,8 +1160,11 @@ hipError_t launch_build(const int32_t *offset, const float *R, const float *xy, 
                         int64_t *inst_state, hipStream_t s)
 {
     const double c2 = cutoff * cutoff;
-    unsigned long long *state = reinterpret_cast<unsigned long long *>(inst_state);
-    build_clear_kernel<<<(B - 1) / kBuildBlock + 1, kBuildBlock, 0, s>>>(state, B);
+    // the caller's workspace may start at any byte: the atomics need 8-byte
+    // words, of which at least B - 1 follow in its 8 B bytes (B = 1: its 256)
+    unsigned long long *state =
+        reinterpret_cast<unsigned long long *>((reinterpret_cast<uintptr_t>(inst_state) + 7) & ~(uintptr_t)7);
+    build_clear_kernel<<<(state_words(B) - 1) / kBuildBlock + 1, kBuildBlock, 0, s>>>(state, B);
     if (format == kListLocal16)
         build_kernel<kListLocal16><<<B, kBuildBlock, 0, s>>>(offset, R, xy, B, total_n, c2, h_req, row,
                                                              col, capacity, num_pairs, state);
