@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
             ci[2 * h + e] = cell_circ[on[e] ? s : 0];
             cell_rows(q[e], on[e], s, g, cell_start, ra[e], rl[e], self[e]);
             // infinity has no neighbors: its runs are emptied
-            if (!(fabsf(q[e].x) <= 3.0e38f && fabsf(q[e].y) <= 3.0e38f)) {
+            if (!(fabsf(q[e].x) < HUGE_VALF && fabsf(q[e].y) < HUGE_VALF)) {
 #pragma unroll
                 for (int r = 0; r < 3; ++r) rl[e][r] = 0;
                 on[e] = false;

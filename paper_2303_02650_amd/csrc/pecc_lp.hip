@@ -97,7 +97,7 @@ __device__ __forceinline__ void feature_quads(const FeatShared &S, const Grid &g
     for (int q = 0; q < 2; ++q) {
         int place;
         // a point that is not finite is near nothing
-        const bool on = act && fabsf(p[q].x) <= 3.0e38f && fabsf(p[q].y) <= 3.0e38f;
+        const bool on = act && fabsf(p[q].x) < HUGE_VALF && fabsf(p[q].y) < HUGE_VALF;
         cell_rows(p[q], on, 0, g, S.cell_start, ra[q], rl[q], place);
         plain[q] = max(rl[q][0], max(rl[q][1], rl[q][2])) <= 32 && rl[q][0] + rl[q][1] + rl[q][2] <= 64;
     }
