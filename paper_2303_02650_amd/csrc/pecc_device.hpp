@@ -70,6 +70,14 @@ __device__ __forceinline__ bool near64(float2 a, float2 b, double c2)
     return dx * dx + dy * dy < c2;
 }
 
+// What the wave wrote to LDS is there for its other lanes.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // wave64 reductions and scans
 // ---------------------------------------------------------------------------

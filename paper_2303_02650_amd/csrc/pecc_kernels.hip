@@ -52,14 +52,22 @@ __device__ __forceinline__ bool writable_range(int off, int n, int64_t total_n)
 // neighbors in space and their runs have similar lengths; the candidates
 // cost an FP32 distance and a mask bit (neighbor_masks); the neighbors of two
 // circles are collected in one set of registers as 16-bit halves and sorted
-// by a network (packed 16-bit minimum and maximum), 8, 12 or 16 entries.  Longer
-// rows, and circles with more candidates than a mask holds, are taken
-// candidate by candidate with an insertion sort.  The instance's segment is
-// staged in LDS and stored in order (stores of 8 bytes), as is the row table.
+// by a network (packed 16-bit minimum and maximum), 8, 12 or 16 entries (at
+// packing density and the packing cutoff of 2.3 a row has 4 to 8, rarely 16).
+// Longer rows, and those of circles with more candidates than a mask holds (32
+// in a cell row, 64 in all), are written from bits in LDS, half a wave per row:
+// 32 words hold the circles of an instance in ascending order.  They stand
+// behind branches that are taken for the wave and laid out of the way: code in
+// the path of the short rows costs its instruction fetches, 9 us of the first
+// workgroups' 27.  The instance's segment is staged in LDS and stored in order
+// (stores of 8 bytes), as is the row table.
 // One pass instead of a count pass, a one-workgroup scan and a fill pass that
-// sorted rows in global memory: 4096 x n = 1000 in 134 us (464 us before),
-// 2048 x n = 96 in 57 us (63 us); of these about 85 us are vector issue, and
-// about 14 us the tickets of the first generation, all on one word.  Looks
+// sorted rows in global memory: 4096 x n = 1000 at cutoff 2.3 in 112 us (442 us
+// before), at cutoff 4 in 317 us (1656 us, and 1723 us while long rows were
+// taken candidate by candidate by their threads), at cutoff 4 in cells of 8 in
+// 884 us (2074, 3790), at cutoff 8 in 0.98 ms (19.5, 21.3); of the 112 about 85
+// are vector issue, and about 14 the tickets of the first generation, all on
+// one word.  Looks
 // back of 256 or 1024 words per turn were slower (172 and 193 us with the
 // energy against 168): words read while they are about to be written.
 // ---------------------------------------------------------------------------
@@ -119,6 +127,7 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
     __shared__ uint16_t cell_circ[kMaxN];
     __shared__ int scan_tmp[kBuildBlock / kWave];
     __shared__ int start_s[kMaxN];              // row lengths, then row starts, by circle
+    __shared__ unsigned bits_s[kBuildBlock];    // per wave: two rows as bits
     // positions in cell order and the sort's scratch, then the staged segment
     __shared__ union {
         struct {
@@ -157,23 +166,104 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
         sort_cells<kBuildBlock, kBuildCpt>(tid, x, nn, g, cell_start, cell_circ, sh.slot_tmp, psort,
                                            scan_tmp, own);
     }
-    // every neighbor of the circle of slot s, candidate by candidate
-    auto each_neighbor = [&](int s, int i, bool half, auto &&f) {
-        const float2 *const src = reinterpret_cast<const float2 *>(xy) + off;
-        const float2 q = src[i];
-        int ra[3], rl[3], self;
-        cell_rows(q, true, s, g, cell_start, ra, rl, self);
-        for (int r = 0; r < 3; ++r)
-            for (int t = ra[r]; t < ra[r] + rl[r]; ++t) {
-                const int j = cell_circ[t];
-                if (t != s && (!half || j > i) && near64(q, src[j], c2)) f(j);
+    // The long rows (bit u of `slow`): more neighbors than a row's registers, or
+    // runs too long for a mask.  Half a wave takes one, 32 candidates a turn.
+    // at(slot, circle) gives a position; f(i, on, turns) is called by the wave
+    // with each half's circle (on: there is one), and turns(v) calls v(has, j)
+    // with every candidate.
+    unsigned slow = 0, far = 0;                 // far: runs too long for a mask
+    const int lane = tid & (kWave - 1);
+    const float c2f = (float)c2, band = c2f * 1e-6f + 1e-30f;
+    auto long_rows = [&](auto &&at, auto &&f) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(slow != 0) == 0, 1)) return;
+#pragma unroll 1
+        for (int u = 0; u < kBuildCpt; ++u) {
+            unsigned long long left = __builtin_amdgcn_ballot_w64((slow >> u & 1) != 0);
+            while (left) {
+                const int l0 = __builtin_ctzll(left);
+                left &= left - 1;
+                const bool two = left != 0;
+                const int l1 = two ? __builtin_ctzll(left) : l0;
+                left &= left - 1;
+                const bool on = lane < 32 || two;
+                const int s = tid - lane + u * kBuildBlock + (lane < 32 ? l0 : l1);
+                const int i = cell_circ[s];
+                const float2 q = at(s, i);
+                int ra[3], rl[3], self;
+                cell_rows(q, on, s, g, cell_start, ra, rl, self);
+                const int n0 = rl[0], n1 = n0 + rl[1], all = n1 + rl[2];
+                const int longest = max(__builtin_amdgcn_readlane(all, 0), __builtin_amdgcn_readlane(all, 32));
+                f(i, on, [&](auto &&v) {
+                    for (int k0 = 0; k0 < longest; k0 += 32) {
+                        const int k = k0 + (lane & 31);
+                        const bool in = k < all;
+                        const int t = in ? k + (k < n0 ? ra[0] : k < n1 ? ra[1] - n0 : ra[2] - n1) : s;
+                        const int j = cell_circ[t];
+                        // (as neighbor_masks: the FP64 predicate within the band)
+                        const float2 p = at(t, j);
+                        const float dx = q.x - p.x, dy = q.y - p.y;
+                        const float d = fmaf(dx, dx, fmaf(dy, dy, -c2f));
+                        bool has = d < 0.f;
+                        if (__builtin_amdgcn_ballot_w64(!(fabsf(d) > band))) has = near64(q, p, c2);
+                        v(in && t != s && has, j);
+                    }
+                });
             }
+        }
+    };
+    auto at_slot = [&](int s, int) { return psort[s]; };
+    // A thread's circle with runs too long for a mask: f(w, first) gets 32
+    // candidates at a time, bit b of w for a neighbor at slot first + b.
+    auto wide_words = [&](float2 q, bool on, int own, auto &&f) {
+        const int cx = cell_coord(q.x, g), cy = cell_coord(q.y, g);
+        const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx < g.nc - 1 ? cx + 1 : cx;
+#pragma unroll 1
+        for (int r = -1; r <= 1; ++r) {
+            const int y = cy + r;
+            const bool row = on && y >= 0 && y < g.nc;
+            int first = row ? cell_start[y * g.nc + x0] : 0;
+            int len = row ? cell_start[y * g.nc + x1 + 1] - first : 0;
+            const int longest = wave_max_dpp(max(len, 0));
+            constexpr int kTurn = 4;
+#pragma unroll 1
+            for (int k0 = 0; k0 < longest; k0 += 32, first += 32, len -= 32) {
+                unsigned w;
+                float dmin = 3.0e38f;
+                auto scan = [&](auto exact) {
+                    w = 0;
+                    // downwards, so that the bit shifted in last is the first candidate
+#pragma unroll 1
+                    for (int k = min(32, (longest - k0 + kTurn - 1) / kTurn * kTurn) - kTurn; k >= 0; k -= kTurn) {
+                        float2 c[kTurn];
+                        const float2 *src = psort + min(first + k, kMaxN);
+#pragma unroll
+                        for (int v = 0; v < kTurn; ++v) c[v] = src[v];
+#pragma unroll
+                        for (int v = kTurn - 1; v >= 0; --v) {
+                            if constexpr (decltype(exact)::value) {
+                                w = w << 1 | (near64(q, c[v], c2) ? 1u : 0u);
+                            } else {
+                                const float dx = q.x - c[v].x, dy = q.y - c[v].y;
+                                const float t = fmaf(dx, dx, fmaf(dy, dy, -c2f));
+                                w = __builtin_amdgcn_alignbit(w, __float_as_uint(t), 31);
+                                dmin = fminf(dmin, fabsf(t));
+                            }
+                        }
+                    }
+                };
+                scan(std::false_type{});
+                if (__builtin_amdgcn_ballot_w64(dmin <= band)) scan(std::true_type{});
+                w &= len >= 32 ? ~0u : len > 0 ? (1u << len) - 1u : 0u;
+                const unsigned place = (unsigned)(own - first);
+                if (place < 32u) w &= ~(1u << place);
+                f(w, first);
+            }
+        }
     };
     // ---- neighbor masks of the circles of slots tid + 256 u, two at a time ---
     unsigned long long mask[kBuildCpt];
     unsigned firsts[kBuildCpt], lens[kBuildCpt];        // the three runs, 10 bits each (a first slot of 1024 is an empty run, and so are those after it)
     int ci[kBuildCpt], mine = 0;
-    bool plain[kBuildCpt];                      // row in registers
 #pragma unroll
     for (int h = 0; h < kBuildCpt / 2; ++h) {
         float2 q[2];
@@ -194,6 +284,7 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
             }
             fits[e] = max(rl[e][0], max(rl[e][1], rl[e][2])) <= 32 && rl[e][0] + rl[e][1] + rl[e][2] <= 64;
             // a circle with too many candidates stands aside (empty runs)
+            far |= on[e] && !fits[e] ? 1u << (2 * h + e) : 0u;
             on[e] = on[e] && fits[e];
 #pragma unroll
             for (int r = 0; r < 3; ++r) {
@@ -210,10 +301,29 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int u = 2 * h + e, pop = __builtin_popcountll(mk[e]);
-            plain[u] = fits[e] && pop <= kRowRegs;
             mine += pop;
-            mask[u] = plain[u] ? mk[e] : 0ull;
-            if (!fits[e]) each_neighbor(tid + u * kBuildBlock, ci[u], false, [&](int) { ++mine; });
+            mask[u] = pop <= kRowRegs ? mk[e] : 0ull;
+            slow |= pop <= kRowRegs ? 0u : 1u << u;
+            if (!kHalf && pop > kRowRegs) start_s[ci[u]] = pop;
+        }
+    }
+    slow |= far;
+    // lengths of the long rows that no mask gave (a half list's rows hold only
+    // the circles above their own)
+    const unsigned uncounted = kHalf ? slow : far;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(uncounted != 0) != 0, 0)) {
+#pragma unroll 1
+        for (int u = 0; u < kBuildCpt; ++u) {
+            const bool on = (uncounted >> u & 1) != 0;
+            const int own = tid + u * kBuildBlock, i = cell_circ[on ? own : 0];
+            int pop = 0, len = 0;
+            wide_words(psort[on ? own : 0], on, own, [&](unsigned w, int first) {
+                pop += __builtin_popcount(w);
+                if (kHalf)
+                    for (; w; w &= w - 1) len += cell_circ[first + __builtin_ctz(w)] > i ? 1 : 0;
+            });
+            mine += (far >> u & 1) ? pop : 0;
+            if (on) start_s[i] = kHalf ? len : pop;
         }
     }
     // The instance's count, published before the rows are collected: the
@@ -282,10 +392,7 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
 #pragma unroll
     for (int u = 0; u < kBuildCpt; ++u) {
         const int s = tid + u * kBuildBlock;
-        if (s < nn) {
-            if (!plain[u]) each_neighbor(s, ci[u], kHalf, [&](int) { ++cnt[u]; });
-            start_s[ci[u]] = cnt[u];
-        }
+        if (s < nn && !(slow >> u & 1)) start_s[ci[u]] = cnt[u];
     }
     __syncthreads();
     // ---- row starts: thread t holds circles 4 t .. 4 t + 3 -------------------
@@ -303,27 +410,52 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
         run += len4[u];
     }
     __syncthreads();
+    // A long row in ascending order: its circles as bits in LDS, a word per lane
+    // of the half, and every lane's places from a prefix sum over the words.
+    // put(place in the segment, circle).
+    auto put_long_rows = [&](auto &&at, auto &&put) {
+        unsigned *const word = bits_s + (tid - lane);
+        long_rows(at, [&](int i, bool on, auto &&turns) {
+            word[lane] = 0;
+            wave_sync();
+            turns([&](bool has, int j) {
+                if (has) atomicOr(&word[(lane & 32) + (j >> 5)], 1u << (j & 31));
+            });
+            wave_sync();
+            unsigned w = word[lane];
+            if (kHalf) {
+                const int first = i + 1 - 32 * (lane & 31);      // bits below it are not listed
+                w = first >= 32 ? 0u : first > 0 ? w & (~0u << first) : w;
+            }
+            int before = __builtin_popcount(w);
+            const int own = before;
+            before += dppi<0x111>(before);                       // row_shr 1, 2, 4, 8
+            before += dppi<0x112>(before);
+            before += dppi<0x114>(before);
+            before += dppi<0x118>(before);
+            before += dppi<kDppBcast15, 0xa>(before);            // a half is two rows
+            int place = start_s[i] + before - own;
+            while (on && w) {
+                put(place++, 32 * (lane & 31) + __builtin_ctz(w));
+                w &= w - 1;
+            }
+            wave_sync();
+        });
+    };
     // ---- the segment into LDS -----------------------------------------------
     const bool staged = total <= kStage;
     if (staged) {
 #pragma unroll
         for (int u = 0; u < kBuildCpt; ++u) {
-            const int s = tid + u * kBuildBlock;
-            if (s >= nn) continue;
+            if (tid + u * kBuildBlock >= nn) continue;
             uint16_t *dst = stage + start_s[ci[u]];
-            if (plain[u]) {
 #pragma unroll
-                for (int k = 0; k < kRowRegs; ++k)
-                    if (k < used[u / 2] && k < cnt[u]) dst[k] = nb[u / 2][k][u % 2];
-            } else {
-                int w = 0;
-                each_neighbor(s, ci[u], kHalf, [&](int j) {
-                    int k = w++;
-                    for (; k > 0 && dst[k - 1] > j; --k) dst[k] = dst[k - 1];
-                    dst[k] = (uint16_t)j;
-                });
-            }
+            for (int k = 0; k < kRowRegs; ++k)
+                if (k < used[u / 2] && k < cnt[u]) dst[k] = nb[u / 2][k][u % 2];
         }
+        // (the sorted positions are overwritten by now)
+        put_long_rows([&](int, int j) { return reinterpret_cast<const float2 *>(xy)[off + j]; },
+                      [&](int place, int j) { stage[place] = (uint16_t)j; });
     }
     // ---- where the segment goes: the counts of the instances before ----------
     // One wave looks, a word per lane, so that little is read of words that
@@ -391,29 +523,18 @@ __global__ __launch_bounds__(kBuildBlock, 5) void build_kernel(
         if (tid < len - done) dst[done + tid] = (Idx)(add + stage[done + tid]);
         return;
     }
-    // a segment too long for LDS: every thread stores its rows itself
+    // a segment too long for LDS: rows from registers by their threads
 #pragma unroll
     for (int u = 0; u < kBuildCpt; ++u) {
-        const int s = tid + u * kBuildBlock;
-        if (s >= nn) continue;
+        if (tid + u * kBuildBlock >= nn) continue;
         const long long a = base + start_s[ci[u]];
-        if (plain[u]) {
 #pragma unroll
-            for (int k = 0; k < kRowRegs; ++k)
-                if (k < cnt[u] && a + k < capacity) col[a + k] = (Idx)(add + nb[u / 2][k][u % 2]);
-        } else {
-            long long w = a;
-            each_neighbor(s, ci[u], kHalf, [&](int j) {
-                if (w < capacity) {
-                    const Idx key = (Idx)(add + j);
-                    long long k = w;
-                    for (; k > a && col[k - 1] > key; --k) col[k] = col[k - 1];
-                    col[k] = key;
-                }
-                ++w;
-            });
-        }
+        for (int k = 0; k < kRowRegs; ++k)
+            if (k < cnt[u] && a + k < capacity) col[a + k] = (Idx)(add + nb[u / 2][k][u % 2]);
     }
+    put_long_rows(at_slot, [&](int place, int j) {
+        if (base + place < capacity) col[base + place] = (Idx)(add + j);
+    });
 }
 
 // ---------------------------------------------------------------------------

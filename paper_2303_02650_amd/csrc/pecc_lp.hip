@@ -551,13 +551,6 @@ struct GradShared {
     } u;
 };
 
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ float sum16(float v)   // over the 16 lanes of a group
 {
     v += dpp<kDppXor1>(v);
