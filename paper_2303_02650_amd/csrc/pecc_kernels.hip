@@ -1121,6 +1121,12 @@ __global__ __launch_bounds__(kHalfBlock) __attribute__((amdgpu_waves_per_eu(8, 8
 constexpr int kVerifyBlock = 256;
 constexpr int kVerifyCpt = kMaxN / kVerifyBlock;
 constexpr int kVerifyNc = 32;            // cells per axis at most (side 2.2 at n = 1024, R = 35)
+// Candidates of a circle from which its wave takes them all in FP64 (packings
+// have about five, layouts compressed to a third of their width 45).  500 of
+// 1000 circles in a box of 4 x 4, 256 instances: 106 us, 148 with a branch per
+// overlap and 111 with every pair tested in FP64 from LDS; all 1000 in it 281,
+// 401 and 162; 512 layouts at a third of their width 53.5, 65 and 254.
+constexpr int kVerifyCrowd = 32;
 constexpr int kVerifyBrute = 64;         // 2048 instances of 96: 14.8 us tested pair by pair, of 200 sorted 12.9
 
 __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
@@ -1193,6 +1199,7 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
     } else {
         const Grid g = make_grid<kVerifyNc>(R[b], 2.0f * (1.0f + kCellSafety));
         int own[kVerifyCpt];
+        if (tid == 0) psort[kMaxN] = make_float2(HUGE_VALF, HUGE_VALF);       // overlaps nothing
         sort_cells<kVerifyBlock, kVerifyCpt>(tid, p, n, g, cell_start, cell_circ, slot_tmp, psort,
                                              scan_tmp, own);
 #pragma unroll
@@ -1206,19 +1213,44 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_kernel(
             const int a1 = cell_start[up * g.nc + x0], z1 = cell_start[up * g.nc + x1 + 1];
             const int z0 = cell_start[cy * g.nc + x1 + 1];
             const int run0 = on ? z0 - (s + 1) : 0, run1 = on && up > cy ? z1 - a1 : 0;
+            const int run = run0 + run1;
+            // a crowded neighborhood, where most candidates overlap: the FP64
+            // terms of four side by side, without the FP32 test
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(run > kVerifyCrowd) != 0, 0)) {
+                const int longest = wave_max_dpp(run);
+                const double xi = p[u].x, yi = p[u].y;
+                for (int k0 = 0; k0 < longest; k0 += 4) {
+                    double d[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int k = k0 + q;
+                        const float2 pj = psort[k < run0 ? s + 1 + k : k < run ? a1 + (k - run0) : kMaxN];
+                        const double dx = xi - (double)pj.x, dy = yi - (double)pj.y;
+                        d[q] = 2.0 - sqrt(dx * dx + dy * dy);
+                        asm volatile("" : "+v"(d[q]));
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        d[q] = fmax(d[q], 0.0);       // no overlap, and NaN, add zero
+                        sp = sp + d[q] * d[q];
+                        mp = fmax(mp, d[q]);
+                    }
+                }
+                continue;
+            }
             // both runs as one, four candidates in flight
-            for (int k0 = 0; k0 < run0 + run1; k0 += 4) {
+            for (int k0 = 0; k0 < run; k0 += 4) {
                 float2 pj[4];
                 bool hit[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int k = k0 + q;
-                    pj[q] = psort[k < run0 ? s + 1 + k : k < run0 + run1 ? a1 + (k - run0) : 0];
+                    pj[q] = psort[k < run0 ? s + 1 + k : k < run ? a1 + (k - run0) : 0];
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float dx = p[u].x - pj[q].x, dy = p[u].y - pj[q].y;
-                    hit[q] = k0 + q < run0 + run1 && dx * dx + dy * dy < near2;
+                    hit[q] = k0 + q < run && dx * dx + dy * dy < near2;
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
