@@ -237,9 +237,11 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(
     }
     const int c0 = blockIdx.x * kFeatChunk;
     const int c1 = min(C, c0 + kFeatChunk);
-    for (int k0 = c0; k0 < c1; k0 += kFeatBlock) {
-        // threads past the end take the last candidate (whole waves: the
-        // longest runs are found across the lanes) and store nothing
+    // (a wave's first candidate, uniform: waves past the end have none)
+    const int w0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
+    for (int k0 = c0; k0 + w0 < c1; k0 += kFeatBlock) {
+        // lanes past the end take the last candidate (the longest runs are
+        // found across the lanes) and store nothing
         const int k = min(k0 + tid, c1 - 1);
         const int64_t gi = (int64_t)b * C + k;
         const int i = cand_circle[gi];
