@@ -65,7 +65,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // 128 x 4096 candidates at n = 1000: 48 us (127 us with every distance in
 // FP64, a square root evaluated by the whole wave at nearly every circle).
 constexpr int kFeatBlock = 512;
-constexpr int kFeatCpt = kMaxN / kFeatBlock;
 constexpr int kFeatChunk = 1024;     // candidates per workgroup
 constexpr float kDensRadius = 4.0f;  // widest radius a feature looks at
 
@@ -201,12 +200,14 @@ __device__ __forceinline__ void feature_quads(const FeatShared &S, const Grid &g
     }
 }
 
-__global__ __launch_bounds__(kFeatBlock) void features_kernel(
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void features_kernel(
     const int32_t *__restrict__ offset, const float *__restrict__ Rf,
     const double *__restrict__ R64, const float *__restrict__ xy, int C,
     const int32_t *__restrict__ cand_circle, const float *__restrict__ cand_dest,
     float *__restrict__ feat)
 {
+    constexpr int kCpt = kMaxN / BLOCK;
     __shared__ FeatShared S;
     const int b = blockIdx.y, tid = threadIdx.x;
     const int o = offset[b];
@@ -217,29 +218,29 @@ __global__ __launch_bounds__(kFeatBlock) void features_kernel(
     const float2 *p2 = reinterpret_cast<const float2 *>(xy) + o;
     const Grid g = make_grid(Rf[b], kDensRadius * (1.0f + kCellSafety));
     {
-        float2 x[kFeatCpt];
-        int own[kFeatCpt];
+        float2 x[kCpt];
+        int own[kCpt];
 #pragma unroll
-        for (int u = 0; u < kFeatCpt; ++u) {
-            const int i = tid + u * kFeatBlock;
+        for (int u = 0; u < kCpt; ++u) {
+            const int i = tid + u * BLOCK;
             x[u] = i < n ? p2[i] : make_float2(0.f, 0.f);
             // a circle at NaN is near nothing, like one at infinity (whose
             // sign bits are known)
             if (x[u].x != x[u].x) x[u].x = HUGE_VALF;
             if (x[u].y != x[u].y) x[u].y = HUGE_VALF;
         }
-        sort_cells<kFeatBlock, kFeatCpt>(tid, x, n, g, S.cell_start, S.cell_circ, S.slot_tmp, S.psort,
+        sort_cells<BLOCK, kCpt>(tid, x, n, g, S.cell_start, S.cell_circ, S.slot_tmp, S.psort,
                                          S.scan_tmp, own);
 #pragma unroll
-        for (int u = 0; u < kFeatCpt; ++u)
-            if (tid + u * kFeatBlock < n) S.slot_of[tid + u * kFeatBlock] = (uint16_t)own[u];
+        for (int u = 0; u < kCpt; ++u)
+            if (tid + u * BLOCK < n) S.slot_of[tid + u * BLOCK] = (uint16_t)own[u];
         __syncthreads();
     }
     const int c0 = blockIdx.x * kFeatChunk;
     const int c1 = min(C, c0 + kFeatChunk);
     // (a wave's first candidate, uniform: waves past the end have none)
     const int w0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
-    for (int k0 = c0; k0 + w0 < c1; k0 += kFeatBlock) {
+    for (int k0 = c0; k0 + w0 < c1; k0 += BLOCK) {
         // lanes past the end take the last candidate (the longest runs are
         // found across the lanes) and store nothing
         const int k = min(k0 + tid, c1 - 1);
@@ -940,8 +941,16 @@ hipError_t launch_features(const int32_t *offset, const float *R, const double *
 {
     if (B <= 0 || C <= 0) return hipSuccess;
     dim3 grid((C + kFeatChunk - 1) / kFeatChunk, B);
-    hipLaunchKernelGGL(features_kernel, grid, dim3(kFeatBlock), 0, s, offset, R, R64, xy, C,
-                       cand_circle, cand_dest, feat);
+    // half the threads where they cover the candidates of an instance and there
+    // are more instances than CUs: 2048 instances with 64 candidates, n = 10
+    // 17.7 us (21.8 with 512 threads), n = 1000 28.3 us (32.7); one instance of
+    // n = 1000 sorts its circles faster with 512 (10.8 us, 11.2 with 256)
+    if (C <= kFeatBlock / 2 && B > 256)
+        features_kernel<kFeatBlock / 2><<<grid, kFeatBlock / 2, 0, s>>>(offset, R, R64, xy, C,
+                                                                     cand_circle, cand_dest, feat);
+    else
+        features_kernel<kFeatBlock><<<grid, kFeatBlock, 0, s>>>(offset, R, R64, xy, C, cand_circle,
+                                                                cand_dest, feat);
     return hipGetLastError();
 }
 
