@@ -24,9 +24,15 @@
  *    calling thread.  Per-instance numerical outcomes (non-finite input, a
  *    line search that cannot decrease E, ...) are reported in result
  *    structs, never as return codes.  Device-side argument problems that
- *    the host cannot see (n_b > PECC_MAX_N, n_b > max_n, decreasing offsets)
- *    make the affected instance report PECC_STATUS_BAD_INSTANCE or an empty
- *    result.
+ *    the host cannot see (n_b > PECC_MAX_N, decreasing offsets) make the
+ *    affected instance report PECC_STATUS_BAD_INSTANCE or an empty result.
+ *  * max_n must bound every n_b.  It picks the workgroups of the L-BFGS
+ *    descents and of the container adjustment (for up to 64, 128, 256, 512
+ *    or 1024 circles; 512 or 1024 in the limited-memory k-batch descent):
+ *    there an instance above max_n reports PECC_STATUS_BAD_INSTANCE once it
+ *    exceeds the workgroup's size, and its layout stays as it was.  The
+ *    other calls compute it (the dense descent where its workspace, whose
+ *    size follows max_n, holds the matrices).
  */
 #ifndef PECC_H
 #define PECC_H
@@ -55,7 +61,7 @@ extern "C" {
 #define PECC_STATUS_STALLED      4  /* no step length passed the line search    */
 #define PECC_STATUS_MAX_ITER     5  /* iteration budget spent                  */
 #define PECC_STATUS_NONFINITE    6  /* E or g not finite                       */
-#define PECC_STATUS_BAD_INSTANCE 7  /* n_b outside [0, PECC_MAX_N]             */
+#define PECC_STATUS_BAD_INSTANCE 7  /* n_b outside [0, PECC_MAX_N], or above max_n (see above) */
 
 /* A batch of instances.  Host struct holding device pointers. */
 typedef struct pecc_instances {
