@@ -1822,7 +1822,8 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
             // with the radius as a variable, E reports the energy without
             // the penalty (the last lambda was halved once more after the round)
             r.E32 = (ADJ && A.rounds > 0) ? E - 2.f * lam * Rz * Rz : E;
-            r.gnorm = sqrtf(fmaxf(SOLO ? sh.Bring[SOLO ? kG * kRS + 4 * kMM : 0] : sh.Bm[cur][SOLO ? 0 : kG * kNB + kG], 0.f));
+            // (no round: no evaluation, and the ring is not there to be read)
+            r.gnorm = ADJ && A.rounds == 0 ? 0.f : sqrtf(fmaxf(SOLO ? sh.Bring[SOLO ? kG * kRS + 4 * kMM : 0] : sh.Bm[cur][SOLO ? 0 : kG * kNB + kG], 0.f));
             r.E64 = fp64 ? E64t : -1.0;
             if (SEQ && visits) {
                 // outer iterations; whole-instance energies; the sum of the

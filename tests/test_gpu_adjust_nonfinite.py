@@ -42,3 +42,22 @@ def test_others_are_untouched(n, B, bad):
     assert x[~ill].tobytes() == want_x[k].tobytes()
     assert Ro[~ill].tobytes() == want_R[k].tobytes()
     assert res[~ill].tobytes() == want[k].tobytes()
+
+
+@pytest.mark.parametrize("n,B", [(40, 300), (300, 300), (520, 300)])
+def test_no_rounds(n, B):
+    """Nothing is evaluated: layouts and radii as given, zeros in the result, also
+    right after calls that leave numbers in the workgroups' memory."""
+    import paper_2303_02650_amd as P
+
+    inst = synth.instance_set(B, n, float(np.sqrt(n / 0.8)), seed=n)
+    d = P.DeviceInstances.from_host(inst.offset, inst.R)
+    for _ in range(3):
+        xy = torch.from_numpy(inst.xy.reshape(-1).copy()).cuda()
+        P.adjust_container(d, xy.clone(), P.DescentParams(max_iter=3), rounds=1)
+        Ro, out = P.adjust_container(d, xy, P.DescentParams(), rounds=0)
+        res = P.results(out)
+        assert xy.cpu().numpy().tobytes() == inst.xy.reshape(-1).tobytes()
+        assert (Ro.cpu().numpy() == inst.R.astype(np.float32)).all()
+        for f in ("status", "iters", "evals", "rebuilds", "pair_evals", "E32", "gnorm", "cell_evals"):
+            assert (res[f] == 0).all(), f
