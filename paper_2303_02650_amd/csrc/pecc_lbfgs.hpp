@@ -85,14 +85,14 @@ __device__ __forceinline__ double as_f64(float2 v) { return __hiloint2double(__f
 
 // A circle's history pushed by one pair, in place (the value moves of the
 // plain assignments are otherwise allocated to a second set of registers and
-// copied back at the end of the loop body).
+// copied back at the end of the loop body).  Early-clobbered: v is read last.
 __device__ __forceinline__ void push_history(double (&H)[kMM], double v)
 {
     asm("v_mov_b64 %0, %1\n\tv_mov_b64 %1, %2\n\tv_mov_b64 %2, %3\n\tv_mov_b64 %3, %4\n\t"
         "v_mov_b64 %4, %5\n\tv_mov_b64 %5, %6\n\tv_mov_b64 %6, %7\n\tv_mov_b64 %7, %8\n\t"
         "v_mov_b64 %8, %9\n\tv_mov_b64 %9, %10"
-        : "+v"(H[0]), "+v"(H[1]), "+v"(H[2]), "+v"(H[3]), "+v"(H[4]), "+v"(H[5]), "+v"(H[6]),
-          "+v"(H[7]), "+v"(H[8]), "+v"(H[9])
+        : "+&v"(H[0]), "+&v"(H[1]), "+&v"(H[2]), "+&v"(H[3]), "+&v"(H[4]), "+&v"(H[5]), "+&v"(H[6]),
+          "+&v"(H[7]), "+&v"(H[8]), "+&v"(H[9])
         : "v"(v));
 }
 
@@ -210,7 +210,7 @@ __device__ __forceinline__ float wave_sum_dpp(float v)
 #define PECC_DOWN(FILL, S, J) PECC_LOOP_STEP("v_mul_f32 %[t], %[rho], %[acc]", FILL, J, S, "-", J)
 #define PECC_UP(FILL, SRC, S, J) PECC_LOOP_STEP("v_fma_f32 %[t], -%[rho], %[acc], %[cf]", FILL, SRC, S, "", J)
 #define PECC_LOOP_OPERANDS                                                                            \
-    : [acc] "+v"(acc), [cf] "+v"(cf), [t] "=&v"(t), [s0] "=&s"(s0), [s1] "=&s"(s1)                    \
+    : [acc] "+&v"(acc), [cf] "+&v"(cf), [t] "=&v"(t), [s0] "=&s"(s0), [s1] "=&s"(s1)                    \
     : [rho] "v"(rho), [b0] "v"(b[0]), [b1] "v"(b[1]), [b2] "v"(b[2]), [b3] "v"(b[3]), [b4] "v"(b[4]), \
       [b5] "v"(b[5]), [b6] "v"(b[6]), [b7] "v"(b[7]), [b8] "v"(b[8]), [b9] "v"(b[9])
 __device__ __forceinline__ void two_loop_down(const float *b, float rho, float &acc, float &cf)
