@@ -844,17 +844,6 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 const int ent = lane + kWave * r;
                 if (ent < kNB * kNB) sh.Bm[nxt][ent] = gv[r];
             }
-            if constexpr (!SEQ) {
-                // 1 / s_j'y_j follows the Gram entries (shifted on a push,
-                // the newest from the new entry): the two-loop reads them
-                // instead of dividing every iteration
-                if (lane < kMM) {
-                    const float keep = sh.rho[cur][lane < kMM - 1 ? lane + 1 : lane];
-                    const float sy = lane_value(tot, sScYc);
-                    sh.rho[nxt][lane] = !push ? sh.rho[cur][lane]
-                                              : lane < kMM - 1 ? keep : 1.f / sy;
-                }
-            }
             cur = nxt;
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -1134,7 +1123,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                                     if (masked) hf = hf || sq.bat[jj < kNM ? jj : kNM - 1] != cb;
                                 }
                                 float l2;
-                                const float il = pair_term32s(xq, pj[q][c], hf, two_r, four_r2, four_r2_band,
+                                const float il = pair_term32s(xq, pj[q][c], hf, two_r, four_r2,
                                                               ecA[c], e1cA[c], gxA[c], gyA[c], l2, kE1);
                                 // FP64 energies only where FP32 sees (nearly) an overlap:
                                 // outside a 1e-5 band the FP64 terms are zero
@@ -1669,32 +1658,32 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
             const float E1t = lane_value(tot, sE1);
 
             // ================= what the evaluation was for =====================
-            if constexpr (SEQ) {
-                if (visits && req == kReqTotal) {
-                    // ---- top of an outer iteration: stop tests on the whole instance
-                    E_tot = Et;
-                    E64o = so;
-                    E64t = st;
-                    const double Eacc = fp64 ? E64o : (double)E_tot;
-                    if (!isfinite(E_tot)) { status = 6; break; }
-                    if (E64t < A.e_feasible) { status = 1; break; }
-                    if (it > 0 && gsum_prev <= A.g_tol) { status = 2; break; }
-                    if (A.ftol > 0.f && it >= W && decreased_too_little(Eacc, (it - W) % (W + 1), A.ftol)) { status = 3; break; }
-                    if (lane == it % (W + 1)) ehist = Eacc;
-                    if (it > 0 && nvis > 0 && nstall == nvis) { status = 4; break; }
-                    if (it >= A.max_iter) { status = 5; break; }
-                    if (!fp64 && A.tau64 > 0.0 && (double)fminf(E_tot, E1t) < A.tau64) fp64 = true;
-                    gsum = 0.f;
-                    nvis = 0;
-                    nstall = 0;
-                    cb = first_b;
-                    k = __builtin_amdgcn_readlane(kb_v, cb);
-                    req = kReqInit;
-                    continue;
-                }
+            // (the dense descent only from here on: batches visited in turn,
+            // one batch too)
+            if (req == kReqTotal) {
+                // ---- top of an outer iteration: stop tests on the whole instance
+                E_tot = Et;
+                E64o = so;
+                E64t = st;
+                const double Eacc = fp64 ? E64o : (double)E_tot;
+                if (!isfinite(E_tot)) { status = 6; break; }
+                if (E64t < A.e_feasible) { status = 1; break; }
+                if (it > 0 && gsum_prev <= A.g_tol) { status = 2; break; }
+                if (A.ftol > 0.f && it >= W && decreased_too_little(Eacc, (it - W) % (W + 1), A.ftol)) { status = 3; break; }
+                if (lane == it % (W + 1)) ehist = Eacc;
+                if (it > 0 && nvis > 0 && nstall == nvis) { status = 4; break; }
+                if (it >= A.max_iter) { status = 5; break; }
+                if (!fp64 && A.tau64 > 0.0 && (double)fminf(E_tot, E1t) < A.tau64) fp64 = true;
+                gsum = 0.f;
+                nvis = 0;
+                nstall = 0;
+                cb = first_b;
+                k = __builtin_amdgcn_readlane(kb_v, cb);
+                req = kReqInit;
+                continue;
             }
             bool accept = false, push = false;
-            bool vend = false;     // batch descent: the visit ends with this evaluation
+            bool vend = false;     // the visit ends with this evaluation
             if (req == kReqTrial) {
                 const bool ok = fp64 ? so <= E64o + (double)A.c1 * (double)alpha * (double)gp
                                      : Et <= E + A.c1 * alpha * gp;
@@ -1702,22 +1691,18 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     accept = true;
                     const float sy = lane_value(tot, sScYc), yy = lane_value(tot, sYcYc);
                     push = sy > A.eps_curv * yy;
-                    vend = SEQ && visits;
+                    vend = true;
                 } else {
                     alpha *= 0.5f;
                     if (++h > A.max_halvings) {
-                        if (!(SEQ && visits)) { status = 4; break; }   // STALLED
                         vend = true;                                   // the batch stays
                         ++nstall;
                     } else {
                         continue;
                     }
                 }
-            } else if (req == kReqInit) {
-                accept = true;   // g and the g row of B from this evaluation
-            } else {             // kReqFp64: FP64 energies of the current point
-                E64o = so;
-                E64t = st;
+            } else {
+                accept = true;   // kReqInit: g and the g row of B from this evaluation
             }
             if (accept) {
                 gram_update(tot, par, push, lane);
@@ -1727,74 +1712,45 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                     g[c] = gt[c];
                 }
                 if (push) k = k + 1 > A.m ? A.m : k + 1;
-                if (req == kReqTrial && !(SEQ && visits)) ++it;   // visits: outer iterations
                 E = Et;
                 if (fp64) { E64o = so; E64t = st; }
-                // FP64 regime once either FP32 energy is small: with a contact
-                // margin the unit circles can be overlap-free while E (radius
-                // rad) still sums (2 mu)^2 over every contact
-                if (!(SEQ && visits) && !fp64 && A.tau64 > 0.0 &&
-                    (double)fminf(E, E1t) < A.tau64) {
-                    fp64 = true;
-                    req = kReqFp64;          // FP64 energies of x before going on
-                    continue;
-                }
             }
 
-            if constexpr (SEQ) {
-                if (visits && vend) {
-                    // ---- end of a visit (this path's batch mode is the dense
-                    // one): record the accepted pair, then the next batch
-                    kb_v = lane == cb ? k : kb_v;
-                    if (push) dense_record(lane_value(tot, sScYc), sc, yc);
-                    int nx = cb + 1;
-                    while (nx < A.nbat && sq.cnt[nx] == 0) ++nx;
-                    if (nx >= A.nbat) {           // outer iteration done
-                        ++it;
-                        gsum_prev = gsum;
-                        if (A.anm) anm_step();
-                        req = kReqTotal;
-                        continue;
-                    }
-                    cb = nx;
-                    k = __builtin_amdgcn_readlane(kb_v, cb);
-                    req = kReqInit;
+            if constexpr (DENSE) if (vend) {
+                // ---- end of a visit: record the accepted pair, then the next
+                // batch
+                kb_v = lane == cb ? k : kb_v;
+                if (push) dense_record(lane_value(tot, sScYc), sc, yc);
+                int nx = cb + 1;
+                while (nx < A.nbat && sq.cnt[nx] == 0) ++nx;
+                if (nx >= A.nbat) {           // outer iteration done
+                    ++it;
+                    gsum_prev = gsum;
+                    if (A.anm) anm_step();
+                    req = kReqTotal;
                     continue;
                 }
-                if (!visits && A.anm && it > anm_it) {
-                    // one batch: ANM after every iteration; changed lists
-                    // re-evaluate the current point over the new lists
-                    anm_it = it;
-                    if (anm_step()) { req = kReqInit; continue; }
-                }
+                cb = nx;
+                k = __builtin_amdgcn_readlane(kb_v, cb);
+                req = kReqInit;
+                continue;
             }
 
-            // ================= top of an iteration: stop tests =================
+            // ================= a visit's first evaluation ======================
+            // its gradient norm joins the sum
             const float gg = sh.Bm[cur][DENSE ? kG * kNB + kG : 0];
             const float gn = sqrtf(fmaxf(gg, 0.f));
-            if (SEQ && visits) {
-                // a visit's first evaluation: its gradient norm joins the sum
-                gsum += gn;
-                ++nvis;
-            } else {
-                const double Eacc = fp64 ? E64o : (double)E;
-                if (!isfinite(E) || !isfinite(gn)) { status = 6; break; }
-                if (fp64 && E64t < A.e_feasible) { status = 1; break; }
-                if (gn <= A.g_tol) { status = 2; break; }
-                if (A.ftol > 0.f && it >= W && decreased_too_little(Eacc, (it - W) % (W + 1), A.ftol)) { status = 3; break; }
-                if (lane == it % (W + 1)) ehist = Eacc;
-                if (it >= A.max_iter) { status = 5; break; }
-            }
+            gsum += gn;
+            ++nvis;
 
             // ================= direction: p = -H_p g (Eq. 8) ==================
             gp = dense_direction();
             if (k > 0 && !(gp < 0.f)) {
                 k = 0;
-                if constexpr (DENSE) dense_reset();
+                dense_reset();
 #pragma unroll
                 for (int c = 0; c < kCPT; ++c)
-                    p[c] = (!SEQ || !visits || batc_of(c) == cb) ? make_float2(-g[c].x, -g[c].y)
-                                                              : make_float2(0.f, 0.f);
+                    p[c] = batc_of(c) == cb ? make_float2(-g[c].x, -g[c].y) : make_float2(0.f, 0.f);
                 gp = -gg;
             }
             if (k > 0) alpha = 1.f;

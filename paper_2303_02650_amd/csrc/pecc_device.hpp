@@ -95,13 +95,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-__device__ __forceinline__ double wave_max(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
 __device__ __forceinline__ int wave_sum(int v)
 {
 #pragma unroll
@@ -159,22 +152,6 @@ __device__ __forceinline__ T block_sum(T v, T *tmp)
     T s = tmp[0];
 #pragma unroll
     for (int i = 1; i < NW; ++i) s += tmp[i];
-    return s;
-}
-
-template <int BLOCK>
-__device__ __forceinline__ double block_max(double v, double *tmp)
-{
-    constexpr int NW = BLOCK / kWave;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = threadIdx.x / kWave;
-    v = wave_max(v);
-    __syncthreads();
-    if (lane == 0) tmp[w] = v;
-    __syncthreads();
-    double s = tmp[0];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) s = fmax(s, tmp[i]);
     return s;
 }
 

@@ -911,11 +911,9 @@ __device__ __forceinline__ double sqrt64_from32(double m2, float l32, float il)
 // and a zero term without a test of their own) and l2, the seeds of
 // pair_term64s.
 __device__ __forceinline__ float pair_term32s(float2 q, float2 pj, bool count_e, float two_r,
-                                              float four_r2, float four_r2_band, float &e,
-                                              float &e1, float &gx, float &gy, float &l2o,
-                                              bool want_e1 = true)
+                                              float four_r2, float &e, float &e1, float &gx,
+                                              float &gy, float &l2o, bool want_e1 = true)
 {
-    (void)four_r2_band;
     const float dx = q.x - pj.x, dy = q.y - pj.y;
     const float l2 = dot2(dx, dx, dy, dy);
     const bool ov = l2 < four_r2;
