@@ -336,9 +336,9 @@ __device__ __forceinline__ uint32_t ring_entry(int hd, int l)
 // instance's results have the same bits in all of them.
 // Waves per SIMD the registers are limited to.  Two is what the history of
 // two circles per thread leaves (one workgroup of 512 per CU).  With one
-// circle per thread the whole-instance descent fits two workgroups of 512 at
-// 128 registers, three of 256 at 168; the adjustment and the batch descent
-// would spill there.
+// circle per thread the whole-instance descent holds two workgroups of 512 at
+// 128 registers and three of 256 at 168, with 44 and 52 bytes per lane spilled;
+// the adjustment and the batch descent would spill more there.
 constexpr int descend_waves(int mode, int block, int cpt)
 {
     return mode != kModeWhole || cpt == 2 || block < 256 ? 2 : block == 256 ? 3 : 4;

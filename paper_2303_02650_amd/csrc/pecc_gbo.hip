@@ -41,12 +41,17 @@
 // bits.  Eight waves take up to eight batches of a colour at once, and share
 // the lists, energies and moves; the instance's sums keep the order of four
 // waves of four circles per thread.  64 instances of n = 1000 in 4 x 4 blocks,
-// 300 outer iterations: 16.7 ms (16.9 with three neighbors per turn, 17.6 with
-// four, 17.3 with eight, 18.3 with twelve: a list has five to twelve, and
-// places past its end cost their terms); with four waves 17.8 ms, and 24.5 ms
-// with one load or neighbor at a time.  64 instances of n = 900 in 6 x 6
-// blocks, 100 outer iterations: 7.05 ms, 10.5 ms with four waves.  Loading the
-// next visit's history ahead gained under 1 % more (not kept).
+// 300 outer iterations: 16.7 ms; with four waves 17.8 ms, and 24.5 ms with one
+// load or neighbor at a time.  64 instances of n = 900 in 6 x 6 blocks, 100
+// outer iterations: 7.05 ms, 10.5 ms with four waves.  Loading the next visit's
+// history ahead gained under 1 % more (not kept).
+// Neighbors per turn were chosen by time alone, at n = 1000 in 4 x 4 blocks: 16.9
+// ms with three, 17.6 with four, 16.7 with six, 17.3 with eight, 18.3 with
+// twelve (a list has five to twelve, so places past its end cost their terms,
+// but that does not order these figures).  At two waves per SIMD a visit does
+// not fit its 256 registers: 112 bytes per lane are spilled (with three to
+// eight neighbors; 144 with twelve), 164 with FP64 sweeps; four waves of the
+// same code had room for all of it.
 #include "pecc_device.hpp"
 #include "pecc_host.hpp"
 #include "pecc_launch.hpp"
@@ -109,7 +114,7 @@ __host__ __device__ inline size_t gbo_instance_bytes(int nbat)
 
 // Neighbor lists at the current positions: the circles sorted into cells, and
 // of every circle the neighbors (predicate near64 with c2) in the order of the
-// cells.  Mask bits over the sorted positions (neighbor_masks), the four circles
+// cells.  Mask bits over the sorted positions (neighbor_masks), the two circles
 // of a thread side by side; a wave with a circle that has more candidates than
 // a mask holds goes through them one by one.  Returns whether some list is too long.
 __device__ __forceinline__ bool gbo_build(GboShared &sh, int tid, int n, const Grid &grid, double c2)
@@ -348,7 +353,7 @@ __global__ __launch_bounds__(kGT) void gbo_descend_kernel(
                     ec[u] = 0.f;
                     etc[u] = 0.0;
                 }
-                // every pair once, at its lower circle; a thread's four circles
+                // every pair once, at its lower circle; a thread's two circles
                 // side by side, two neighbors each in flight (a neighbor that
                 // does not count stands beyond everything and adds zeros)
                 auto visit_pair = [&](float2 q, float2 pj, float &ecu, double &etu) {
