@@ -948,7 +948,6 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         float Rz = R, gR = 0.f, pR = 0.f, lam = ADJ ? A.lambda0 : 0.f;
         float hR_v = 0.f;
         int iters_all = 0;
-        bool ended = false;               // (uniform, unlike status) no further round
         for (int round = 0;; ++round) {
         if constexpr (ADJ) {
             if (round >= A.rounds) break;
@@ -1615,7 +1614,6 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                 }
                 if constexpr (SEQ)
                     if (fl & kDecAnm) anm_compare();                    // every wave
-                if constexpr (ADJ) ended = (fl & kDecEnd) != 0;
                 if (fl & kDecStop) break;
                 if (fl & kDecNext) continue;
                 // ---- direction p = -(gamma g + sum_j cs_j s_j + cy_j y_j),
@@ -1760,7 +1758,9 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         }
         iters_all += it;
         if constexpr (!ADJ) break;
-        if (ended) break;                        // NONFINITE ends the adjustment
+        // NONFINITE ends the adjustment, for every wave (only the deciding one
+        // knows the status; the word stands until the next round's evaluation)
+        if (__builtin_amdgcn_readfirstlane(sh.dec.x) & kDecEnd) break;
         lam *= 0.5f;
         }   // rounds
 
