@@ -277,7 +277,7 @@ struct NoShared {
 enum : int { kReqInit = 0, kReqFp64 = 1, kReqTrial = 2, kReqTotal = 3 };
 // outcome of an evaluation in the whole-instance descent
 enum : int { kDecAccept = 1, kDecPush = 2, kDecStop = 4, kDecNext = 8, kDecSteepest = 16, kDecAnm = 32,
-             kDecFp64 = 64, kDecEnd = 128 };   // kDecEnd: NONFINITE, no further round
+             kDecFp64 = 64 };
 constexpr int kDecReq = 8, kDecBatch = 16;   // bit positions of the request and the batch
 
 // Gram ring with pair 0 at storage pair hd: where lane l (basis vector l in
@@ -337,8 +337,8 @@ __device__ __forceinline__ uint32_t ring_entry(int hd, int l)
 // Waves per SIMD the registers are limited to.  Two is what the history of
 // two circles per thread leaves (one workgroup of 512 per CU).  With one
 // circle per thread the whole-instance descent holds two workgroups of 512 at
-// 128 registers and three of 256 at 168, with 44 and 52 bytes per lane spilled;
-// the adjustment and the batch descent would spill more there.
+// 128 registers and three of 256 at 168 (the latter spill 44 bytes per lane);
+// the adjustment and the batch descent would spill there.
 constexpr int descend_waves(int mode, int block, int cpt)
 {
     return mode != kModeWhole || cpt == 2 || block < 256 ? 2 : block == 256 ? 3 : 4;
@@ -948,6 +948,8 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         float Rz = R, gR = 0.f, pR = 0.f, lam = ADJ ? A.lambda0 : 0.f;
         float hR_v = 0.f;
         int iters_all = 0;
+        // (no rounds: the result reads the cleared ring)
+        if constexpr (ADJ) __syncthreads();
         for (int round = 0;; ++round) {
         if constexpr (ADJ) {
             if (round >= A.rounds) break;
@@ -1548,7 +1550,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
                             float cf, gam;
                             const float gpv = two_loop(Bc, live ? rho_l : 0.f, cf, gam);
                             if (status != 0) {
-                                fl |= kDecStop | (status == 6 ? kDecEnd : 0);
+                                fl |= kDecStop;
                             } else {
                                 gp = gpv;
                                 if constexpr (ADJ) {
@@ -1758,9 +1760,11 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
         }
         iters_all += it;
         if constexpr (!ADJ) break;
-        // NONFINITE ends the adjustment, for every wave (only the deciding one
-        // knows the status; the word stands until the next round's evaluation)
-        if (__builtin_amdgcn_readfirstlane(sh.dec.x) & kDecEnd) break;
+        // NONFINITE ends the adjustment, for every wave: only the deciding one
+        // knows the status, and leaves it in the decision's spare word
+        if (tid == 0) sh.dec.w = status;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(sh.dec.w) == 6) break;
         lam *= 0.5f;
         }   // rounds
 
@@ -1778,8 +1782,7 @@ __global__ __launch_bounds__(BLOCK, descend_waves(MODE, BLOCK, CPT)) void lbfgs_
             // with the radius as a variable, E reports the energy without
             // the penalty (the last lambda was halved once more after the round)
             r.E32 = (ADJ && A.rounds > 0) ? E - 2.f * lam * Rz * Rz : E;
-            // (no round: no evaluation, and the ring is not there to be read)
-            r.gnorm = ADJ && A.rounds == 0 ? 0.f : sqrtf(fmaxf(SOLO ? sh.Bring[SOLO ? kG * kRS + 4 * kMM : 0] : sh.Bm[cur][SOLO ? 0 : kG * kNB + kG], 0.f));
+            r.gnorm = sqrtf(fmaxf(SOLO ? sh.Bring[SOLO ? kG * kRS + 4 * kMM : 0] : sh.Bm[cur][SOLO ? 0 : kG * kNB + kG], 0.f));
             r.E64 = fp64 ? E64t : -1.0;
             if (SEQ && visits) {
                 // outer iterations; whole-instance energies; the sum of the
