@@ -75,7 +75,8 @@ struct DescentShared {
     // what the deciding wave leaves for the others: kDec* bits, what the
     // next evaluation is for, the FP64 regime and the batch of the next
     // evaluation (packed, see kDecReq), its step length, gamma of the
-    // direction; the coefficients of s_j, then of y_j in the direction
+    // direction, the status of an adjustment's round after its end; the
+    // coefficients of s_j, then of y_j in the direction
     int4 dec;
     float4 coef[2 * kMM / 4];
     // the constants of the decisions, read where used (kept in registers
